@@ -1,11 +1,12 @@
 // Per-tile rasterisation: front-to-back compositing and its adjoint.
 //
-// One wavefront (64 lanes) per tile.  Lane l owns the pixels of column
-// l % TW in rows l / TW + k * (64 / TW), k < TW * TH / 64 (a 16x16 tile gives
-// each lane a strip of 4 pixels).  The tile's sorted records are staged
-// through LDS 64 at a time (one per lane); every lane then walks the batch.
-// Because a lane's pixels share one column, dx = px - mx is shared and the
-// quadratic form costs r = A + dy (B + c dy) per pixel with A, B per record.
+// One wavefront (64 lanes) per tile, or per band of TH / SPLIT rows of it in
+// frames of few tiles.  Lane l owns the pixels of column l % TW in rows
+// l / TW + k * (64 / TW) of its band (a whole 16x16 tile gives each lane a
+// strip of 4 pixels).  The tile's sorted records are staged through LDS 64 at
+// a time (one per lane); every lane then walks the batch.  Because a lane's
+// pixels share one column, dx = px - mx is shared and the quadratic form
+// costs r = A + dy (B + c dy) per pixel with A, B per record.
 //
 // Forward: a pixel stops before the first record that would take its
 // transmittance below 1e-4; the wavefront stops when all its pixels have.
@@ -15,6 +16,13 @@
 // its ten per-record sums onto fewer lanes with lane swaps, finishes them
 // with DPP sums within 16-lane rows and half-rows, and ten lanes add the
 // ten totals to the record's accumulator in one atomic instruction.
+//
+// Both passes are bound by vector instruction issue; the forward's 64-pixel
+// strip costs 4 instructions for the support test and, for the 2.6 of a
+// tile's four strips that a record's ellipse reaches, 13 plus two
+// transcendentals inside it (1M 7-D primitives at 1080p 63.0 -> 58.7 us, 1M
+// 6-D 115 -> 107 us with the selects of the stop and skip tests replaced by
+// lane masks and stopped pixels left out by their NaN row).
 //
 // Both passes take every per-pixel decision (support test, skip, stop)
 // through the same inline functions, so the backward pass visits exactly
@@ -46,6 +54,17 @@ __device__ __forceinline__ Staged stage_record(const float* __restrict__ records
   return s;
 }
 
+// Whether a record may reach the pixel centres with rows in [y0, y1]: the
+// half-height sqrt(rho a / det) of {r <= rho}, widened by 1 % and a pixel (a
+// determinant that cancels in float32, or is no number, keeps the record).
+__device__ __forceinline__ bool may_reach_rows(const Staged& s, float y0, float y1) {
+  const float a = s.g0.z, b = 0.5f * s.g0.w, c = s.g1.x, rho = s.g1.y;
+  const float det = a * c - b * b;
+  if (!(det > 1e-3f * (a * c))) return true;
+  const float h = 1.01f * sqrtf(rho * a / det) + 1.0f;
+  return !(s.g0.y + h < y0) && !(s.g0.y - h > y1);
+}
+
 // Column terms of the quadratic form for one record and one lane:
 // r = a dx^2 + 2 b dx dy + c dy^2 = A + dy (B + c dy), A = dx (a dx), B = 2b dx.
 struct ColTerms {
@@ -75,86 +94,114 @@ __device__ __forceinline__ int view_of_tile(const DevView* __restrict__ views, i
   return lo;
 }
 
-template <int TW, int TH>
+// SPLIT wavefronts share a tile, each one a band of TH / SPLIT rows.
+template <int TW, int TH, int SPLIT>
 struct TileGeom {
-  static constexpr int PPL = TW * TH / 64;   // pixels per lane
+  static constexpr int ROWS = TH / SPLIT;    // rows of a wavefront's band
+  static constexpr int PPL = TW * ROWS / 64; // pixels per lane
   static constexpr int RSTEP = 64 / TW;      // rows between a lane's pixels
-  static_assert(TW * TH % 64 == 0 && 64 % TW == 0, "tile shape");
+  static_assert(TH % SPLIT == 0 && TW * ROWS % 64 == 0 && 64 % TW == 0, "tile shape");
 };
 
-template <int TW, int TH, int BATCH>
+template <int TW, int TH, int BATCH, int SPLIT>
 __device__ __forceinline__ void raster_fwd_tile(
-    uint32_t tile, float4* s0, float4* s1, float4* s2, const float* __restrict__ records,
+    uint32_t tile, int band, float4* s0, float4* s1, float4* s2, const float* __restrict__ records,
     const uint32_t* __restrict__ values, const uint32_t* __restrict__ ranges,
     const DevView* __restrict__ views, int n_views, float* __restrict__ image,
     float* __restrict__ t_ws, float* __restrict__ t_user, uint32_t* __restrict__ ncontrib) {
-  constexpr int PPL = TileGeom<TW, TH>::PPL;
-  constexpr int RSTEP = TileGeom<TW, TH>::RSTEP;
+  constexpr int PPL = TileGeom<TW, TH, SPLIT>::PPL;
+  constexpr int RSTEP = TileGeom<TW, TH, SPLIT>::RSTEP;
   constexpr int PER_LANE = BATCH / 64;
   const int lane = threadIdx.x;
   const DevView& V = views[view_of_tile(views, n_views, tile)];
   const uint32_t lt = tile - V.tile_base;
   const int ty = int(lt) / V.tiles_x, tx = int(lt) - ty * V.tiles_x;
   const int px = tx * TW + lane % TW;
-  const int py0 = ty * TH + lane / TW;
+  const int py0 = ty * TH + band * TileGeom<TW, TH, SPLIT>::ROWS + lane / TW;
   const float fx = float(px) + 0.5f;
-  // T: transmittance; a pixel that has stopped keeps it negated, so that
-  // every later record fails its T (1 - alpha) >= 1e-4 test (instead of the
-  // pixel's state being tested on every record); |T| is the final value
-  // (pixels outside the image start stopped)
-  float T[PPL], cr[PPL], cg[PPL], cb[PPL];
+  // fy: the pixels' row coordinates.  A pixel that has stopped (or lies
+  // outside the image) gets a NaN row: its r is NaN, so the support test
+  // fails for every later record without a test of its own, and a record is
+  // skipped whole where its only pixels have stopped
+  float T[PPL], fy[PPL], cr[PPL], cg[PPL], cb[PPL];
   uint32_t last[PPL];
 #pragma unroll
   for (int k = 0; k < PPL; ++k) {
-    T[k] = (px >= V.W || py0 + k * RSTEP >= V.H) ? -1.0f : 1.0f;
+    T[k] = 1.0f;
+    fy[k] = (px >= V.W || py0 + k * RSTEP >= V.H) ? __builtin_nanf("")
+                                                  : float(py0 + k * RSTEP) + 0.5f;
     cr[k] = cg[k] = cb[k] = 0.0f; last[k] = 0;
   }
+  const float band_y0 = float(ty * TH + band * TileGeom<TW, TH, SPLIT>::ROWS) + 0.5f;
+  const float band_y1 = band_y0 + float(TileGeom<TW, TH, SPLIT>::ROWS - 1);
   const uint32_t start = ranges[2 * size_t(tile)], end = ranges[2 * size_t(tile) + 1];
   for (uint32_t b0 = start; b0 < end; b0 += BATCH) {
     // the tile is finished once every pixel has stopped (checked per batch)
     bool running = false;
 #pragma unroll
-    for (int k = 0; k < PPL; ++k) running = running || T[k] >= 0.0f;
+    for (int k = 0; k < PPL; ++k) running = running || fy[k] == fy[k];
     if (__ballot(running) == 0ull) break;
     __syncthreads();
+    // (wavefront-uniform: the record loop runs on scalar counters)
+    int nb = __builtin_amdgcn_readfirstlane(int(min(uint32_t(BATCH), end - b0)));
+    if constexpr (SPLIT == 1) {
 #pragma unroll
-    for (int m = 0; m < PER_LANE; ++m) {
-      const uint32_t idx = b0 + uint32_t(m * 64 + lane);
-      if (idx < end) {
-        const Staged st = stage_record(records, values[idx]);
-        s0[m * 64 + lane] = st.g0;
-        s1[m * 64 + lane] = st.g1;
-        s2[m * 64 + lane] = st.g2;
+      for (int m = 0; m < PER_LANE; ++m) {
+        const uint32_t idx = b0 + uint32_t(m * 64 + lane);
+        if (idx < end) {
+          const Staged st = stage_record(records, values[idx]);
+          s0[m * 64 + lane] = st.g0;
+          s1[m * 64 + lane] = st.g1;
+          s2[m * 64 + lane] = st.g2;
+        }
       }
+    } else {
+      // only the records that may reach the band, their positions with them
+      bool keep = lane < nb;
+      Staged st;
+      if (keep) {
+        st = stage_record(records, values[b0 + uint32_t(lane)]);
+        keep = may_reach_rows(st, band_y0, band_y1);
+      }
+      const uint64_t kept = __ballot(keep);
+      if (keep) {
+        const int at = __popcll(kept & ((1ull << lane) - 1ull));
+        st.g2.w = __uint_as_float(b0 - start + uint32_t(lane) + 1u);
+        s0[at] = st.g0;
+        s1[at] = st.g1;
+        s2[at] = st.g2;
+      }
+      nb = __popcll(kept);
     }
     __syncthreads();
-    // (wavefront-uniform: the record loop runs on scalar counters)
-    const int nb = __builtin_amdgcn_readfirstlane(int(min(uint32_t(BATCH), end - b0)));
+    const uint32_t pos1 = __builtin_amdgcn_readfirstlane(b0 - start + 1u);
     for (int j = 0; j < nb; ++j) {
       const float4 g0 = s0[j], g1 = s1[j], g2 = s2[j];
       const ColTerms ct = col_terms(g0, fx - g0.x);
 #pragma unroll
       for (int k = 0; k < PPL; ++k) {
-        const float dy = float(py0 + k * RSTEP) + 0.5f - g0.y;
+        const float dy = fy[k] - g0.y;
         const float r = eval_r(ct, g1.x, dy);
         if (!(r <= g1.y)) continue;
-        // one branch per pixel: skipping (alpha below 1/255) and stopping
-        // are taken by selects
         float l2;
         const float sigma = eval_sigma(r, g1.z, g1.w, &l2);
         const float alpha = fminf(kAlphaMax, sigma);
         const float test = T[k] * (1.0f - alpha);
-        const bool hit = alpha >= kAlphaMin;
-        const bool pass = test >= kTStop;
-        const bool con = hit && pass;
-        const float w = con ? alpha * T[k] : 0.0f;
-        cr[k] += g2.x * w;
-        cg[k] += g2.y * w;
-        cb[k] += g2.z * w;
-        // a hit that fails the stop test stops the pixel (T kept negated)
-        const float tn = pass ? test : -fabsf(T[k]);
-        T[k] = hit ? tn : T[k];
-        last[k] = con ? b0 - start + uint32_t(j) + 1u : last[k];
+        // (as lane masks: the update runs under the mask, without selects)
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin);
+        const uint64_t pass = __builtin_amdgcn_ballot_w64(test >= kTStop);
+        // a hit that fails the stop test stops the pixel (rare)
+        if ((hit & ~pass) != 0ull) {
+          if (__builtin_amdgcn_inverse_ballot_w64(hit & ~pass)) fy[k] = __builtin_nanf("");
+        }
+        if (__builtin_amdgcn_inverse_ballot_w64(hit & pass)) {
+          const float w = alpha * T[k];
+          cr[k] += g2.x * w;
+          cg[k] += g2.y * w;
+          cb[k] += g2.z * w;
+          T[k] = test;
+          last[k] = SPLIT == 1 ? pos1 + uint32_t(j) : __float_as_uint(g2.w);
+        }
       }
     }
   }
@@ -166,9 +213,9 @@ __device__ __forceinline__ void raster_fwd_tile(
       image[3 * pix] = cr[k];
       image[3 * pix + 1] = cg[k];
       image[3 * pix + 2] = cb[k];
-      // (the internal copy keeps the sign: negative for a pixel that stopped)
-      t_ws[pix] = T[k];
-      if (t_user) t_user[pix] = fabsf(T[k]);
+      // (the internal copy is negated for a pixel that stopped)
+      t_ws[pix] = fy[k] == fy[k] ? T[k] : -T[k];
+      if (t_user) t_user[pix] = T[k];
       ncontrib[pix] = last[k];
     }
   }
@@ -184,7 +231,7 @@ __device__ __forceinline__ uint32_t next_tile(uint32_t* work, bool first) {
   return uint32_t(__shfl(int(t), 0, 64));
 }
 
-template <int TW, int TH, int BATCH>
+template <int TW, int TH, int BATCH, int SPLIT>
 __global__ void __launch_bounds__(64) raster_fwd_kernel(
     const float* __restrict__ records, const uint32_t* __restrict__ values,
     const uint32_t* __restrict__ ranges, const DevView* __restrict__ views, int n_views,
@@ -192,9 +239,10 @@ __global__ void __launch_bounds__(64) raster_fwd_kernel(
     float* __restrict__ image, float* __restrict__ t_ws, float* __restrict__ t_user,
     uint32_t* __restrict__ ncontrib) {
   __shared__ float4 s0[BATCH], s1[BATCH], s2[BATCH];
-  for (uint32_t q = next_tile(work, true); q < n_tiles; q = next_tile(work, false))
-    raster_fwd_tile<TW, TH, BATCH>(order[q], s0, s1, s2, records, values, ranges, views, n_views,
-                                   image, t_ws, t_user, ncontrib);
+  for (uint32_t q = next_tile(work, true); q / SPLIT < n_tiles; q = next_tile(work, false))
+    raster_fwd_tile<TW, TH, BATCH, SPLIT>(order[q / SPLIT], int(q % SPLIT), s0, s1, s2, records,
+                                          values, ranges, views, n_views, image, t_ws, t_user,
+                                          ncontrib);
 }
 
 // Sums over each 16-lane row by DPP row rotations (by 1, 2, 4, 8), of N
@@ -260,8 +308,8 @@ __device__ __forceinline__ void raster_bwd_tile(
     const uint32_t* __restrict__ ncontrib, const float* __restrict__ d_image,
     const float* __restrict__ d_tfinal, const float* __restrict__ l1_image,
     const float* __restrict__ l1_target, float l1_scale, float* __restrict__ grad2d) {
-  constexpr int PPL = TileGeom<TW, TH>::PPL;
-  constexpr int RSTEP = TileGeom<TW, TH>::RSTEP;
+  constexpr int PPL = TileGeom<TW, TH, 1>::PPL;
+  constexpr int RSTEP = TileGeom<TW, TH, 1>::RSTEP;
   constexpr int PER_LANE = BATCH / 64;
   const int lane = threadIdx.x;
   const DevView& V = views[view_of_tile(views, n_views, tile)];
@@ -490,40 +538,58 @@ __global__ void reset_counter_kernel(uint32_t* __restrict__ c) {
   if (threadIdx.x == 0) *c = 0u;
 }
 
-// Launch geometry: one wavefront per tile (grid = tiles), or a persistent
-// grid of `persistent_blocks` wavefronts taking tiles from a queue; either
-// way the q-th tile handed out is order[q] (the binning's order, longest
-// tiles first).
+// Launch geometry: one wavefront per tile (or per band of one, `split` bands
+// a tile), or a persistent grid of `persistent_blocks` wavefronts taking tiles
+// from a queue; either way the q-th tile handed out is order[q] (the
+// binning's order, longest tiles first).
 struct RasterLaunch {
   uint32_t n_tiles;
   uint32_t* work;            // queue counter, or nullptr
   uint32_t grid;
   const uint32_t* order;
+  int split;
 };
 
+// Wavefronts per tile.  A frame of few tiles leaves SIMDs idle or with one
+// or two wavefronts each, and its time is the chain of its longest tile: two
+// or four wavefronts a tile, each staging only the records that may reach its
+// band, shorten that chain.  Beyond the limits the records staged and tested
+// several times cost more than that saves.  Forward only.  Measured on 16x16 tiles, one / two / four wavefronts a tile (us):
+//   forward   64 tiles 62 / 34 / 23, 1200 21 / 14 / 11, 1900 51 / 31 / 22,
+//             3072 43 / 27 / 24, 4108 68 / 43 / 46, 8160 59 / 58 / 67 and
+//             107 / 105 / 120, 14400 105 / 114 / 133
+// (the default tile shape and batch depth only: the others are the
+// autotuner's alternatives).
+constexpr uint32_t kFwdBands4 = 3072, kFwdBands2 = 8192;
+constexpr bool can_split(int tw, int th, int batch) { return tw == 16 && th == 16 && batch <= 64; }
+
 static RasterLaunch raster_geometry(uint32_t n_tiles, uint32_t* work, uint32_t persistent_blocks,
-                                    const uint32_t* order, hipStream_t st) {
-  RasterLaunch g{n_tiles, nullptr, n_tiles, order};
+                                    const uint32_t* order, uint32_t bands4, uint32_t bands2,
+                                    hipStream_t st) {
+  RasterLaunch g{n_tiles, nullptr, n_tiles, order, 1};
   if (work && persistent_blocks > 0 && persistent_blocks < n_tiles) {
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, st, work);
     g.work = work;
     g.grid = persistent_blocks;
+    return g;
   }
+  g.split = n_tiles <= bands4 ? 4 : (n_tiles <= bands2 ? 2 : 1);
+  g.grid = n_tiles * uint32_t(g.split);
   return g;
 }
 
-template <int TW, int TH, int BATCH>
+template <int TW, int TH, int BATCH, int SPLIT = 1>
 static hipError_t raster_fwd_t(const RasterLaunch& g, const float* records, const uint32_t* values,
                                const uint32_t* ranges, const DevView* views, int n_views,
                                float* image, float* t_ws, float* t_user, uint32_t* ncontrib,
                                hipStream_t st) {
-  hipLaunchKernelGGL((raster_fwd_kernel<TW, TH, BATCH>), dim3(g.grid), dim3(64), 0, st, records,
-                     values, ranges, views, n_views, g.n_tiles, g.order, g.work, image, t_ws,
-                     t_user, ncontrib);
+  hipLaunchKernelGGL((raster_fwd_kernel<TW, TH, BATCH, SPLIT>), dim3(g.grid), dim3(64), 0, st,
+                     records, values, ranges, views, n_views, g.n_tiles, g.order, g.work, image,
+                     t_ws, t_user, ncontrib);
   return hipGetLastError();
 }
 
-template <int TW, int TH, int BATCH>
+template <int TW, int TH, int BATCH, int = 1>
 static hipError_t raster_bwd_t(const RasterLaunch& g, uint32_t* grad_dirty, const float* records,
                                const uint32_t* values, const uint32_t* ranges,
                                const DevView* views, int n_views,
@@ -531,9 +597,10 @@ static hipError_t raster_bwd_t(const RasterLaunch& g, uint32_t* grad_dirty, cons
                                const float* d_tfinal, const float* l1_image,
                                const float* l1_target, float l1_scale, float* grad2d,
                                hipStream_t st) {
-  hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, BATCH>), dim3(g.grid), dim3(64), 0, st, records,
-                     values, ranges, views, n_views, g.n_tiles, g.order, g.work, grad_dirty, t_ws,
-                     ncontrib, d_image, d_tfinal, l1_image, l1_target, l1_scale, grad2d);
+  hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, BATCH>), dim3(g.grid), dim3(64), 0, st,
+                     records, values, ranges, views, n_views, g.n_tiles, g.order, g.work,
+                     grad_dirty, t_ws, ncontrib, d_image, d_tfinal, l1_image, l1_target, l1_scale,
+                     grad2d);
   return hipGetLastError();
 }
 
@@ -541,6 +608,8 @@ static hipError_t raster_bwd_t(const RasterLaunch& g, uint32_t* grad_dirty, cons
   do {                                                                                 \
     const int bd = batch <= 64 ? 64 : (batch <= 128 ? 128 : 256);                      \
     if (tw == 16 && th == 16) {                                                        \
+      if (bd == 64 && g.split == 4) return FN<16, 16, 64, 4>(__VA_ARGS__);             \
+      if (bd == 64 && g.split == 2) return FN<16, 16, 64, 2>(__VA_ARGS__);             \
       if (bd == 64) return FN<16, 16, 64>(__VA_ARGS__);                                \
       if (bd == 128) return FN<16, 16, 128>(__VA_ARGS__);                              \
       return FN<16, 16, 256>(__VA_ARGS__);                                             \
@@ -570,7 +639,9 @@ hipError_t launch_raster_fwd(int tw, int th, int batch, uint32_t persistent_bloc
                              uint32_t n_tiles, float* image, float* t_ws, float* t_user,
                              uint32_t* ncontrib, hipStream_t st) {
   if (n_tiles == 0) return hipSuccess;
-  const RasterLaunch g = raster_geometry(n_tiles, work, persistent_blocks, order, st);
+  const bool split = can_split(tw, th, batch);
+  const RasterLaunch g = raster_geometry(n_tiles, work, persistent_blocks, order,
+                                         split ? kFwdBands4 : 0u, split ? kFwdBands2 : 0u, st);
   UBS_TILE_DISPATCH(raster_fwd_t, g, records, values, ranges, views, n_views, image, t_ws, t_user,
                     ncontrib, st);
 }
@@ -585,7 +656,7 @@ hipError_t launch_raster_bwd(int tw, int th, int batch, uint32_t persistent_bloc
                              const float* l1_target, float l1_scale, float* grad2d,
                              hipStream_t st) {
   if (n_tiles == 0) return hipSuccess;
-  const RasterLaunch g = raster_geometry(n_tiles, work, persistent_blocks, order, st);
+  const RasterLaunch g = raster_geometry(n_tiles, work, persistent_blocks, order, 0u, 0u, st);
   UBS_TILE_DISPATCH(raster_bwd_t, g, grad_dirty, records, values, ranges, views, n_views, t_ws,
                     ncontrib, d_image, d_tfinal, l1_image, l1_target, l1_scale, grad2d, st);
 }
