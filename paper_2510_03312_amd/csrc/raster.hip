@@ -13,16 +13,18 @@
 // Backward: each tile is walked back to front from the last contributor;
 // the transmittance in front of a record is recovered by division.  A lane
 // first sums the gradient terms of its own pixels; the wavefront then folds
-// its ten per-record sums onto fewer lanes with lane swaps, finishes them
-// with DPP sums within 16-lane rows and half-rows, and ten lanes add the
-// ten totals to the record's accumulator in one atomic instruction.
+// the ten per-record sums of two records onto fewer lanes with lane swaps,
+// finishes them with DPP sums within 16-lane rows and banks, and twenty lanes
+// add the totals to the records' accumulators in one atomic instruction.
 //
-// Both passes are bound by vector instruction issue; the forward's 64-pixel
-// strip costs 4 instructions for the support test and, for the 2.6 of a
-// tile's four strips that a record's ellipse reaches, 13 plus two
-// transcendentals inside it (1M 7-D primitives at 1080p 63.0 -> 58.7 us, 1M
-// 6-D 115 -> 107 us with the selects of the stop and skip tests replaced by
-// lane masks and stopped pixels left out by their NaN row).
+// Both passes are bound by vector instruction issue (the per-pixel code runs
+// for the 2.6 of a tile's four 64-pixel strips that a record's ellipse
+// reaches, with half the lanes inside it), so they are counted in
+// instructions: a strip costs the forward 4 for the support test and 13 plus
+// two transcendentals inside it, the backward 4 and 23 plus four, and a
+// record 23 more in the backward for its wavefront sums.  1M 7-D primitives
+// at 1080p, before and after the present forms: forward 63.0 -> 58.7 us,
+// backward 132 -> 121 us; 1M 6-D 115 -> 107 and 247 -> 224 us.
 //
 // Both passes take every per-pixel decision (support test, skip, stop)
 // through the same inline functions, so the backward pass visits exactly
@@ -299,25 +301,27 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
 }
 
 // HAS_DT: a gradient of the final transmittance is given (d_tfinal).
-template <int TW, int TH, int BATCH, bool HAS_DT>
+template <int TW, int TH, int BATCH, int SPLIT, bool HAS_DT>
 __device__ __forceinline__ void raster_bwd_tile(
-    uint32_t tile, float4* s0, float4* s1, float4* s2,
+    uint32_t tile, int band, float4* s0, float4* s1, float4* s2, uint32_t* s_pos,
     const float* __restrict__ records,
     const uint32_t* __restrict__ values, const uint32_t* __restrict__ ranges,
     const DevView* __restrict__ views, int n_views, const float* __restrict__ t_ws,
     const uint32_t* __restrict__ ncontrib, const float* __restrict__ d_image,
     const float* __restrict__ d_tfinal, const float* __restrict__ l1_image,
     const float* __restrict__ l1_target, float l1_scale, float* __restrict__ grad2d) {
-  constexpr int PPL = TileGeom<TW, TH, 1>::PPL;
-  constexpr int RSTEP = TileGeom<TW, TH, 1>::RSTEP;
+  constexpr int PPL = TileGeom<TW, TH, SPLIT>::PPL;
+  constexpr int RSTEP = TileGeom<TW, TH, SPLIT>::RSTEP;
   constexpr int PER_LANE = BATCH / 64;
   const int lane = threadIdx.x;
   const DevView& V = views[view_of_tile(views, n_views, tile)];
   const uint32_t lt = tile - V.tile_base;
   const int ty = int(lt) / V.tiles_x, tx = int(lt) - ty * V.tiles_x;
   const int px = tx * TW + lane % TW;
-  const int py0 = ty * TH + lane / TW;
+  const int py0 = ty * TH + band * TileGeom<TW, TH, SPLIT>::ROWS + lane / TW;
   const float fx = float(px) + 0.5f;
+  const float band_y0 = float(ty * TH + band * TileGeom<TW, TH, SPLIT>::ROWS) + 0.5f;
+  const float band_y1 = band_y0 + float(TileGeom<TW, TH, SPLIT>::ROWS - 1);
   const uint32_t start = ranges[2 * size_t(tile)];
   // gTf: d loss / d T_final times T_final (the transmittance gradient enters
   // every record's d alpha as - gTf / (1 - alpha)); D: the pixel's colour
@@ -363,26 +367,51 @@ __device__ __forceinline__ void raster_bwd_tile(
   // only records at or beyond the smallest last contributor of a stopped
   // pixel need the position test.
   const uint32_t stop_min = __builtin_amdgcn_readfirstlane(wave_min_u32(lane_stop));
+  // the field this lane adds for a pair of records (add_pair), or -1
+  int out_field = -1;
+  if ((lane & 3) == 0)
+    out_field = 4 * ((lane >> 2) & 1) + 2 * ((lane >> 3) & 1) + (lane >> 5);
+  else if ((lane & 15) == 1)
+    out_field = 8 + (lane >> 5);
   for (uint32_t hi = span; hi > 0;) {
     const uint32_t lo = hi > uint32_t(BATCH) ? hi - uint32_t(BATCH) : 0u;
-    const uint32_t cnt = hi - lo;
+    uint32_t cnt = hi - lo;
     __syncthreads();
+    if constexpr (SPLIT == 1) {
 #pragma unroll
-    for (int m = 0; m < PER_LANE; ++m) {
-      const uint32_t q = uint32_t(m * 64 + lane);
-      if (q < cnt) {
-        const Staged st = stage_record(records, values[start + lo + q]);
-        s0[q] = st.g0;
-        s1[q] = st.g1;
-        s2[q] = st.g2;
+      for (int m = 0; m < PER_LANE; ++m) {
+        const uint32_t q = uint32_t(m * 64 + lane);
+        if (q < cnt) {
+          const Staged st = stage_record(records, values[start + lo + q]);
+          s0[q] = st.g0;
+          s1[q] = st.g1;
+          s2[q] = st.g2;
+        }
       }
+    } else {
+      // only the records that may reach the band
+      bool keep = uint32_t(lane) < cnt;
+      Staged st;
+      if (keep) {
+        st = stage_record(records, values[start + lo + uint32_t(lane)]);
+        keep = may_reach_rows(st, band_y0, band_y1);
+      }
+      const uint64_t kept = __ballot(keep);
+      if (keep) {
+        const int at = __popcll(kept & ((1ull << lane) - 1ull));
+        s0[at] = st.g0;
+        s1[at] = st.g1;
+        s2[at] = st.g2;
+        s_pos[at] = lo + uint32_t(lane);
+      }
+      cnt = uint32_t(__popcll(kept));
     }
     __syncthreads();
-    // one record: the lane's pixel sums, then their wavefront totals added to
-    // the record's gradient row (CHECK: test each pixel's last contributor)
-    auto record = [&](auto check, int j) {
+    // one record: the lane's pixel sums, folded (CHECK: test each pixel's last
+    // contributor)
+    auto record = [&](auto check, int j, float* h) {
       constexpr bool CHECK = decltype(check)::value;
-      const uint32_t pos = lo + uint32_t(j);
+      const uint32_t pos = SPLIT == 1 ? lo + uint32_t(j) : s_pos[j];
       const float4 g0 = s0[j], g1 = s1[j], g2 = s2[j];
       const float dx = fx - g0.x;
       const ColTerms ct = col_terms(g0, dx);
@@ -401,18 +430,11 @@ __device__ __forceinline__ void raster_bwd_tile(
       for (int k = 0; k < PPL; ++k) {
         const float dy = float(py0 + k * RSTEP) + 0.5f - g0.y;
         const float r = eval_r(ct, g1.x, dy);
-        // one branch per pixel: the rare cases inside it (alpha below
-        // 1/255 at the support's rim, sigma at the 0.99 clamp) are taken
-        // by zeroing alpha or sigma, which makes their updates no-ops
         if (!((!CHECK || pos < last[k]) && r <= g1.y)) continue;
         float l2;
-        const float sigma0 = eval_sigma(r, g1.z, g1.w, &l2);
-        const bool con = fminf(kAlphaMax, sigma0) >= kAlphaMin;
-        const float alpha = con ? fminf(kAlphaMax, sigma0) : 0.0f;
-        // sigma where alpha follows it (below the clamp), else 0
-        const float sigma = alpha < kAlphaMax ? alpha : 0.0f;
-        // (alpha = 0 gives ioma = 1 exactly: the hardware reciprocal is exact
-        // on powers of two, so T passes unchanged)
+        const float sigma = eval_sigma(r, g1.z, g1.w, &l2);
+        const float alpha = fminf(kAlphaMax, sigma);
+        if (!(alpha >= kAlphaMin)) continue;   // (the support's rim)
         const float ioma = fast_rcp(1.0f - alpha);
         const float Ti = T[k] * ioma;
         const float w = alpha * Ti;
@@ -422,9 +444,13 @@ __device__ __forceinline__ void raster_bwd_tile(
         // g . (c - S): the colour gradient g dotted with the record's colour
         // minus the colour S composited behind it; S updates as
         // S += alpha (c - S), so D = g . S as D += alpha dot
-        const float dot = (gR[k] * g2.x + gG[k] * g2.y + gB[k] * g2.z) - D[k];
-        const float dalpha = HAS_DT ? Ti * dot - gTf[k] * ioma : Ti * dot;
-        const float sd = sigma * dalpha;
+        const float dot = gR[k] * g2.x + (gG[k] * g2.y + (gB[k] * g2.z - D[k]));
+        D[k] += alpha * dot;
+        T[k] = Ti;
+        // sigma follows alpha below the 0.99 clamp: s = sigma d alpha with
+        // sigma d alpha = alpha T dot = w dot there, and nothing at the clamp
+        if (!(alpha < kAlphaMax)) continue;
+        const float sd = HAS_DT ? w * dot - alpha * (gTf[k] * ioma) : w * dot;
         a_o += sd;
         a_be += sd * l2;
         const float q = sd * fast_rcp(1.0f - r);
@@ -432,84 +458,89 @@ __device__ __forceinline__ void raster_bwd_tile(
         const float qy = q * dy;
         a_dry += qy;
         a_dryy += qy * dy;
-        D[k] += alpha * dot;
-        T[k] = Ti;
       }
-      // the record's pixel sums (a record none of whose pixels contribute,
-      // a few in a hundred thousand, adds zeros) (P, Q, U, V, E, A_o, A_b, colour): the
-      // per-primitive adjoint turns them into record-field gradients
-      float gv[kGradFloats];
-      gv[0] = dx * a_dr;
-      gv[1] = a_dry;
-      gv[2] = dx * gv[0];
-      gv[3] = dx * a_dry;
-      gv[4] = a_dryy;
-      gv[5] = a_o;
-      gv[6] = a_be;
-      gv[7] = a_r;
-      gv[8] = a_g;
-      gv[9] = a_b;
-      // sums over the wavefront: halves folded onto each other (permlane32
-      // swap: field 2p in lanes 0-31, 2p+1 in lanes 32-63), row pairs folded
-      // (permlane16 swap: one field per row), then DPP sums within rows and
-      // half-rows
-      float h[5];
+      // the record's pixel sums P, Q, U, V, E, A_o, A_b and colour (zeros for
+      // a record none of whose pixels contribute, a few in a hundred
+      // thousand; the per-primitive adjoint turns them into record-field
+      // gradients), the wavefront's halves folded onto each other: field 2p
+      // in lanes 0-31 of h[p], field 2p+1 in lanes 32-63
+      const float gv0 = dx * a_dr;
+      const float gv[kGradFloats] = {gv0, a_dry, dx * gv0, dx * a_dry, a_dryy,
+                                     a_o, a_be,  a_r,      a_g,        a_b};
 #pragma unroll
       for (int p = 0; p < 5; ++p) {
         const FPair sw = swap_halves(gv[2 * p], gv[2 * p + 1]);
         h[p] = sw.a + sw.b;
       }
-      float t3[3];
-      {
-        const FPair s0 = swap_rows(h[0], h[1]);   // rows: fields 0, 2, 1, 3
-        const FPair s1 = swap_rows(h[2], h[3]);   // rows: fields 4, 6, 5, 7
-        t3[0] = s0.a + s0.b;
-        t3[1] = s1.a + s1.b;
-        t3[2] = h[4];   // rows: fields 8, 8, 9, 9, each row a partial sum
+    };
+    // two records' folded sums to their totals, added to their gradient rows.
+    // Every step but the last two halves the number of registers, as a step
+    // of two registers is one of each half, row, half-row or bank; a single
+    // record's ten fields leave the later steps half empty (31 vector
+    // instructions a record and an atomic instruction each, against 24 and
+    // half an atomic instruction for two at a time).
+    auto add_pair = [&](const float* ha, const float* hb, int ja, int jb) {
+      float t[5];   // rows: field 2p of a, of b, field 2p + 1 of a, of b
+#pragma unroll
+      for (int p = 0; p < 5; ++p) {
+        const FPair sw = swap_rows(ha[p], hb[p]);
+        t[p] = sw.a + sw.b;
       }
-      // t3[0] and t3[1] share one register from here: pairs of lanes 8
-      // apart are summed in each, half-rows take t3[0]'s (lanes 0-7) or
-      // t3[1]'s (8-15) sums, and a half-row mirror and two quad
-      // permutations finish the 8-lane sums; t3[2] is summed over its rows
-      float x0 = t3[0] + dpp_row<0x128>(t3[0]), x1 = t3[1] + dpp_row<0x128>(t3[1]);
-      asm volatile("" : "+v"(x0), "+v"(x1));   // (both sums, then a select, not a branch)
-      float u = (lane & 8) ? x1 : x0;
-      u += dpp_row<0x141>(u);   // lane l of a half-row and lane 7 - l
-      u += dpp_row<0x4E>(u);    // quad permutation [2, 3, 0, 1]
-      u += dpp_row<0xB1>(u);    // quad permutation [1, 0, 3, 2]
-      row_sum_all<1>(&t3[2]);
-      // rows 1 and 3 add the totals of rows 0 and 2 (DPP row broadcast of
-      // each row's lane 15 into the next row; rows 0 and 2 are not written):
-      // fields 8 and 9 complete.  (One DPP add: the compiler would build it
-      // from a move and an add.  The nop gives the two wait states a DPP
-      // read needs after the VALU write of its source.)
-      asm volatile("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf"
-                   : "+v"(t3[2]));
-      // keep the last DPP adds ahead of the branch (sunk into it, an add
-      // could no longer take its operand through DPP)
-      asm volatile("" : "+v"(u), "+v"(t3[2]));
-      // one atomic instruction: lanes 7 + 8k add the eight totals of u, lanes
-      // 22 and 54 (rows 1 and 3 of t3[2]) fields 8 and 9
-      const bool lane_u = (lane & 7) == 7, lane_t = (lane & 31) == 22;
-      if (lane_u || lane_t) {
-        const int row = lane >> 4;
-        const int sub = row == 1 ? 2 : (row == 2 ? 1 : row);
-        const int field = lane_u ? ((lane & 8) ? 4 : 0) + sub : 8 + (row >> 1);
-        atomicAdd(grad2d + size_t(__float_as_uint(g2.w)) * kGradFloats + field, lane_u ? u : t3[2]);
+      // u0: t0 in the lower half-rows, t1 in the upper; u1: t2, t3; u2: t4;
+      // then t0: banks u0, u1, u0, u1 (fields of t0, t2, t1, t3), t4: u2; then
+      // the sums within the banks of four lanes.  (Two wait states between
+      // the write of a register and its DPP read: by the order and the nops.)
+      float u0, u1, u2;
+      asm volatile(
+          "s_nop 1\n\t"
+          "v_add_f32_dpp %5, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+          "v_add_f32_dpp %6, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+          "v_add_f32_dpp %7, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+          "v_add_f32_dpp %5, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+          "v_add_f32_dpp %6, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+          "v_add_f32_dpp %4, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+          "v_add_f32_dpp %0, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+          "v_add_f32_dpp %0, %6, %6 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+          "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+          "s_nop 0\n\t"
+          "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+          "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+          "s_nop 0\n\t"
+          "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+          : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "=&v"(u0), "=&v"(u1),
+            "=&v"(u2));
+      // one atomic instruction: lane 0 of each bank adds t0 and lane 1 of each
+      // row t4, odd rows for record b (none for jb < 0)
+      const int j = (lane & 16) ? jb : ja;
+      if (out_field >= 0 && j >= 0) {
+        atomicAdd(grad2d + size_t(__float_as_uint(s2[j].w)) * kGradFloats + out_field,
+                  (lane & 1) ? t[4] : t[0]);
       }
     };
-    if (hi <= stop_min) {
-      for (int j = int(cnt) - 1; j >= 0; --j) record(std::false_type{}, j);
-    } else {
-      for (int j = int(cnt) - 1; j >= 0; --j) record(std::true_type{}, j);
-    }
+    auto walk = [&](auto check) {
+      int j = int(cnt) - 1;
+      for (; j > 0; j -= 2) {
+        float ha[5], hb[5];
+        record(check, j, ha);
+        record(check, j - 1, hb);
+        add_pair(ha, hb, j, j - 1);
+      }
+      if (j == 0) {   // the odd one out: paired with zeros
+        float ha[5], hb[5];
+        record(check, 0, ha);
+#pragma unroll
+        for (int p = 0; p < 5; ++p) hb[p] = 0.0f;
+        add_pair(ha, hb, 0, -1);
+      }
+    };
+    if (hi <= stop_min) walk(std::false_type{}); else walk(std::true_type{});
     hi = lo;
   }
 }
 
 // grad_dirty: set, so that a later backward pass over the same binning
 // clears the record gradients first.
-template <int TW, int TH, int BATCH>
+template <int TW, int TH, int BATCH, int SPLIT>
 __global__ void __launch_bounds__(64) raster_bwd_kernel(
     const float* __restrict__ records, const uint32_t* __restrict__ values,
     const uint32_t* __restrict__ ranges, const DevView* __restrict__ views, int n_views,
@@ -520,17 +551,20 @@ __global__ void __launch_bounds__(64) raster_bwd_kernel(
     const float* __restrict__ d_tfinal, const float* __restrict__ l1_image,
     const float* __restrict__ l1_target, float l1_scale, float* __restrict__ grad2d) {
   __shared__ float4 s0[BATCH], s1[BATCH], s2[BATCH];
+  __shared__ uint32_t s_pos[SPLIT > 1 ? BATCH : 1];   // positions of the kept records
   if (blockIdx.x == 0 && threadIdx.x == 0) *grad_dirty = 1u;
-  for (uint32_t q = next_tile(work, true); q < n_tiles; q = next_tile(work, false)) {
-    const uint32_t tile = order[q];
+  for (uint32_t q = next_tile(work, true); q / SPLIT < n_tiles; q = next_tile(work, false)) {
+    const uint32_t tile = order[q / SPLIT];
+    const int band = int(q % SPLIT);
     if (d_tfinal)
-      raster_bwd_tile<TW, TH, BATCH, true>(tile, s0, s1, s2, records, values, ranges, views,
-                                           n_views, t_ws, ncontrib, d_image, d_tfinal, l1_image,
-                                           l1_target, l1_scale, grad2d);
+      raster_bwd_tile<TW, TH, BATCH, SPLIT, true>(tile, band, s0, s1, s2, s_pos, records, values, ranges,
+                                                  views, n_views, t_ws, ncontrib, d_image,
+                                                  d_tfinal, l1_image, l1_target, l1_scale, grad2d);
     else
-      raster_bwd_tile<TW, TH, BATCH, false>(tile, s0, s1, s2, records, values, ranges, views,
-                                            n_views, t_ws, ncontrib, d_image, d_tfinal, l1_image,
-                                            l1_target, l1_scale, grad2d);
+      raster_bwd_tile<TW, TH, BATCH, SPLIT, false>(tile, band, s0, s1, s2, s_pos, records, values, ranges,
+                                                   views, n_views, t_ws, ncontrib, d_image,
+                                                   d_tfinal, l1_image, l1_target, l1_scale,
+                                                   grad2d);
   }
 }
 
@@ -554,13 +588,18 @@ struct RasterLaunch {
 // or two wavefronts each, and its time is the chain of its longest tile: two
 // or four wavefronts a tile, each staging only the records that may reach its
 // band, shorten that chain.  Beyond the limits the records staged and tested
-// several times cost more than that saves.  Forward only.  Measured on 16x16 tiles, one / two / four wavefronts a tile (us):
+// several times (and, backward, reduced several times) cost more than that
+// saves.  Measured on 16x16 tiles, one / two / four wavefronts a tile (us):
 //   forward   64 tiles 62 / 34 / 23, 1200 21 / 14 / 11, 1900 51 / 31 / 22,
 //             3072 43 / 27 / 24, 4108 68 / 43 / 46, 8160 59 / 58 / 67 and
 //             107 / 105 / 120, 14400 105 / 114 / 133
+//   backward  64 tiles 87 / 49 / 32, 1200 29 / 19 / 16, 1900 71 / 44 / 45 and
+//             111 / 67 / 47, 3072 61 / 45 / 53, 4108 99 / 97 / 129 and
+//             33 / 31 / 34, 8160 121 / 143 / 211
 // (the default tile shape and batch depth only: the others are the
 // autotuner's alternatives).
 constexpr uint32_t kFwdBands4 = 3072, kFwdBands2 = 8192;
+constexpr uint32_t kBwdBands4 = 2048, kBwdBands2 = 4352;
 constexpr bool can_split(int tw, int th, int batch) { return tw == 16 && th == 16 && batch <= 64; }
 
 static RasterLaunch raster_geometry(uint32_t n_tiles, uint32_t* work, uint32_t persistent_blocks,
@@ -589,7 +628,7 @@ static hipError_t raster_fwd_t(const RasterLaunch& g, const float* records, cons
   return hipGetLastError();
 }
 
-template <int TW, int TH, int BATCH, int = 1>
+template <int TW, int TH, int BATCH, int SPLIT = 1>
 static hipError_t raster_bwd_t(const RasterLaunch& g, uint32_t* grad_dirty, const float* records,
                                const uint32_t* values, const uint32_t* ranges,
                                const DevView* views, int n_views,
@@ -597,7 +636,7 @@ static hipError_t raster_bwd_t(const RasterLaunch& g, uint32_t* grad_dirty, cons
                                const float* d_tfinal, const float* l1_image,
                                const float* l1_target, float l1_scale, float* grad2d,
                                hipStream_t st) {
-  hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, BATCH>), dim3(g.grid), dim3(64), 0, st,
+  hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, BATCH, SPLIT>), dim3(g.grid), dim3(64), 0, st,
                      records, values, ranges, views, n_views, g.n_tiles, g.order, g.work,
                      grad_dirty, t_ws, ncontrib, d_image, d_tfinal, l1_image, l1_target, l1_scale,
                      grad2d);
@@ -656,7 +695,9 @@ hipError_t launch_raster_bwd(int tw, int th, int batch, uint32_t persistent_bloc
                              const float* l1_target, float l1_scale, float* grad2d,
                              hipStream_t st) {
   if (n_tiles == 0) return hipSuccess;
-  const RasterLaunch g = raster_geometry(n_tiles, work, persistent_blocks, order, 0u, 0u, st);
+  const bool split = can_split(tw, th, batch);
+  const RasterLaunch g = raster_geometry(n_tiles, work, persistent_blocks, order,
+                                         split ? kBwdBands4 : 0u, split ? kBwdBands2 : 0u, st);
   UBS_TILE_DISPATCH(raster_bwd_t, g, grad_dirty, records, values, ranges, views, n_views, t_ws,
                     ncontrib, d_image, d_tfinal, l1_image, l1_target, l1_scale, grad2d, st);
 }
