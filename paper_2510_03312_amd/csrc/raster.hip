@@ -21,10 +21,17 @@
 // for the 2.6 of a tile's four 64-pixel strips that a record's ellipse
 // reaches, with half the lanes inside it), so they are counted in
 // instructions: a strip costs the forward 4 for the support test and 13 plus
-// two transcendentals inside it, the backward 4 and 23 plus four, and a
+// two transcendentals inside it, the backward 4 and 25 plus four, and a
 // record 23 more in the backward for its wavefront sums.  1M 7-D primitives
 // at 1080p, before and after the present forms: forward 63.0 -> 58.7 us,
-// backward 132 -> 121 us; 1M 6-D 115 -> 107 and 247 -> 224 us.
+// backward 132 -> 123 us; 1M 6-D 115 -> 107 and 247 -> 229 us.
+//
+// The order of the backward's float32 operations is kept with care.  A record
+// whose 2-D covariance is nearly singular (the symmetrised conditional
+// covariance need not be definite) has moment sums that cancel by factors of
+// 1e5 and more in the chain to the covariance, so a sum rounded differently
+// changes such a gradient in its second digit; w (g . (c - S)) in place of
+// sigma (T (g . (c - S))), two instructions a strip fewer (121 us), did.
 //
 // Both passes take every per-pixel decision (support test, skip, stop)
 // through the same inline functions, so the backward pass visits exactly
@@ -444,13 +451,12 @@ __device__ __forceinline__ void raster_bwd_tile(
         // g . (c - S): the colour gradient g dotted with the record's colour
         // minus the colour S composited behind it; S updates as
         // S += alpha (c - S), so D = g . S as D += alpha dot
-        const float dot = gR[k] * g2.x + (gG[k] * g2.y + (gB[k] * g2.z - D[k]));
+        const float dot = (gR[k] * g2.x + gG[k] * g2.y + gB[k] * g2.z) - D[k];
+        const float dalpha = HAS_DT ? Ti * dot - gTf[k] * ioma : Ti * dot;
         D[k] += alpha * dot;
         T[k] = Ti;
-        // sigma follows alpha below the 0.99 clamp: s = sigma d alpha with
-        // sigma d alpha = alpha T dot = w dot there, and nothing at the clamp
-        if (!(alpha < kAlphaMax)) continue;
-        const float sd = HAS_DT ? w * dot - alpha * (gTf[k] * ioma) : w * dot;
+        if (!(alpha < kAlphaMax)) continue;   // (sigma follows alpha below the clamp only)
+        const float sd = alpha * dalpha;
         a_o += sd;
         a_be += sd * l2;
         const float q = sd * fast_rcp(1.0f - r);
