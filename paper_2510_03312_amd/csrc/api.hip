@@ -9,15 +9,15 @@
 
 namespace ubs {
 
-hipError_t launch_preprocess_fwd(bool fp64, const DevScene& S, int scene, const DevView* views,
-                                 int n_views, float* records, LiveOut live, uint32_t* partial,
+hipError_t launch_preprocess_fwd(bool fp64, const DevScene& S, const DevView* views,
+                                 const int32_t* view_order, float* records, LiveOut live, uint32_t* partial,
                                  uint32_t stride, hipStream_t st);
 hipError_t launch_bin_prepare(uint32_t* words, size_t n_words, const uint32_t* partial,
                               uint32_t n_partials, uint32_t stride, DevStatus* status,
                               hipStream_t st);
-hipError_t launch_preprocess_bwd(bool fp64, const DevScene& S, int scene, const DevView* views,
-                                 int n_views, const float* records, float* grad2d, LiveIn kept,
-                                 float* compact, hipStream_t st);
+hipError_t launch_preprocess_bwd(bool fp64, const DevScene& S, const DevView* views,
+                                 const int32_t* view_order, const float* records, float* grad2d,
+                                 LiveIn kept, float* compact, hipStream_t st);
 hipError_t launch_bin_count(const float* records, const uint8_t* live, const DevView* views,
                             int n_views,
                             uint32_t n_records, uint32_t* tile_counts, uint32_t* hit_mask,
@@ -63,13 +63,16 @@ struct ViewChunk {
   int32_t first, count;
 };
 
-// Writes a chunk of view descriptors; the first chunk's launch also clears
-// the status block (s != nullptr) and the n_scenes kept-primitive counters.
+// Writes a chunk of view descriptors and their entries of the list of views
+// by scene; the first chunk's launch also clears the status block (s != nullptr) and the n_scenes kept-primitive counters.
 __global__ void upload_views_kernel(ViewChunk c, DevView* __restrict__ dst,
-                                    DevStatus* __restrict__ s, uint32_t* __restrict__ n_kept,
-                                    int n_counters) {
+                                    int32_t* __restrict__ order, DevStatus* __restrict__ s,
+                                    uint32_t* __restrict__ n_kept, int n_counters) {
   const int k = threadIdx.x;
-  if (k < c.count) dst[c.first + k] = c.v[k];
+  if (k < c.count) {
+    dst[c.first + k] = c.v[k];
+    order[c.v[k].order_slot] = c.first + k;
+  }
   if (s)
     for (int j = k; j < n_counters; j += int(blockDim.x)) n_kept[j] = 0u;
   if (s && k == 0) {
@@ -235,7 +238,19 @@ static ubs_status plan(const ubs_frame* f, Layout* L, std::vector<DevView>* dv,
     n_pix += uint64_t(V.width) * uint64_t(V.height);
     if (n_rec > 0x7fffffffull || n_tiles > 0x7fffffffull || n_pix > 0x7fffffffull)
       return UBS_ERR_UNSUPPORTED;
+    (*ds)[size_t(V.scene)].n_views += 1;
     dv->push_back(d);
+  }
+  // the list of views by scene, ascending within a scene
+  int32_t slot = 0;
+  for (DevScene& d : *ds) {
+    d.view0 = slot;
+    slot += d.n_views;
+    d.n_views = 0;
+  }
+  for (DevView& d : *dv) {
+    DevScene& sc = (*ds)[size_t(d.scene)];
+    d.order_slot = uint32_t(sc.view0 + sc.n_views++);
   }
   Layout& l = *L;
   memset(&l, 0, sizeof(l));
@@ -258,6 +273,7 @@ static ubs_status plan(const ubs_frame* f, Layout* L, std::vector<DevView>* dv,
   auto take = [&](uint64_t bytes) { const uint64_t o = off; off = align256(off + bytes); return o; };
   l.pub.off_status = take(sizeof(DevStatus));
   l.off_views = take(sizeof(DevView) * uint64_t(f->n_views > 0 ? f->n_views : 1));
+  l.off_view_order = take(4 * uint64_t(f->n_views > 0 ? f->n_views : 1));
   l.off_scenes = take(sizeof(DevScene) * uint64_t(f->n_scenes > 0 ? f->n_scenes : 1));
   l.pub.off_records = take(uint64_t(kRecFloats) * 4 * n_rec);
   l.off_tile_counts = take(4 * (n_tiles + 2));
@@ -312,9 +328,7 @@ struct Plan {
 
 // Scenes some view renders (preprocess launches one kernel for each).
 static bool scene_used(const Plan& p, int sc) {
-  for (const DevView& v : p.dv)
-    if (v.scene == sc) return true;
-  return false;
+  return p.ds[size_t(sc)].n_views > 0;
 }
 
 // Workgroups of the preprocess launches: the per-workgroup counts they left.
@@ -371,7 +385,7 @@ ubs_status ubs_preprocess(const ubs_frame* frame, void* ws, uint64_t ws_bytes, u
     c.count = frame->n_views - first < kViewChunk ? frame->n_views - first : kViewChunk;
     for (int k = 0; k < c.count; ++k) c.v[k] = p.dv[first + k];
     hipLaunchKernelGGL(upload_views_kernel, dim3(1), dim3(64), 0, s, c, views,
-                       first == 0 ? status : nullptr,
+                       at<int32_t>(ws, L.off_view_order), first == 0 ? status : nullptr,
                        at<uint32_t>(ws, L.off_live_count), frame->n_scenes * int(kKeptLists));
   }
   UBS_HIP(hipGetLastError());
@@ -382,9 +396,7 @@ ubs_status ubs_preprocess(const ubs_frame* frame, void* ws, uint64_t ws_bytes, u
   const uint32_t stride = uint32_t(L.n_pre_partials);
   uint32_t block_base = 0;
   for (int sc = 0; sc < frame->n_scenes; ++sc) {
-    bool used = false;
-    for (const DevView& v : p.dv) used = used || v.scene == sc;
-    if (!used || p.ds[sc].n == 0) continue;
+    if (!scene_used(p, sc) || p.ds[sc].n == 0) continue;
     const LiveOut kept{at<uint8_t>(ws, L.pub.off_live),
                        at<uint32_t>(ws, L.off_kept) + p.ds[sc].prim_base,
                        at<uint32_t>(ws, L.off_offsets) + p.ds[sc].prim_base,
@@ -392,7 +404,8 @@ ubs_status ubs_preprocess(const ubs_frame* frame, void* ws, uint64_t ws_bytes, u
                        at<uint32_t>(ws, L.off_live_count) + size_t(sc) * kKeptLists,
                        kept_list_cap(p.ds[sc].n),
                        at<float>(ws, L.off_par_compact) + p.ds[sc].par_base};
-    UBS_HIP(launch_preprocess_fwd(fp64, p.ds[sc], sc, views, frame->n_views, records, kept,
+    UBS_HIP(launch_preprocess_fwd(fp64, p.ds[sc], views, at<int32_t>(ws, L.off_view_order),
+                                  records, kept,
                                   partial + block_base, stride, s));
     block_base += uint32_t((p.ds[sc].n + 255) / 256);
   }
@@ -509,9 +522,7 @@ ubs_status ubs_render_bwd(const ubs_frame* frame, void* ws, uint64_t ws_bytes,
   stage_mark(frame, UBS_STAGE_PRE_BWD, 0, s);
   for (int sc = 0; sc < frame->n_scenes; ++sc) {
     if (p.ds[sc].n == 0) continue;
-    bool used = false;
-    for (const DevView& v : p.dv) used = used || v.scene == sc;
-    if (!used) {  // a scene no view sees has zero gradient
+    if (!scene_used(p, sc)) {  // a scene no view sees has zero gradient
       launch_fill_zero(p.ds[sc].dparams, size_t(p.ds[sc].F) * size_t(p.ds[sc].n), s);
       continue;
     }
@@ -524,7 +535,7 @@ ubs_status ubs_render_bwd(const ubs_frame* frame, void* ws, uint64_t ws_bytes,
                       at<uint32_t>(ws, L.off_live_count) + size_t(sc) * kKeptLists,
                       kept_list_cap(p.ds[sc].n),
                       at<float>(ws, L.off_par_compact) + p.ds[sc].par_base};
-    UBS_HIP(launch_preprocess_bwd(fp64, p.ds[sc], sc, views, frame->n_views,
+    UBS_HIP(launch_preprocess_bwd(fp64, p.ds[sc], views, at<int32_t>(ws, L.off_view_order),
                                   at<float>(ws, L.pub.off_records), grad2d, kept,
                                   at<float>(ws, L.off_grad_compact), s));
   }

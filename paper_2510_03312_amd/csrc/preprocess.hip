@@ -7,14 +7,44 @@
 // parameter rows of the primitives some view kept to a compacted copy laid
 // out like the adjoint's work lists, so that the adjoint reads dense rows
 // instead of gathering a fifth of every line of the parameter array.
+#include <type_traits>
+
 #include "prim_math.hpp"
+#include "prim_math_f32.hpp"
 
 namespace ubs {
 
+constexpr int kCountBins = 64;
+
+// The forward's forms for T: those of prim_math.hpp, or the float32 option's.
 template <typename T, int C, int ROT>
-__global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S, int scene,
+struct Forms {
+  using G = Geo<T, C, ROT>;
+  using S = ViewState<T, C>;
+  __device__ __forceinline__ static void geo(const Raw<C, ROT>& r, G& g, uint32_t variant) {
+    geo_forward<T, C, ROT>(r, g, variant);
+  }
+  __device__ __forceinline__ static void view(const Raw<C, ROT>& r, const G& g, const DevView& V, S& s) {
+    view_forward<T, C, ROT, false>(r, g, V, s);
+  }
+};
+template <int C, int ROT>
+struct Forms<float, C, ROT> {
+  using G = f32::Geo<C, ROT>;
+  using S = f32::ViewState<C>;
+  __device__ __forceinline__ static void geo(const Raw<C, ROT>& r, G& g, uint32_t variant) {
+    f32::geo_forward<C, ROT>(r, g, variant);
+  }
+  __device__ __forceinline__ static void view(const Raw<C, ROT>& r, const G& g, const DevView& V, S& s) {
+    f32::view_forward<C, ROT>(r, g, V, s);
+  }
+};
+
+template <typename T, int C, int ROT>
+__global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S,
                                                              const DevView* __restrict__ views,
-                                                             int n_views, float* __restrict__ records,
+                                                             const int32_t* __restrict__ view_order,
+                                                             float* __restrict__ records,
                                                              LiveOut kept,
                                                              uint32_t* __restrict__ partial,
                                                              uint32_t partial_stride) {
@@ -25,7 +55,8 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S, int sce
   const bool active = i < S.n;
   bool finite = true;
   Raw<C, ROT> r;
-  Geo<T, C, ROT> g;
+  using Form = Forms<T, C, ROT>;
+  typename Form::G g;
   if (active) {
     load_raw_rows<C, ROT>(
         [&](int k) {
@@ -35,15 +66,14 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S, int sce
         },
         r);
     finite = r.finite;
-    geo_forward<T, C, ROT>(r, g, S.variant);
+    Form::geo(r, g, S.variant);
   }
   uint32_t visible = 0;
-  for (int v = 0; v < n_views; ++v) {
-    const DevView& V = views[v];
-    if (V.scene != scene) continue;
+  for (int q = 0; q < S.n_views; ++q) {
+    const DevView& V = views[view_order[S.view0 + q]];
     if (!active) continue;
-    ViewState<T, C> s;
-    view_forward<T, C, ROT>(r, g, V, s);
+    typename Form::S s;
+    Form::view(r, g, V, s);
     bool live = s.live && finite;
     float4 o0, o1, o2;
     if (live) {
@@ -77,7 +107,9 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S, int sce
   // rows (from LDS) to their columns of the compacted copy.
   __shared__ uint32_t s_cnt[2], s_run;
   __shared__ unsigned long long s_keep[4];
+  __shared__ uint32_t s_bin[kCountBins];
   if (threadIdx.x == 0) { s_cnt[0] = 0; s_cnt[1] = 0; }
+  if (threadIdx.x < kCountBins) s_bin[threadIdx.x] = 0u;
   __syncthreads();
   const unsigned long long nf = __ballot(active && !finite);
   const unsigned long long km = __ballot(keep);
@@ -100,12 +132,34 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S, int sce
     s_run = n_keep ? atomicAdd(&kept.count[which], n_keep) : 0u;
   }
   __syncthreads();
-  if (!keep) return;
-  // entry q of the run: the kept primitives in thread order
+  // entry q of the run: the kept primitives in thread order, or, where several
+  // views see the scene, by their number of live records (kCountBins bins,
+  // every second workgroup of a list the other way round, so that the ends of
+  // neighbouring runs have about the same)
   uint32_t q = uint32_t(__popcll(km & ((1ull << lane) - 1ull)));
   if (wave > 0) q += uint32_t(__popcll(m0));
   if (wave > 1) q += uint32_t(__popcll(m1));
   if (wave > 2) q += uint32_t(__popcll(m2));
+  if (S.n_views > 1) {
+    uint32_t bin = min(visible, uint32_t(kCountBins - 1));
+    if ((blockIdx.x / kKeptLists) & 1u) bin = uint32_t(kCountBins - 1) - bin;
+    uint32_t rank = 0;
+    if (keep) rank = atomicAdd(&s_bin[bin], 1u);
+    __syncthreads();
+    if (wave == 0) {
+      const uint32_t c = s_bin[lane];
+      uint32_t incl = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+      }
+      s_bin[lane] = incl - c;
+    }
+    __syncthreads();
+    q = s_bin[bin] + rank;
+  }
+  if (!keep) return;
   const uint32_t p = s_run + q;
   kept.list[size_t(which) * kept.cap + p] = uint32_t(i);
   kept.pos[i] = p;
@@ -139,15 +193,218 @@ __device__ __forceinline__ void record_gradient_from_sums(const float* rf, float
   g[6] = g[6] * 0.69314718f;
 }
 
-// One thread per entry of the kept lists: the adjoint of the primitive at
-// entry e of list l, its parameters read from column t = l cap + e of the
-// compacted copy and its gradient written to column t of the compacted
-// [F][kKeptLists cap] buffer (both coalesced); scatter_dparams_kernel moves
-// it to the primitive's column.
+// What the adjoint reads of a record: its live flag, gradient sums and fields
+// 2-7 (every row lies inside the workspace; a culled record's are not used).
+struct RecordIn {
+  float sums[kGradFloats];
+  float fields[6];
+  uint32_t live;
+};
+__device__ __forceinline__ void load_record(const uint8_t* __restrict__ rec_live,
+                                            const float* __restrict__ records,
+                                            const float* __restrict__ grad2d, size_t rec,
+                                            RecordIn& x) {
+  x.live = rec_live[rec];
+  const float2* gp = reinterpret_cast<const float2*>(grad2d + rec * kGradFloats);
+  const float2* rp = reinterpret_cast<const float2*>(records + rec * kRecFloats + 2);
+#pragma unroll
+  for (int k = 0; k < kGradFloats / 2; ++k) {
+    const float2 v = gp[k];
+    x.sums[2 * k] = v.x;
+    x.sums[2 * k + 1] = v.y;
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float2 v = rp[k];
+    x.fields[2 * k] = v.x;
+    x.fields[2 * k + 1] = v.y;
+  }
+}
+
+// The adjoint of one record: its share of the primitive's gradient rows is
+// added to the lane's column of s_grad.  (Plain adds: every column is one
+// lane's.  LDS float atomics took pre_bwd from 82 to 130 us.)
+template <typename T, int C, int ROT, int LANES>
+__device__ __forceinline__ void record_adjoint(const Raw<C, ROT>& r, const Geo<T, C, ROT>& g,
+                                               const DevView& V, RecordIn& x,
+                                               float* __restrict__ grad_row,
+                                               float (*s_grad)[LANES], int lane) {
+  record_gradient_from_sums(x.fields, x.sums);
+  // (rows start 8-byte aligned)
+  float2* gp = reinterpret_cast<float2*>(grad_row);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) gp[k] = make_float2(x.sums[2 * k], x.sums[2 * k + 1]);
+  grad_row[6] = x.sums[6];
+  ViewState<T, C> s;
+  view_forward<T, C, ROT, true>(r, g, V, s);
+  view_backward<T, C, ROT>(g, V, s, x.sums, [&](int k, T y) { s_grad[k][lane] += float(y); });
+}
+
+// The last step: gradient rows to parameter rows, written to column t of the
+// compacted buffer.  AGAIN: the parameters are read once more, and what only
+// this step needs of them (s, M, Sigma_xq, H) is formed again; kept over the
+// views they would take the registers of the second wavefront per SIMD.
+template <typename T, int C, int ROT, int LANES, bool AGAIN>
+__device__ __forceinline__ void write_gradient(const Raw<C, ROT>& r, const float* __restrict__ par,
+                                               int64_t stride, uint32_t t, Geo<T, C, ROT>& g,
+                                               float (*s_grad)[LANES], int lane,
+                                               float* __restrict__ compact) {
+  auto grad = [&](int k) { return s_grad[k][lane]; };
+  auto out = [&](int k, float x) { compact[int64_t(k) * stride + t] = x; };
+  if constexpr (AGAIN) {
+    uint32_t t2 = t;
+    asm volatile("" : "+v"(t2));
+    Raw<C, ROT> r2;
+    load_raw<C, ROT>(par, stride, t2, r2);
+    geo_frame<T, C, ROT>(r2, g);
+    if constexpr (C > 0) geo_h<T, C, ROT>(g);
+    geo_backward<T, C, ROT>(r2, g, grad, out);
+  } else {
+    geo_backward<T, C, ROT>(r, g, grad, out);
+  }
+}
+
+// Adjoint of a scene that one view sees.  One lane per entry of the kept
+// lists: the primitive at entry e of list l, its parameters read from column
+// t = l cap + e of the compacted copy and its gradient written to column t of
+// the compacted [F][kKeptLists cap] buffer (both coalesced);
+// scatter_dparams_kernel moves it to the primitive's column.
+//
+// Bound by latency: the float64 state leaves two wavefronts per SIMD (one
+// beyond 7-D), so a workgroup is one wavefront (a SIMD takes the next as soon
+// as it is free, not when its workgroup's others are), the parameters, the
+// list entry and the list's count are read together, the gradient rows lie in
+// LDS and not in registers, and the last step reads the parameters again.
+// With the triangular forms of prim_math.hpp: 1M 7-D at 1080p 49 -> 34 us, 1M
+// 6-D 55 -> 38, 1M 10-D 223 -> 43 (its state no longer spills).  A scene of up
+// to kOneRound primitives fills no SIMD twice: it keeps the parameters in
+// registers instead (250,000 7-D 14.2 us, 18 with AGAIN).
+constexpr int64_t kOneRound = 1 << 18;
+
+template <typename T, int C, int ROT, bool AGAIN>
+__global__ void __launch_bounds__(64, AGAIN && C <= 4 ? 2 : 1) preprocess_bwd_kernel(
+    DevScene S, const DevView* __restrict__ views, const int32_t* __restrict__ view_order,
+    const float* __restrict__ records, float* __restrict__ grad2d, LiveIn kept,
+    float* __restrict__ compact) {
+  constexpr int ROWS = grad_rows(C).N;
+  __shared__ float s_grad[ROWS][64];
+  // workgroup b takes entries 64 (b / kKeptLists) + [0, 64) of kept list
+  // b mod kKeptLists (cap is a multiple of 64), so the workgroups holding
+  // entries come first in the grid whatever the lists' counts
+  const int lane = threadIdx.x;
+  const uint32_t lo = blockIdx.x % kKeptLists;
+  const uint32_t pos = (blockIdx.x / kKeptLists) * 64u + threadIdx.x;
+  const uint32_t t = lo * kept.cap + pos;
+  const uint32_t n_entries = kept.count[lo];
+  if ((blockIdx.x / kKeptLists) * 64u >= n_entries) return;
+  // (a lane past the list's end reads an unused entry of its own list and column)
+  const uint32_t i = kept.list[t];
+  const int64_t stride = int64_t(kKeptLists) * kept.cap;
+  Raw<C, ROT> r;
+  load_raw<C, ROT>(kept.par, stride, t, r);
+#pragma unroll
+  for (int k = 0; k < ROWS; ++k) s_grad[k][lane] = 0.0f;
+  if (pos >= n_entries) return;
+  const DevView& V = views[view_order[S.view0]];
+  const size_t rec = size_t(V.rec_base) + i;
+  RecordIn x;
+  // (registers allow the record's read ahead of the geometry here)
+  if constexpr (!AGAIN) load_record(kept.rec_live, records, grad2d, rec, x);
+  Geo<T, C, ROT> g;
+  geo_forward<T, C, ROT>(r, g, S.variant);
+  if constexpr (AGAIN) load_record(kept.rec_live, records, grad2d, rec, x);
+  if (x.live)
+    record_adjoint<T, C, ROT, 64>(r, g, V, x, grad2d + rec * kGradFloats, s_grad, lane);
+  write_gradient<T, C, ROT, 64, AGAIN>(r, kept.par, stride, t, g, s_grad, lane, compact);
+}
+
+// Adjoint of a scene that several views see.  A primitive is live in some of
+// them only (2.3 of eight on the batched workloads), and a wavefront runs as
+// many steps as its busiest lane has live records.  So each lane takes its own
+// live views one after the other, and the preprocess lists the kept
+// primitives of a workgroup by their number of live records: a wavefront's
+// lanes then have about the same.  (The columns stay dense that way: sorting
+// the entries afterwards, in groups of 1024, made every wavefront read its
+// parameters from all over the group: 640 us where this takes 390.)  2M 7-D in
+// 8 views 726 -> 385 us, 4 scenes in 32 views 2.05 -> 1.07 ms, the forms of
+// prim_math.hpp included (580 us and 1.45 ms with all lanes in step over the
+// scene's views); the preprocess pays 15 us for the sorting of the 8 views.
+constexpr int kManyViews = 32;   // views of a live mask
+constexpr int kViewWords = int(sizeof(DevView) / 4);
+
 template <typename T, int C, int ROT>
-__global__ void __launch_bounds__(256) preprocess_bwd_kernel(DevScene S, int scene,
+__global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel(
+    DevScene S, const DevView* __restrict__ views, const int32_t* __restrict__ view_order,
+    const float* __restrict__ records, float* __restrict__ grad2d, LiveIn kept,
+    float* __restrict__ compact) {
+  constexpr int ROWS = grad_rows(C).N;
+  __shared__ float s_grad[ROWS][64];
+  __shared__ uint32_t s_views[kManyViews][kViewWords];
+  const int lane = threadIdx.x;
+  const uint32_t lo = blockIdx.x % kKeptLists;
+  const uint32_t pos = (blockIdx.x / kKeptLists) * 64u + threadIdx.x;
+  const uint32_t n_entries = kept.count[lo];
+  if ((blockIdx.x / kKeptLists) * 64u >= n_entries) return;
+  const bool active = pos < n_entries;
+  // (a lane past the list's end reads an unused entry of its own list and column)
+  const uint32_t t = lo * kept.cap + pos;
+  const uint32_t entry = kept.list[t];
+  const uint32_t i = active ? entry : 0u;
+  const int64_t stride = int64_t(kKeptLists) * kept.cap;
+  Raw<C, ROT> r;
+  load_raw<C, ROT>(kept.par, stride, t, r);
+  auto view = [&](int q) -> const DevView& { return *reinterpret_cast<const DevView*>(s_views[q]); };
+  // the descriptors of views [q0, q0 + nq) of the scene into LDS; the lane's
+  // live records among them as a mask
+  auto stage_views = [&](int q0, int nq) {
+    __syncthreads();
+    for (int w = lane; w < nq * kViewWords; w += 64)
+      s_views[w / kViewWords][w % kViewWords] =
+          reinterpret_cast<const uint32_t*>(views + view_order[S.view0 + q0 + w / kViewWords])[w % kViewWords];
+    __syncthreads();
+    uint32_t live = 0u;
+#pragma unroll 8
+    for (int q = 0; q < nq; ++q)
+      live |= (kept.rec_live[size_t(view(q).rec_base) + i] != 0 ? 1u : 0u) << q;
+    return active ? live : 0u;
+  };
+  int nq = min(kManyViews, S.n_views);
+  uint32_t live = stage_views(0, nq);
+#pragma unroll
+  for (int k = 0; k < ROWS; ++k) s_grad[k][lane] = 0.0f;
+  Geo<T, C, ROT> g;
+  geo_forward<T, C, ROT>(r, g, S.variant);
+  for (int q0 = 0;;) {
+    while (live != 0) {
+      const int cur = __ffs(int(live)) - 1;
+      live &= live - 1;
+      const DevView& V = view(cur);
+      const size_t rec = size_t(V.rec_base) + i;
+      RecordIn y;
+      load_record(kept.rec_live, records, grad2d, rec, y);
+      // (not carried from view to view as float64 copies)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(r.mu[k]));
+#pragma unroll
+      for (int k = 0; k < C; ++k) asm volatile("" : "+v"(r.muq[k]));
+      asm volatile("" : "+v"(r.o), "+v"(r.bx));
+      record_adjoint<T, C, ROT, 64>(r, g, V, y, grad2d + rec * kGradFloats, s_grad, lane);
+    }
+    q0 += nq;
+    if (q0 >= S.n_views) break;
+    nq = min(kManyViews, S.n_views - q0);
+    live = stage_views(q0, nq);
+  }
+  if (!active) return;
+  write_gradient<T, C, ROT, 64, true>(r, kept.par, stride, t, g, s_grad, lane, compact);
+}
+
+// Adjoint of the float32 option (a lane per list entry, all lanes in step over
+// the scene's views).
+template <int C, int ROT>
+__global__ void __launch_bounds__(256) preprocess_bwd_f32_kernel(DevScene S,
                                                              const DevView* __restrict__ views,
-                                                             int n_views,
+                                                             const int32_t* __restrict__ view_order,
                                                              const float* __restrict__ records,
                                                              float* __restrict__ grad2d,
                                                              LiveIn kept,
@@ -165,13 +422,12 @@ __global__ void __launch_bounds__(256) preprocess_bwd_kernel(DevScene S, int sce
   Raw<C, ROT> r;
   // (dense rows of the compacted copy the preprocess wrote)
   load_raw<C, ROT>(kept.par, stride, t, r);
-  Geo<T, C, ROT> g;
-  geo_forward<T, C, ROT>(r, g, S.variant);
-  GeoGrad<T, C> G;
-  geograd_zero<T, C>(G);
-  for (int v = 0; v < n_views; ++v) {
-    const DevView& V = views[v];
-    if (V.scene != scene) continue;
+  f32::Geo<C, ROT> g;
+  f32::geo_forward<C, ROT>(r, g, S.variant);
+  f32::GeoGrad<C> G;
+  f32::geograd_zero<C>(G);
+  for (int q = 0; q < S.n_views; ++q) {
+    const DevView& V = views[view_order[S.view0 + q]];
     const size_t rec = size_t(V.rec_base) + size_t(i);
     // the record's sums and fields are read together with its live flag
     // (every row lies inside the workspace; a culled record's are unused)
@@ -192,13 +448,13 @@ __global__ void __launch_bounds__(256) preprocess_bwd_kernel(DevScene S, int sce
     record_gradient_from_sums(rf, gr);
 #pragma unroll
     for (int k = 0; k < 7; ++k) gp[k] = gr[k];
-    ViewState<T, C> s;
-    view_forward<T, C, ROT>(r, g, V, s);
-    view_backward<T, C, ROT>(r, g, V, s, gr, G);
+    f32::ViewState<C> s;
+    f32::view_forward<C, ROT>(r, g, V, s);
+    f32::view_backward<C, ROT>(r, g, V, s, gr, G);
   }
   constexpr int F = param_rows(C, ROT).F;
   float out[F];
-  geo_backward<T, C, ROT>(r, g, G, out);
+  f32::geo_backward<C, ROT>(r, g, G, out);
 #pragma unroll
   for (int k = 0; k < F; ++k) compact[int64_t(k) * stride + t] = out[k];
 }
@@ -246,23 +502,37 @@ __global__ void __launch_bounds__(256) scatter_dparams_kernel(DevScene S, LiveIn
 }
 
 template <typename T, int C, int ROT>
-static hipError_t pre_fwd_t(const DevScene& S, int scene, const DevView* views, int n_views,
+static hipError_t pre_fwd_t(const DevScene& S, const DevView* views, const int32_t* view_order,
                             float* records, LiveOut live, uint32_t* partial, uint32_t stride,
                             hipStream_t st) {
   const unsigned blocks = unsigned((S.n + 255) / 256);
-  hipLaunchKernelGGL((preprocess_fwd_kernel<T, C, ROT>), dim3(blocks), dim3(256), 0, st, S, scene,
-                     views, n_views, records, live, partial, stride);
+  hipLaunchKernelGGL((preprocess_fwd_kernel<T, C, ROT>), dim3(blocks), dim3(256), 0, st, S,
+                     views, view_order, records, live, partial, stride);
   return hipGetLastError();
 }
 
 template <typename T, int C, int ROT>
-static hipError_t pre_bwd_t(const DevScene& S, int scene, const DevView* views, int n_views,
+static hipError_t pre_bwd_t(const DevScene& S, const DevView* views, const int32_t* view_order,
                             const float* records, float* grad2d, LiveIn kept, float* compact,
                             hipStream_t st) {
-  // one thread per entry of the kKeptLists lists of cap entries
-  const unsigned blocks = unsigned(uint64_t(kKeptLists) * kept.cap / 256);
-  hipLaunchKernelGGL((preprocess_bwd_kernel<T, C, ROT>), dim3(blocks), dim3(256), 0, st, S, scene,
-                     views, n_views, records, grad2d, kept, compact);
+  // one lane per entry of the kKeptLists lists of cap entries
+  const uint64_t entries = uint64_t(kKeptLists) * kept.cap;
+  if constexpr (std::is_same<T, float>::value) {
+    hipLaunchKernelGGL((preprocess_bwd_f32_kernel<C, ROT>), dim3(unsigned(entries / 256)),
+                       dim3(256), 0, st, S, views, view_order, records, grad2d, kept, compact);
+  } else if (S.n_views == 1) {
+    constexpr bool kMayKeep = C <= 4;   // (beyond 7-D the state spills with the parameters in it)
+    if (kMayKeep && S.n <= kOneRound)
+      hipLaunchKernelGGL((preprocess_bwd_kernel<T, C, ROT, !kMayKeep>),
+                         dim3(unsigned(entries / 64)), dim3(64), 0, st, S, views, view_order,
+                         records, grad2d, kept, compact);
+    else
+      hipLaunchKernelGGL((preprocess_bwd_kernel<T, C, ROT, true>), dim3(unsigned(entries / 64)),
+                         dim3(64), 0, st, S, views, view_order, records, grad2d, kept, compact);
+  } else {
+    hipLaunchKernelGGL((preprocess_bwd_many_kernel<T, C, ROT>), dim3(unsigned(entries / 64)),
+                       dim3(64), 0, st, S, views, view_order, records, grad2d, kept, compact);
+  }
   // 16-byte stores when every row of dparams starts 16-byte aligned
   if (S.n % 4 == 0 && reinterpret_cast<uintptr_t>(S.dparams) % 16 == 0)
     hipLaunchKernelGGL(scatter_dparams_kernel<4>, dim3(unsigned((S.n / 4 + 255) / 256)), dim3(256),
@@ -274,67 +544,68 @@ static hipError_t pre_bwd_t(const DevScene& S, int scene, const DevView* views, 
 }
 
 template <typename T>
-static hipError_t pre_fwd_dispatch(const DevScene& S, int scene, const DevView* views, int n_views,
+static hipError_t pre_fwd_dispatch(const DevScene& S, const DevView* views,
+                                   const int32_t* view_order,
                                    float* records, LiveOut live, uint32_t* partial,
                                    uint32_t stride, hipStream_t st) {
   const int C = S.dim - 3;
   if (S.rot == UBS_ROT_QUAT) {
-    if (C == 0) return pre_fwd_t<T, 0, 0>(S, scene, views, n_views, records, live, partial, stride, st);
-    if (C == 3) return pre_fwd_t<T, 3, 0>(S, scene, views, n_views, records, live, partial, stride, st);
-    if (C == 4) return pre_fwd_t<T, 4, 0>(S, scene, views, n_views, records, live, partial, stride, st);
-    if (C == 5) return pre_fwd_t<T, 5, 0>(S, scene, views, n_views, records, live, partial, stride, st);
-    if (C == 6) return pre_fwd_t<T, 6, 0>(S, scene, views, n_views, records, live, partial, stride, st);
-    if (C == 7) return pre_fwd_t<T, 7, 0>(S, scene, views, n_views, records, live, partial, stride, st);
+    if (C == 0) return pre_fwd_t<T, 0, 0>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 3) return pre_fwd_t<T, 3, 0>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 4) return pre_fwd_t<T, 4, 0>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 5) return pre_fwd_t<T, 5, 0>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 6) return pre_fwd_t<T, 6, 0>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 7) return pre_fwd_t<T, 7, 0>(S, views, view_order, records, live, partial, stride, st);
   } else {
-    if (C == 0) return pre_fwd_t<T, 0, 1>(S, scene, views, n_views, records, live, partial, stride, st);
-    if (C == 3) return pre_fwd_t<T, 3, 1>(S, scene, views, n_views, records, live, partial, stride, st);
-    if (C == 4) return pre_fwd_t<T, 4, 1>(S, scene, views, n_views, records, live, partial, stride, st);
-    if (C == 5) return pre_fwd_t<T, 5, 1>(S, scene, views, n_views, records, live, partial, stride, st);
-    if (C == 6) return pre_fwd_t<T, 6, 1>(S, scene, views, n_views, records, live, partial, stride, st);
-    if (C == 7) return pre_fwd_t<T, 7, 1>(S, scene, views, n_views, records, live, partial, stride, st);
+    if (C == 0) return pre_fwd_t<T, 0, 1>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 3) return pre_fwd_t<T, 3, 1>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 4) return pre_fwd_t<T, 4, 1>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 5) return pre_fwd_t<T, 5, 1>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 6) return pre_fwd_t<T, 6, 1>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 7) return pre_fwd_t<T, 7, 1>(S, views, view_order, records, live, partial, stride, st);
   }
   return hipErrorInvalidValue;
 }
 
 template <typename T>
-static hipError_t pre_bwd_dispatch(const DevScene& S, int scene, const DevView* views, int n_views,
+static hipError_t pre_bwd_dispatch(const DevScene& S, const DevView* views, const int32_t* view_order,
                                    const float* records, float* grad2d, LiveIn kept,
                                    float* compact, hipStream_t st) {
   const int C = S.dim - 3;
   if (S.rot == UBS_ROT_QUAT) {
-    if (C == 0) return pre_bwd_t<T, 0, 0>(S, scene, views, n_views, records, grad2d, kept, compact, st);
-    if (C == 3) return pre_bwd_t<T, 3, 0>(S, scene, views, n_views, records, grad2d, kept, compact, st);
-    if (C == 4) return pre_bwd_t<T, 4, 0>(S, scene, views, n_views, records, grad2d, kept, compact, st);
-    if (C == 5) return pre_bwd_t<T, 5, 0>(S, scene, views, n_views, records, grad2d, kept, compact, st);
-    if (C == 6) return pre_bwd_t<T, 6, 0>(S, scene, views, n_views, records, grad2d, kept, compact, st);
-    if (C == 7) return pre_bwd_t<T, 7, 0>(S, scene, views, n_views, records, grad2d, kept, compact, st);
+    if (C == 0) return pre_bwd_t<T, 0, 0>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 3) return pre_bwd_t<T, 3, 0>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 4) return pre_bwd_t<T, 4, 0>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 5) return pre_bwd_t<T, 5, 0>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 6) return pre_bwd_t<T, 6, 0>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 7) return pre_bwd_t<T, 7, 0>(S, views, view_order, records, grad2d, kept, compact, st);
   } else {
-    if (C == 0) return pre_bwd_t<T, 0, 1>(S, scene, views, n_views, records, grad2d, kept, compact, st);
-    if (C == 3) return pre_bwd_t<T, 3, 1>(S, scene, views, n_views, records, grad2d, kept, compact, st);
-    if (C == 4) return pre_bwd_t<T, 4, 1>(S, scene, views, n_views, records, grad2d, kept, compact, st);
-    if (C == 5) return pre_bwd_t<T, 5, 1>(S, scene, views, n_views, records, grad2d, kept, compact, st);
-    if (C == 6) return pre_bwd_t<T, 6, 1>(S, scene, views, n_views, records, grad2d, kept, compact, st);
-    if (C == 7) return pre_bwd_t<T, 7, 1>(S, scene, views, n_views, records, grad2d, kept, compact, st);
+    if (C == 0) return pre_bwd_t<T, 0, 1>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 3) return pre_bwd_t<T, 3, 1>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 4) return pre_bwd_t<T, 4, 1>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 5) return pre_bwd_t<T, 5, 1>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 6) return pre_bwd_t<T, 6, 1>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 7) return pre_bwd_t<T, 7, 1>(S, views, view_order, records, grad2d, kept, compact, st);
   }
   return hipErrorInvalidValue;
 }
 
 // partial: this launch's slice of the per-workgroup counts (visible records
 // at partial[b], non-finite primitives at partial[stride + b]).
-hipError_t launch_preprocess_fwd(bool fp64, const DevScene& S, int scene, const DevView* views,
-                                 int n_views, float* records, LiveOut live, uint32_t* partial,
+hipError_t launch_preprocess_fwd(bool fp64, const DevScene& S, const DevView* views,
+                                 const int32_t* view_order, float* records, LiveOut live, uint32_t* partial,
                                  uint32_t stride, hipStream_t st) {
   if (S.n == 0) return hipSuccess;
-  return fp64 ? pre_fwd_dispatch<double>(S, scene, views, n_views, records, live, partial, stride, st)
-              : pre_fwd_dispatch<float>(S, scene, views, n_views, records, live, partial, stride, st);
+  return fp64 ? pre_fwd_dispatch<double>(S, views, view_order, records, live, partial, stride, st)
+              : pre_fwd_dispatch<float>(S, views, view_order, records, live, partial, stride, st);
 }
 
-hipError_t launch_preprocess_bwd(bool fp64, const DevScene& S, int scene, const DevView* views,
-                                 int n_views, const float* records, float* grad2d, LiveIn kept,
+hipError_t launch_preprocess_bwd(bool fp64, const DevScene& S, const DevView* views,
+                                 const int32_t* view_order, const float* records, float* grad2d, LiveIn kept,
                                  float* compact, hipStream_t st) {
   if (S.n == 0) return hipSuccess;
-  return fp64 ? pre_bwd_dispatch<double>(S, scene, views, n_views, records, grad2d, kept, compact, st)
-              : pre_bwd_dispatch<float>(S, scene, views, n_views, records, grad2d, kept, compact, st);
+  return fp64 ? pre_bwd_dispatch<double>(S, views, view_order, records, grad2d, kept, compact, st)
+              : pre_bwd_dispatch<float>(S, views, view_order, records, grad2d, kept, compact, st);
 }
 
 }  // namespace ubs

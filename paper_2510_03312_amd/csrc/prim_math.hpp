@@ -1,4 +1,5 @@
-// Per-primitive math of Universal Beta Splatting, forward and adjoint.
+// Per-primitive math of Universal Beta Splatting, forward and adjoint, in
+// float64 (T; prim_math_f32.hpp has the float32 option's).
 //
 // Forward (Section 4.2, 4.3 and the projection of Section 3):
 //   Sigma = L L^T with L = [[R_x diag(s_x), 0], [L_qx, L_q]]
@@ -12,32 +13,104 @@
 //   mu_c = mu_x + K diag(bt) v; Sigma_c = Sigma_x - sym(K diag(bt) Sigma_qx)
 //   p = W mu_c + t; Sigma' = J W Sigma_c W^T J^T + 0.3 I; conic = Sigma'^-1
 //   rho = 1 - (255 o(q))^(-1/beta_x), beta_x = 4 exp(b_x)
-// Adjoint: reverse of the above, written by hand.  The Cholesky adjoint is
-//   Sigma_bar = sym(Lhat^-T Phi(Lhat^T Lhat_bar) Lhat^-1), Phi = lower
-//   triangle with the diagonal halved (Murray 2016).
+// The conditioning is evaluated through the inverse factor Li = Lhat^-1
+// (lower triangular), never through Sigma_q^-1 itself:
+//   A = Sigma_xq Li^T, H = Sigma_xq diag(bt) Li^T, y = Li diag(bt) v;
+//   mu_c = mu_x + A y, Sigma_c = Sigma_x - (A H^T + H A^T) / 2
+// (K = A Li).  Sigma_c, A and H do not depend on the view; a view costs the
+// triangular products w and y and the projection.
+// Adjoint: reverse of the above, written by hand.  A view adds to the
+// gradients of Sigma_c, A, Li, bt and the direct parameters; once per
+// primitive they are chained through A, H and Li:
+//   Sigma_q_bar = Li^T sym(Phi(-Li_bar Li^T)) Li, Phi = lower triangle with
+//   the diagonal halved
+// (the Cholesky adjoint of Murray 2016 with Lhat_bar = -Li^T Li_bar Li^T,
+// where Lhat^T Lhat_bar = -Li_bar Li^T).  Symmetric matrices are kept as one
+// triangle, and triangular ones are multiplied within their triangles: the
+// adjoint of a 7-D primitive in one view is about 1,900 instructions this
+// way, 4,000 with full matrices through Sigma_q^-1.
 #pragma once
 
 #include "ubs_internal.hpp"
 
 namespace ubs {
 
-template <typename T> __device__ __forceinline__ T m_exp(T x);
-template <> __device__ __forceinline__ float m_exp<float>(float x) { return expf(x); }
-template <> __device__ __forceinline__ double m_exp<double>(double x) { return exp(x); }
-template <typename T> __device__ __forceinline__ T m_sqrt(T x);
-template <> __device__ __forceinline__ float m_sqrt<float>(float x) { return sqrtf(x); }
-template <> __device__ __forceinline__ double m_sqrt<double>(double x) { return sqrt(x); }
+// exp of a float32 parameter.  In float64: x = n ln 2 + r with |r| <= ln 2 / 2
+// (ln 2 in two parts, the first with 21 trailing zero bits, so that n times
+// it is exact), exp(r) = 1 + r + r^2 Q(r) with Q the polynomial of degree 9
+// through (exp(r) - 1 - r) / r^2 at ten Chebyshev nodes (relative error of
+// exp(r) 1.6e-17), scaled by 2^n (to infinity or zero beyond the range).
+// 20 instructions; the library's exp, whose argument may be any float64, 32.
+template <typename T> __device__ __forceinline__ T m_exp(float x);
+template <> __device__ __forceinline__ double m_exp<double>(float x) {
+  // (a NaN becomes a number here: every caller's parameter passes the finite test too)
+  const float xc = __builtin_amdgcn_fmed3f(x, -1000.0f, 1000.0f);
+  const float n = __builtin_rintf(xc * 1.44269504f);
+  const double dn = double(n);
+  double r = __builtin_fma(dn, -0x1.62e42fee00000p-1, double(xc));
+  r = __builtin_fma(dn, -0x1.a39ef35793c76p-33, r);
+  double q = 0x1.af38d53857513p-26;
+  q = __builtin_fma(q, r, 0x1.2891a8c1d838dp-22);
+  q = __builtin_fma(q, r, 0x1.71de0d9c145d0p-19);
+  q = __builtin_fma(q, r, 0x1.a019b8ef67c6cp-16);
+  q = __builtin_fma(q, r, 0x1.a01a01a7c8d47p-13);
+  q = __builtin_fma(q, r, 0x1.6c16c17893833p-10);
+  q = __builtin_fma(q, r, 0x1.11111111109adp-7);
+  q = __builtin_fma(q, r, 0x1.5555555553d4fp-5);
+  q = __builtin_fma(q, r, 0x1.5555555555556p-3);
+  q = __builtin_fma(q, r, 0x1.0000000000001p-1);
+  const double e = 1.0 + __builtin_fma(r * r, q, r);
+  return __builtin_ldexp(e, int(n));
+}
 // 1 / sqrt(x): where both sqrt(x) and its reciprocal are needed, sqrt(x) is
 // taken as x * rsqrt(x) (one library call instead of a root and a division)
 template <typename T> __device__ __forceinline__ T m_rsqrt(T x);
-template <> __device__ __forceinline__ float m_rsqrt<float>(float x) { return rsqrtf(x); }
 template <> __device__ __forceinline__ double m_rsqrt<double>(double x) { return rsqrt(x); }
 
 // Scalar factors of the opacity (the modulation terms, o(q), beta_x, rho)
 // are well conditioned in their arguments, so they are evaluated in float32
 // whatever T is; the linear algebra of the conditioning stays in T.
 __device__ __forceinline__ float s_exp(float x) { return expf(x); }
-__device__ __forceinline__ float s_log1p_exp_m2(float x) { return log1pf(expf(-2.0f * x)); }
+__device__ __forceinline__ float s_log1p(float x) { return log1pf(x); }
+
+// The same factors in the adjoint, where no decision hangs on their last bit:
+// exp(y) for y <= 0 and log(1 + t) for t in [0, 1] in float64 to about 3e-10
+// (exp(y) = 2^n (1 + r + r^2 Q(r)), Q of degree 5 through six Chebyshev nodes
+// of |r| <= ln 2 / 2, y below -800 giving 0; log(1 + t) = t P(t), P of degree
+// 10 through eleven).  13 and 11 instructions; the library's float32 expf and
+// log1pf take about 25 and 70 and round to float32, but their bits decide
+// records' opacities, so the forward keeps them.
+__device__ __forceinline__ double s_exp_neg(double y) {
+  const double yc = __builtin_fmax(y, -800.0);
+  const double n = __builtin_rint(yc * 0x1.71547652b82fep+0);
+  const double r = __builtin_fma(n, -0x1.62e42fefa39efp-1, yc);
+  double q = 0x1.a125285dbcbf1p-13;
+  q = __builtin_fma(q, r, 0x1.6d4362097d81ap-10);
+  q = __builtin_fma(q, r, 0x1.1110e0de7be2bp-7);
+  q = __builtin_fma(q, r, 0x1.5554e8d9c7d96p-5);
+  q = __builtin_fma(q, r, 0x1.5555555a7c16bp-3);
+  q = __builtin_fma(q, r, 0x1.0000000b9847ep-1);
+  return __builtin_ldexp(1.0 + __builtin_fma(r * r, q, r), int(n));
+}
+__device__ __forceinline__ double s_log1p_unit(double t) {
+  double q = 0x1.046679cb2b7ebp-9;
+  q = __builtin_fma(q, t, -0x1.b02381e6f92c7p-7);
+  q = __builtin_fma(q, t, 0x1.4fed049df857ap-5);
+  q = __builtin_fma(q, t, -0x1.4f61d4fd9d9cap-4);
+  q = __builtin_fma(q, t, 0x1.fb00b1a6ce14cp-4);
+  q = __builtin_fma(q, t, -0x1.49797a179fca6p-3);
+  q = __builtin_fma(q, t, 0x1.9742f82e42739p-3);
+  q = __builtin_fma(q, t, -0x1.ffb933dac867dp-3);
+  q = __builtin_fma(q, t, 0x1.55532471bce50p-2);
+  q = __builtin_fma(q, t, -0x1.fffff23ca5d8fp-2);
+  q = __builtin_fma(q, t, 0x1.fffffff8bf536p-1);
+  return q * t;
+}
+// (1 + tanh x) / 2 = 1 / (1 + exp(-2 x)), t = exp(-2 x)
+__device__ __forceinline__ double s_half_tanh(double t) {
+  const double u = 1.0 + t, y = __builtin_amdgcn_rcp(u);
+  return __builtin_fma(__builtin_fma(-u, y, 1.0), y, y);
+}
 // 1 - y^(-1/beta) for y >= 1, as -expm1(-log(y) / beta) (no cancellation for
 // y near 1)
 __device__ __forceinline__ float s_rho(float y, float beta) { return -expm1f(-logf(y) / beta); }
@@ -106,15 +179,21 @@ __device__ __forceinline__ void load_raw(const float* __restrict__ P, int64_t n,
       [&](int row) { return __builtin_nontemporal_load(&P[int64_t(row) * n + i]); }, r);
 }
 
+// Index of entry (a, b) of a symmetric 3 x 3 matrix kept as 00 01 02 11 12 22.
+__device__ __forceinline__ constexpr int sym3(int a, int b) {
+  return a <= b ? 3 * a - a * (a + 1) / 2 + b : 3 * b - b * (b + 1) / 2 + a;
+}
+
 // View-independent quantities of a primitive.
 template <typename T, int C, int ROT>
 struct Geo {
   T s[3];
   T M[3][3];                         // R diag(s)
-  T Sx[3][3];
   T Sxq[3][Cdim<C>::V];
-  T Lh[Cdim<C>::V][Cdim<C>::V];      // chol(Sigma_q)
-  T Li[Cdim<C>::V][Cdim<C>::V];      // Lh^-1 (lower)
+  T Li[Cdim<C>::V][Cdim<C>::V];      // chol(Sigma_q)^-1 (lower triangle)
+  T A[3][Cdim<C>::V];                // Sigma_xq Li^T
+  T H[3][Cdim<C>::V];                // Sigma_xq diag(bt) Li^T
+  T Sc[6];                           // Sigma_c
   T bt[Cdim<C>::V];                  // min(exp(b_q), 1); 1 without the Beta condition
   T e[Cdim<C>::V];                   // 4 exp(b_q); 1 without the Beta opacity
   bool ok;
@@ -128,22 +207,19 @@ constexpr uint32_t kVarNoBetaOpacity = UBS_TUNE_NO_BETA_OPACITY;
 // Activated L_q (lower triangular, diagonal exp of the stored log scale).
 template <typename T, int C, int ROT>
 __device__ __forceinline__ T lq_entry(const Raw<C, ROT>& r, int a, int b) {
-  return b < a ? T(r.lq[a][b]) : (b == a ? m_exp<T>(T(r.lq[a][a])) : T(0));
+  return b < a ? T(r.lq[a][b]) : (b == a ? m_exp<T>(r.lq[a][a]) : T(0));
 }
 
+// s, M = R diag(s) and Sigma_xq = M Lqx^T; false for a zero quaternion.
 template <typename T, int C, int ROT>
-__device__ __forceinline__ void geo_forward(const Raw<C, ROT>& r, Geo<T, C, ROT>& g,
-                                            uint32_t variant) {
-  g.ok = r.finite;
-  g.beta_cond = (variant & kVarNoBetaCond) == 0;
-  g.beta_opacity = (variant & kVarNoBetaOpacity) == 0;
-  struct { T R[3][3]; } gr;
-  auto& R = gr.R;
+__device__ __forceinline__ bool geo_frame(const Raw<C, ROT>& r, Geo<T, C, ROT>& g) {
+  bool ok = true;
+  T R[3][3];
   if (ROT == UBS_ROT_QUAT) {
     T w = r.rq[0], x = r.rq[1], y = r.rq[2], z = r.rq[3];
     T nn = w * w + x * x + y * y + z * z;
     T inv = m_rsqrt<T>(nn);
-    if (!(nn > T(0))) g.ok = false;
+    if (!(nn > T(0))) ok = false;
     w *= inv; x *= inv; y *= inv; z *= inv;
     R[0][0] = T(1) - T(2) * (y * y + z * z);
     R[0][1] = T(2) * (x * y - w * z);
@@ -161,7 +237,7 @@ __device__ __forceinline__ void geo_forward(const Raw<C, ROT>& r, Geo<T, C, ROT>
     R[2][0] = -w2;  R[2][1] = w1;   R[2][2] = T(1);
   }
 #pragma unroll
-  for (int k = 0; k < 3; ++k) g.s[k] = m_exp<T>(T(r.logs[k]));
+  for (int k = 0; k < 3; ++k) g.s[k] = m_exp<T>(r.logs[k]);
 #pragma unroll
   for (int a = 0; a < 3; ++a)
 #pragma unroll
@@ -169,71 +245,109 @@ __device__ __forceinline__ void geo_forward(const Raw<C, ROT>& r, Geo<T, C, ROT>
 #pragma unroll
   for (int a = 0; a < 3; ++a)
 #pragma unroll
-    for (int b = 0; b <= a; ++b) {
-      g.Sx[a][b] = g.M[a][0] * g.M[b][0] + g.M[a][1] * g.M[b][1] + g.M[a][2] * g.M[b][2];
-      g.Sx[b][a] = g.Sx[a][b];
+    for (int k = 0; k < C; ++k)
+      g.Sxq[a][k] = g.M[a][0] * T(r.lqx[k][0]) + g.M[a][1] * T(r.lqx[k][1]) + g.M[a][2] * T(r.lqx[k][2]);
+  return ok;
+}
+
+// H = Sigma_xq diag(bt) Li^T.
+template <typename T, int C, int ROT>
+__device__ __forceinline__ void geo_h(Geo<T, C, ROT>& g) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    T SD[Cdim<C>::V];
+#pragma unroll
+    for (int m = 0; m < C; ++m) SD[m] = g.Sxq[a][m] * g.bt[m];
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      T acc = SD[0] * g.Li[k][0];
+#pragma unroll
+      for (int m = 1; m <= k; ++m) acc += SD[m] * g.Li[k][m];
+      g.H[a][k] = acc;
     }
+  }
+}
+
+template <typename T, int C, int ROT>
+__device__ __forceinline__ void geo_forward(const Raw<C, ROT>& r, Geo<T, C, ROT>& g,
+                                            uint32_t variant) {
+  g.ok = geo_frame<T, C, ROT>(r, g) && r.finite;
+  g.beta_cond = (variant & kVarNoBetaCond) == 0;
+  g.beta_opacity = (variant & kVarNoBetaOpacity) == 0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = a; b < 3; ++b)
+      g.Sc[sym3(a, b)] = g.M[a][0] * g.M[b][0] + g.M[a][1] * g.M[b][1] + g.M[a][2] * g.M[b][2];
   if constexpr (C > 0) {
-    T Lq[Cdim<C>::V][Cdim<C>::V];
+    // Sigma_q and its Cholesky factor, lower triangles (Lh in place of Sigma_q)
+    T Lq[Cdim<C>::V][Cdim<C>::V], Lh[Cdim<C>::V][Cdim<C>::V];
 #pragma unroll
     for (int a = 0; a < C; ++a)
 #pragma unroll
-      for (int b = 0; b < C; ++b) Lq[a][b] = lq_entry<T, C, ROT>(r, a, b);
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int k = 0; k < C; ++k)
-        g.Sxq[a][k] = g.M[a][0] * T(r.lqx[k][0]) + g.M[a][1] * T(r.lqx[k][1]) + g.M[a][2] * T(r.lqx[k][2]);
-    T Sq[Cdim<C>::V][Cdim<C>::V];
+      for (int b = 0; b <= a; ++b) Lq[a][b] = lq_entry<T, C, ROT>(r, a, b);
 #pragma unroll
     for (int a = 0; a < C; ++a)
 #pragma unroll
-      for (int b = 0; b < C; ++b) {
+      for (int b = 0; b <= a; ++b) {
         T acc = T(r.lqx[a][0]) * T(r.lqx[b][0]) + T(r.lqx[a][1]) * T(r.lqx[b][1]) +
                 T(r.lqx[a][2]) * T(r.lqx[b][2]);
 #pragma unroll
-        for (int k = 0; k < C; ++k) acc += Lq[a][k] * Lq[b][k];
-        Sq[a][b] = acc;
+        for (int k = 0; k <= b; ++k) acc += Lq[a][k] * Lq[b][k];
+        Lh[a][b] = acc;
       }
-    // Cholesky of Sigma_q (lower, positive diagonal)
 #pragma unroll
     for (int j = 0; j < C; ++j) {
-      T d = Sq[j][j];
+      T d = Lh[j][j];
 #pragma unroll
-      for (int k = 0; k < j; ++k) d -= g.Lh[j][k] * g.Lh[j][k];
+      for (int k = 0; k < j; ++k) d -= Lh[j][k] * Lh[j][k];
       if (!(d > T(0))) { g.ok = false; d = T(1); }
-      T inv = m_rsqrt<T>(d);
-      g.Lh[j][j] = d * inv;
+      const T inv = m_rsqrt<T>(d);
       g.Li[j][j] = inv;
 #pragma unroll
       for (int i = j + 1; i < C; ++i) {
-        T acc = Sq[i][j];
+        T acc = Lh[i][j];
 #pragma unroll
-        for (int k = 0; k < j; ++k) acc -= g.Lh[i][k] * g.Lh[j][k];
-        g.Lh[i][j] = acc * inv;
+        for (int k = 0; k < j; ++k) acc -= Lh[i][k] * Lh[j][k];
+        Lh[i][j] = acc * inv;
       }
-#pragma unroll
-      for (int i = 0; i < j; ++i) g.Lh[i][j] = T(0);
     }
     // inverse of the lower factor
 #pragma unroll
-    for (int j = 0; j < C; ++j) {
+    for (int j = 0; j < C; ++j)
 #pragma unroll
-      for (int i = 0; i < C; ++i) {
-        if (i < j) { g.Li[i][j] = T(0); continue; }
-        if (i == j) continue;   // 1 / Lh[i][i], set by the factorisation
-        T acc = T(0);
+      for (int i = j + 1; i < C; ++i) {
+        T acc = Lh[i][j] * g.Li[j][j];
 #pragma unroll
-        for (int k = j; k < i; ++k) acc += g.Lh[i][k] * g.Li[k][j];
+        for (int k = j + 1; k < i; ++k) acc += Lh[i][k] * g.Li[k][j];
         g.Li[i][j] = -acc * g.Li[i][i];
       }
-    }
 #pragma unroll
     for (int k = 0; k < C; ++k) {
-      T eb = m_exp<T>(T(r.bq[k]));
+      T eb = m_exp<T>(r.bq[k]);
       g.bt[k] = (g.beta_cond && r.bq[k] < 0.0f) ? eb : T(1);
       g.e[k] = g.beta_opacity ? T(4) * eb : T(1);
     }
+    // A, H and the conditional covariance
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int k = 0; k < C; ++k) {
+        T acc = g.Sxq[a][0] * g.Li[k][0];
+#pragma unroll
+        for (int m = 1; m <= k; ++m) acc += g.Sxq[a][m] * g.Li[k][m];
+        g.A[a][k] = acc;
+      }
+    geo_h<T, C, ROT>(g);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = a; b < 3; ++b) {
+        T acc = g.A[a][0] * g.H[b][0] + g.H[a][0] * g.A[b][0];
+#pragma unroll
+        for (int k = 1; k < C; ++k) acc += g.A[a][k] * g.H[b][k] + g.H[a][k] * g.A[b][k];
+        g.Sc[sym3(a, b)] -= T(0.5) * acc;
+      }
   }
 }
 
@@ -241,16 +355,18 @@ __device__ __forceinline__ void geo_forward(const Raw<C, ROT>& r, Geo<T, C, ROT>
 template <typename T, int C>
 struct ViewState {
   T dir[3];              // unit query direction
-  T dist;                // |mu_x - camera centre|
+  T idist;               // 1 / |mu_x - camera centre|
   T v[Cdim<C>::V];       // q - mu_q
-  T w[Cdim<C>::V];       // Lh^-1 v
+  T w[Cdim<C>::V];       // Li v
+  T y[Cdim<C>::V];       // Li diag(bt) v
   T ell[Cdim<C>::V];     // log(1 - tanh(w^2))
+  T rt[Cdim<C>::V];      // (1 + tanh(w^2)) / 2
+  T prod;                // o(q) / o
   T oq;                  // o(q)
-  T mu_c[3];
-  T Sc[3][3];
   T p[3];                // camera-frame mean
+  T iz;                  // 1 / p_z
   T Tm[2][3];            // J W
-  T Sp00, Sp01, Sp11;
+  T U[2][3];             // J W Sigma_c
   T ca, cb, cc;          // conic
   T mx, my;              // projected mean (pixels)
   T beta;
@@ -258,23 +374,18 @@ struct ViewState {
   bool live;
 };
 
-template <typename T, int C, int ROT>
+// ADJOINT: for the adjoint, with its scalar factors (rho and live are unused there).
+template <typename T, int C, int ROT, bool ADJOINT>
 __device__ __forceinline__ void view_forward(const Raw<C, ROT>& r, const Geo<T, C, ROT>& g,
                                              const DevView& V, ViewState<T, C>& s) {
   bool live = g.ok;
   T oq = T(r.o);
   T mu_c[3] = {T(r.mu[0]), T(r.mu[1]), T(r.mu[2])};
-  T Sc[3][3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) Sc[a][b] = g.Sx[a][b];
   if constexpr (C > 0) {
     T dv[3] = {T(r.mu[0]) - T(V.cam[0]), T(r.mu[1]) - T(V.cam[1]), T(r.mu[2]) - T(V.cam[2])};
     T dd = dv[0] * dv[0] + dv[1] * dv[1] + dv[2] * dv[2];
     T inv = m_rsqrt<T>(dd);
-    T dist = dd * inv;
-    s.dist = dist;
+    s.idist = inv;
 #pragma unroll
     for (int k = 0; k < 3; ++k) s.dir[k] = dv[k] * inv;
     T q[Cdim<C>::V];
@@ -288,76 +399,48 @@ __device__ __forceinline__ void view_forward(const Raw<C, ROT>& r, const Geo<T, 
 #pragma unroll
       for (int k = 0; k < C; ++k) q[k] = s.dir[k];   // C < 3: leading direction components
     }
+    T Dv[Cdim<C>::V];
 #pragma unroll
-    for (int k = 0; k < C; ++k) s.v[k] = q[k] - T(r.muq[k]);
+    for (int k = 0; k < C; ++k) {
+      s.v[k] = q[k] - T(r.muq[k]);
+      Dv[k] = g.bt[k] * s.v[k];
+    }
     // whitening and opacity: log(1 - tanh x) = log 2 - 2x - log1p(exp(-2x))
     T lsum = T(0);
 #pragma unroll
     for (int i = 0; i < C; ++i) {
-      T acc = T(0);
+      T acc = g.Li[i][0] * s.v[0], acc2 = g.Li[i][0] * Dv[0];
 #pragma unroll
-      for (int k = 0; k <= i; ++k) acc += g.Li[i][k] * s.v[k];
+      for (int k = 1; k <= i; ++k) {
+        acc += g.Li[i][k] * s.v[k];
+        acc2 += g.Li[i][k] * Dv[k];
+      }
       s.w[i] = acc;
-      T x = acc * acc;
+      s.y[i] = acc2;
+      const T x = acc * acc;
       // Gaussian opacity (ablation): e = 1 and ell = -w^2 / 2
-      s.ell[i] = g.beta_opacity
-                     ? T(0.69314718055994530942) - T(2) * x - T(s_log1p_exp_m2(float(x)))
-                     : T(-0.5) * x;
+      if constexpr (ADJOINT) {
+        const T t = s_exp_neg(T(-2) * x);
+        s.rt[i] = s_half_tanh(t);
+        s.ell[i] = g.beta_opacity
+                       ? T(0.69314718055994530942) - T(2) * x - s_log1p_unit(t)
+                       : T(-0.5) * x;
+      } else {
+        s.ell[i] = g.beta_opacity
+                       ? T(0.69314718055994530942) - T(2) * x - T(s_log1p(s_exp(-2.0f * float(x))))
+                       : T(-0.5) * x;
+      }
       lsum += g.e[i] * s.ell[i];
     }
-    oq = T(r.o) * T(s_exp(float(lsum)));
-    // conditioning: K = Sigma_xq Sigma_q^-1 = (Sigma_xq Lh^-T) Lh^-1
-    T K[3][Cdim<C>::V];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      T A[Cdim<C>::V];
-#pragma unroll
-      for (int k = 0; k < C; ++k) {
-        T acc = T(0);
-#pragma unroll
-        for (int m = 0; m <= k; ++m) acc += g.Sxq[a][m] * g.Li[k][m];
-        A[k] = acc;
-      }
-#pragma unroll
-      for (int k = 0; k < C; ++k) {
-        T acc = T(0);
-#pragma unroll
-        for (int m = k; m < C; ++m) acc += A[m] * g.Li[m][k];
-        K[a][k] = acc;
-      }
-    }
-    T Dv[Cdim<C>::V];
-#pragma unroll
-    for (int k = 0; k < C; ++k) Dv[k] = g.bt[k] * s.v[k];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      T acc = T(0);
-#pragma unroll
-      for (int k = 0; k < C; ++k) acc += K[a][k] * Dv[k];
-      mu_c[a] += acc;
-    }
-    T X[3][3];   // K diag(bt) Sigma_qx
+    s.prod = ADJOINT ? s_exp_neg(lsum) : T(s_exp(float(lsum)));
+    oq = T(r.o) * s.prod;
+    // mu_c = mu_x + A y
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        T acc = T(0);
-#pragma unroll
-        for (int k = 0; k < C; ++k) acc += K[a][k] * g.bt[k] * g.Sxq[b][k];
-        X[a][b] = acc;
-      }
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) Sc[a][b] -= T(0.5) * (X[a][b] + X[b][a]);
+      for (int k = 0; k < C; ++k) mu_c[a] += g.A[a][k] * s.y[k];
   }
   s.oq = oq;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    s.mu_c[a] = mu_c[a];
-#pragma unroll
-    for (int b = 0; b < 3; ++b) s.Sc[a][b] = Sc[a][b];
-  }
   // projection
   T p[3];
 #pragma unroll
@@ -368,6 +451,7 @@ __device__ __forceinline__ void view_forward(const Raw<C, ROT>& r, const Geo<T, 
   if (!(p[2] > T(kNear))) live = false;
   T z = p[2] > T(kNear) ? p[2] : T(1);
   T iz = T(1) / z;
+  s.iz = iz;
   T fx = T(V.fx), fy = T(V.fy);
   T J00 = fx * iz, J02 = -fx * p[0] * iz * iz;
   T J11 = fy * iz, J12 = -fy * p[1] * iz * iz;
@@ -376,23 +460,23 @@ __device__ __forceinline__ void view_forward(const Raw<C, ROT>& r, const Geo<T, 
     s.Tm[0][b] = J00 * T(V.R[b]) + J02 * T(V.R[6 + b]);
     s.Tm[1][b] = J11 * T(V.R[3 + b]) + J12 * T(V.R[6 + b]);
   }
-  T U[2][3];   // Tm Sc
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 3; ++b)
-      U[a][b] = s.Tm[a][0] * Sc[0][b] + s.Tm[a][1] * Sc[1][b] + s.Tm[a][2] * Sc[2][b];
-  s.Sp00 = U[0][0] * s.Tm[0][0] + U[0][1] * s.Tm[0][1] + U[0][2] * s.Tm[0][2] + T(kDilation);
-  s.Sp01 = U[0][0] * s.Tm[1][0] + U[0][1] * s.Tm[1][1] + U[0][2] * s.Tm[1][2];
-  s.Sp11 = U[1][0] * s.Tm[1][0] + U[1][1] * s.Tm[1][1] + U[1][2] * s.Tm[1][2] + T(kDilation);
-  T det = s.Sp00 * s.Sp11 - s.Sp01 * s.Sp01;
-  if (!(det > T(0)) || !(s.Sp00 > T(0)) || !(s.Sp11 > T(0))) live = false;
+      s.U[a][b] = s.Tm[a][0] * g.Sc[sym3(0, b)] + s.Tm[a][1] * g.Sc[sym3(1, b)] +
+                  s.Tm[a][2] * g.Sc[sym3(2, b)];
+  const T Sp00 = s.U[0][0] * s.Tm[0][0] + s.U[0][1] * s.Tm[0][1] + s.U[0][2] * s.Tm[0][2] + T(kDilation);
+  const T Sp01 = s.U[0][0] * s.Tm[1][0] + s.U[0][1] * s.Tm[1][1] + s.U[0][2] * s.Tm[1][2];
+  const T Sp11 = s.U[1][0] * s.Tm[1][0] + s.U[1][1] * s.Tm[1][1] + s.U[1][2] * s.Tm[1][2] + T(kDilation);
+  T det = Sp00 * Sp11 - Sp01 * Sp01;
+  if (!(det > T(0)) || !(Sp00 > T(0)) || !(Sp11 > T(0))) live = false;
   T idet = T(1) / (det > T(0) ? det : T(1));
   s.mx = fx * p[0] * iz + T(V.cx);
   s.my = fy * p[1] * iz + T(V.cy);
-  s.ca = s.Sp11 * idet;
-  s.cb = -s.Sp01 * idet;
-  s.cc = s.Sp00 * idet;
+  s.ca = Sp11 * idet;
+  s.cb = -Sp01 * idet;
+  s.cc = Sp00 * idet;
   s.beta = T(4) * T(s_exp(r.bx));
   if (!(oq >= T(kAlphaMin))) live = false;
   T oqs = oq >= T(kAlphaMin) ? oq : T(1);
@@ -401,48 +485,40 @@ __device__ __forceinline__ void view_forward(const Raw<C, ROT>& r, const Geo<T, 
   s.live = live;
 }
 
-// Gradients w.r.t. the view-independent quantities, summed over views
-// (accumulated in float32: each view's contribution is evaluated in T).
-template <typename T, int C>
-struct GeoGrad {
-  float Sx[3][3];
-  float Sxq[3][Cdim<C>::V];
-  float Z[Cdim<C>::V][Cdim<C>::V];   // w.r.t. Sigma_q^-1 (symmetric part used)
-  float Lh[Cdim<C>::V][Cdim<C>::V];  // w.r.t. chol(Sigma_q) (lower)
-  float mu[3], muq[Cdim<C>::V], bq[Cdim<C>::V], bt[Cdim<C>::V];
-  float bx, o, rgb[3];
+// The gradients w.r.t. the view-independent quantities, summed over views,
+// live in LDS, one float32 each (each view's contribution is evaluated in T):
+// entry k of a primitive in row k.  Rows: G_Sc (6), G_A (3 C), G_Li (lower
+// triangle, row-major), mu_x, mu_q, b_q, bt, b_x, o, rgb.
+struct GradRows {
+  int sc, a, li, mu, muq, bq, bt, bx, o, rgb, N;
 };
-
-template <typename T, int C>
-__device__ __forceinline__ void geograd_zero(GeoGrad<T, C>& G) {
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-#pragma unroll
-    for (int b = 0; b < 3; ++b) G.Sx[a][b] = T(0);
-#pragma unroll
-    for (int k = 0; k < C; ++k) G.Sxq[a][k] = T(0);
-    G.mu[a] = T(0);
-    G.rgb[a] = T(0);
-  }
-#pragma unroll
-  for (int a = 0; a < C; ++a) {
-#pragma unroll
-    for (int b = 0; b < C; ++b) { G.Z[a][b] = T(0); G.Lh[a][b] = T(0); }
-    G.muq[a] = G.bq[a] = G.bt[a] = T(0);
-  }
-  G.bx = G.o = T(0);
+__host__ __device__ constexpr GradRows grad_rows(int C) {
+  GradRows r{};
+  int k = 0;
+  r.sc = k; k += 6;
+  r.a = k; k += 3 * C;
+  r.li = k; k += C * (C + 1) / 2;
+  r.mu = k; k += 3;
+  r.muq = k; k += C;
+  r.bq = k; k += C;
+  r.bt = k; k += C;
+  r.bx = k; k += 1;
+  r.o = k; k += 1;
+  r.rgb = k; k += 3;
+  r.N = k;
+  return r;
 }
 
 // Adjoint of view_forward for one view.  gr: d loss / d record fields
-// (mx, my, a, b, c, o(q), beta, r, g, b).
-template <typename T, int C, int ROT>
-__device__ __forceinline__ void view_backward(const Raw<C, ROT>& r, const Geo<T, C, ROT>& g,
-                                              const DevView& V, const ViewState<T, C>& s,
-                                              const float* gr, GeoGrad<T, C>& G) {
-  G.rgb[0] += T(gr[7]);
-  G.rgb[1] += T(gr[8]);
-  G.rgb[2] += T(gr[9]);
-  G.bx += T(gr[6]) * s.beta;
+// (mx, my, a, b, c, o(q), beta, r, g, b); add(row, x) adds to a gradient row.
+template <typename T, int C, int ROT, typename Add>
+__device__ __forceinline__ void view_backward(const Geo<T, C, ROT>& g, const DevView& V,
+                                              const ViewState<T, C>& s, const float* gr, Add add) {
+  constexpr GradRows row = grad_rows(C);
+  add(row.rgb, T(gr[7]));
+  add(row.rgb + 1, T(gr[8]));
+  add(row.rgb + 2, T(gr[9]));
+  add(row.bx, T(gr[6]) * s.beta);
   // conic = Sigma'^-1:  G_Sigma' = -A G_A A with G_A = [[ga, gb/2], [gb/2, gc]]
   T a = s.ca, b = s.cb, c = s.cc;
   T ga = T(gr[2]), gb = T(0.5) * T(gr[3]), gc = T(gr[4]);
@@ -452,160 +528,91 @@ __device__ __forceinline__ void view_backward(const Raw<C, ROT>& r, const Geo<T,
   T G01 = -(P00 * b + P01 * c);
   T G11 = -(P10 * b + P11 * c);
   // Sigma' = Tm Sc Tm^T + 0.3 I
-  T Gs[2][2] = {{G00, G01}, {G01, G11}};
-  T GT[2][3];   // Gs Tm
+  T GT[2][3];   // G_Sigma' Tm
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < 3; ++j) {
+    GT[0][j] = G00 * s.Tm[0][j] + G01 * s.Tm[1][j];
+    GT[1][j] = G01 * s.Tm[0][j] + G11 * s.Tm[1][j];
+  }
 #pragma unroll
-    for (int j = 0; j < 3; ++j) GT[i][j] = Gs[i][0] * s.Tm[0][j] + Gs[i][1] * s.Tm[1][j];
-  T Gc[3][3];   // Tm^T Gs Tm
+  for (int i = 0; i < 3; ++i)   // G_Sc = Tm^T G_Sigma' Tm
 #pragma unroll
-  for (int i = 0; i < 3; ++i)
+    for (int j = i; j < 3; ++j) add(row.sc + sym3(i, j), s.Tm[0][i] * GT[0][j] + s.Tm[1][i] * GT[1][j]);
+  T GTm[2][3];  // 2 G_Sigma' Tm Sc
 #pragma unroll
-    for (int j = 0; j < 3; ++j) Gc[i][j] = s.Tm[0][i] * GT[0][j] + s.Tm[1][i] * GT[1][j];
-  T GTm[2][3];  // 2 Gs Tm Sc
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      GTm[i][j] = T(2) * (GT[i][0] * s.Sc[0][j] + GT[i][1] * s.Sc[1][j] + GT[i][2] * s.Sc[2][j]);
+  for (int j = 0; j < 3; ++j) {
+    GTm[0][j] = T(2) * (G00 * s.U[0][j] + G01 * s.U[1][j]);
+    GTm[1][j] = T(2) * (G01 * s.U[0][j] + G11 * s.U[1][j]);
+  }
   // Tm = J W  ->  G_J = GTm W^T  (W row-major in V.R)
   T GJ00 = GTm[0][0] * T(V.R[0]) + GTm[0][1] * T(V.R[1]) + GTm[0][2] * T(V.R[2]);
   T GJ02 = GTm[0][0] * T(V.R[6]) + GTm[0][1] * T(V.R[7]) + GTm[0][2] * T(V.R[8]);
   T GJ11 = GTm[1][0] * T(V.R[3]) + GTm[1][1] * T(V.R[4]) + GTm[1][2] * T(V.R[5]);
   T GJ12 = GTm[1][0] * T(V.R[6]) + GTm[1][1] * T(V.R[7]) + GTm[1][2] * T(V.R[8]);
-  T z = s.p[2];
-  T iz = T(1) / z, iz2 = iz * iz, iz3 = iz2 * iz;
-  T fx = T(V.fx), fy = T(V.fy);
+  // p -> (fx p_x / z, fy p_y / z), J00 = fx / z, J02 = -fx p_x / z^2, ...
+  T iz = s.iz;
+  T fxz = T(V.fx) * iz, fyz = T(V.fy) * iz;
+  T xz = s.p[0] * iz, yz = s.p[1] * iz;
   T gmx = T(gr[0]), gmy = T(gr[1]);
   T gp[3];
-  gp[0] = gmx * fx * iz + GJ02 * (-fx * iz2);
-  gp[1] = gmy * fy * iz + GJ12 * (-fy * iz2);
-  gp[2] = gmx * (-fx * s.p[0] * iz2) + gmy * (-fy * s.p[1] * iz2) + GJ00 * (-fx * iz2) +
-          GJ02 * (T(2) * fx * s.p[0] * iz3) + GJ11 * (-fy * iz2) + GJ12 * (T(2) * fy * s.p[1] * iz3);
+  gp[0] = fxz * (gmx - GJ02 * iz);
+  gp[1] = fyz * (gmy - GJ12 * iz);
+  gp[2] = fxz * (T(2) * GJ02 * iz * xz - gmx * xz - GJ00 * iz) +
+          fyz * (T(2) * GJ12 * iz * yz - gmy * yz - GJ11 * iz);
   T gmc[3];
 #pragma unroll
   for (int j = 0; j < 3; ++j)
     gmc[j] = T(V.R[j]) * gp[0] + T(V.R[3 + j]) * gp[1] + T(V.R[6 + j]) * gp[2];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    G.mu[i] += gmc[i];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) G.Sx[i][j] += Gc[i][j];
-  }
   T goq = T(gr[5]);
   if constexpr (C == 0) {
-    G.o += goq;
+    add(row.o, goq);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) add(row.mu + i, gmc[i]);
   } else {
-    // ---- conditioning ----
-    // Z = Sigma_q^-1 = Li^T Li
-    T Z[Cdim<C>::V][Cdim<C>::V];
-#pragma unroll
-    for (int i = 0; i < C; ++i)
-#pragma unroll
-      for (int j = 0; j < C; ++j) {
-        T acc = T(0);
-#pragma unroll
-        for (int k = 0; k < C; ++k) acc += g.Li[k][i] * g.Li[k][j];
-        Z[i][j] = acc;
-      }
-    T Dv[Cdim<C>::V], ZDv[Cdim<C>::V], u[Cdim<C>::V], Zu[Cdim<C>::V];
-#pragma unroll
-    for (int k = 0; k < C; ++k) Dv[k] = g.bt[k] * s.v[k];
+    // mu_c = mu_x + A y, y = Li diag(bt) v
+    T gy[Cdim<C>::V];
 #pragma unroll
     for (int k = 0; k < C; ++k) {
-      T acc = T(0), acc2 = T(0);
+      gy[k] = g.A[0][k] * gmc[0] + g.A[1][k] * gmc[1] + g.A[2][k] * gmc[2];
 #pragma unroll
-      for (int m = 0; m < C; ++m) acc += Z[k][m] * Dv[m];
-      ZDv[k] = acc;
-#pragma unroll
-      for (int m = 0; m < 3; ++m) acc2 += g.Sxq[m][k] * gmc[m];
-      u[k] = acc2;
+      for (int i = 0; i < 3; ++i) add(row.a + C * i + k, gmc[i] * s.y[k]);
     }
-#pragma unroll
-    for (int k = 0; k < C; ++k) {
-      T acc = T(0);
-#pragma unroll
-      for (int m = 0; m < C; ++m) acc += Z[k][m] * u[m];
-      Zu[k] = acc;
-    }
-    // Q = Sxq^T G Sxq ; GS = G Sxq
-    T GS[3][Cdim<C>::V];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int k = 0; k < C; ++k)
-        GS[i][k] = Gc[i][0] * g.Sxq[0][k] + Gc[i][1] * g.Sxq[1][k] + Gc[i][2] * g.Sxq[2][k];
-    T Q[Cdim<C>::V][Cdim<C>::V];
-#pragma unroll
-    for (int k = 0; k < C; ++k)
-#pragma unroll
-      for (int l = 0; l < C; ++l)
-        Q[k][l] = g.Sxq[0][k] * GS[0][l] + g.Sxq[1][k] * GS[1][l] + g.Sxq[2][k] * GS[2][l];
-    // G_Sxq += gmc (Z Dv)^T - G Sxq (Z D + D Z)
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int l = 0; l < C; ++l) {
-        T acc = gmc[i] * ZDv[l];
-#pragma unroll
-        for (int k = 0; k < C; ++k) acc -= GS[i][k] * (Z[k][l] * g.bt[l] + g.bt[k] * Z[k][l]);
-        G.Sxq[i][l] += acc;
-      }
-    // G_Z += sym(u Dv^T) - (Q D + D Q)/2
-#pragma unroll
-    for (int k = 0; k < C; ++k)
-#pragma unroll
-      for (int l = 0; l < C; ++l)
-        G.Z[k][l] += T(0.5) * (u[k] * Dv[l] + Dv[k] * u[l]) - T(0.5) * (Q[k][l] * g.bt[l] + g.bt[k] * Q[k][l]);
-    // d bt_k += (Z u)_k v_k - (Z Q)_kk ;  g_v += bt (Z u)
-    T gv[Cdim<C>::V];
-#pragma unroll
-    for (int k = 0; k < C; ++k) {
-      T zq = T(0);
-#pragma unroll
-      for (int m = 0; m < C; ++m) zq += Z[k][m] * Q[m][k];
-      G.bt[k] += Zu[k] * s.v[k] - zq;
-      gv[k] = g.bt[k] * Zu[k];
-    }
-    // ---- opacity ----  o(q) = o exp(sum e_i ell_i),  ell = log(1 - tanh(w^2))
-    T prod;
-    {
-      T lsum = T(0);
-#pragma unroll
-      for (int i = 0; i < C; ++i) lsum += g.e[i] * s.ell[i];
-      prod = T(s_exp(float(lsum)));
-    }
-    G.o += goq * prod;
+    // ---- opacity ----  o(q) = o exp(sum e_i ell_i),  ell = log(1 - tanh(w^2)),
+    // d ell / d w = -2 w (1 + tanh(w^2))
+    add(row.o, goq * s.prod);
+    const T go = goq * s.oq;
     T gw[Cdim<C>::V];
 #pragma unroll
     for (int i = 0; i < C; ++i) {
       if (g.beta_opacity) {
-        G.bq[i] += goq * s.oq * s.ell[i] * g.e[i];
-        T x = s.w[i] * s.w[i];
-        T th = T(tanhf(float(x)));
-        gw[i] = goq * s.oq * g.e[i] * (-(T(1) + th)) * T(2) * s.w[i];
+        const T ge = go * g.e[i];
+        add(row.bq + i, ge * s.ell[i]);
+        gw[i] = T(-4) * ge * s.rt[i] * s.w[i];
       } else {
-        gw[i] = -goq * s.oq * s.w[i];   // d(-w^2/2)/dw; no b_q dependence
+        gw[i] = -go * s.w[i];   // d(-w^2/2)/dw; no b_q dependence
       }
     }
-    // w = Li v:  g_v += Li^T gw ; G_Lh += -tril((Li^T gw) w^T)
-    T ut[Cdim<C>::V];
+    // w = Li v, y = Li diag(bt) v
+    T gv[Cdim<C>::V];
 #pragma unroll
     for (int k = 0; k < C; ++k) {
-      T acc = T(0);
+      T ty = g.Li[k][k] * gy[k], tw = g.Li[k][k] * gw[k];
 #pragma unroll
-      for (int i = k; i < C; ++i) acc += g.Li[i][k] * gw[i];
-      ut[k] = acc;
-      gv[k] += acc;
+      for (int i = k + 1; i < C; ++i) {
+        ty += g.Li[i][k] * gy[i];
+        tw += g.Li[i][k] * gw[i];
+      }
+      add(row.bt + k, ty * s.v[k]);
+      gv[k] = g.bt[k] * ty + tw;
     }
 #pragma unroll
     for (int i = 0; i < C; ++i)
 #pragma unroll
-      for (int j = 0; j <= i; ++j) G.Lh[i][j] -= ut[i] * s.w[j];
+      for (int j = 0; j <= i; ++j)
+        add(row.li + i * (i + 1) / 2 + j, (gy[i] * g.bt[j] + gw[i]) * s.v[j]);
     // v = q - mu_q ; q = [t, d] or d ; d = unit(mu_x - cam)
 #pragma unroll
-    for (int k = 0; k < C; ++k) G.muq[k] -= gv[k];
+    for (int k = 0; k < C; ++k) add(row.muq + k, -gv[k]);
     T gd[3] = {T(0), T(0), T(0)};
     if constexpr (C >= 4) { gd[0] = gv[1]; gd[1] = gv[2]; gd[2] = gv[3]; }
     else if constexpr (C == 3) { gd[0] = gv[0]; gd[1] = gv[1]; gd[2] = gv[2]; }
@@ -614,138 +621,136 @@ __device__ __forceinline__ void view_backward(const Raw<C, ROT>& r, const Geo<T,
       for (int k = 0; k < C; ++k) gd[k] = gv[k];
     }
     T dg = s.dir[0] * gd[0] + s.dir[1] * gd[1] + s.dir[2] * gd[2];
-    T idist = T(1) / s.dist;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) G.mu[k] += (gd[k] - s.dir[k] * dg) * idist;
+    for (int k = 0; k < 3; ++k) add(row.mu + k, gmc[k] + (gd[k] - s.dir[k] * dg) * s.idist);
   }
 }
 
 // Final chain from the view-independent gradients to the raw parameters.
-// out[] is indexed by parameter row.
-template <typename T, int C, int ROT>
+// grad(row) is the sum of a gradient row; out(row, value) takes the gradient of
+// one parameter row.
+template <typename T, int C, int ROT, typename Grad, typename Out>
 __device__ __forceinline__ void geo_backward(const Raw<C, ROT>& r, const Geo<T, C, ROT>& g,
-                                             const GeoGrad<T, C>& G, float* out) {
+                                             Grad grad, Out out) {
   const ParamRows pr = param_rows(C, ROT);
+  constexpr GradRows row = grad_rows(C);
+  T Gsc[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) Gsc[k] = T(grad(row.sc + k));
   T GM[3][3];
-  // Sigma_x = M M^T (G_Sx symmetric): G_M = 2 G_Sx M
+  // Sigma_c = M M^T - ... (G_Sc symmetric): G_M = 2 G_Sc M
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int j = 0; j < 3; ++j)
-      GM[i][j] = (G.Sx[i][0] + G.Sx[0][i]) * g.M[0][j] + (G.Sx[i][1] + G.Sx[1][i]) * g.M[1][j] +
-                 (G.Sx[i][2] + G.Sx[2][i]) * g.M[2][j];
+      GM[i][j] = T(2) * (Gsc[sym3(i, 0)] * g.M[0][j] + Gsc[sym3(i, 1)] * g.M[1][j] +
+                         Gsc[sym3(i, 2)] * g.M[2][j]);
   if constexpr (C > 0) {
-    T Z[Cdim<C>::V][Cdim<C>::V];
+    // Sigma_c = Sigma_x - (A H^T + H A^T) / 2: G_A -= G_Sc H, G_H = -G_Sc A;
+    // A = Sigma_xq Li^T, H = Sigma_xq diag(bt) Li^T
+    T GL[Cdim<C>::V][Cdim<C>::V];   // w.r.t. Li (lower triangle)
+    T GX[3][Cdim<C>::V];            // w.r.t. Sigma_xq
+    T Gbt[Cdim<C>::V];
 #pragma unroll
-    for (int i = 0; i < C; ++i)
+    for (int i = 0; i < C; ++i) {
+#pragma unroll
+      for (int j = 0; j <= i; ++j) GL[i][j] = T(grad(row.li + i * (i + 1) / 2 + j));
+      Gbt[i] = T(grad(row.bt + i));
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      T GA[Cdim<C>::V], GH[Cdim<C>::V];
+#pragma unroll
+      for (int k = 0; k < C; ++k) {
+        GA[k] = T(grad(row.a + C * a + k));
+        GH[k] = T(0);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          GA[k] -= Gsc[sym3(a, b)] * g.H[b][k];
+          GH[k] -= Gsc[sym3(a, b)] * g.A[b][k];
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < C; ++m) {
+        T xa = GA[m] * g.Li[m][m], xh = GH[m] * g.Li[m][m];
+#pragma unroll
+        for (int k = m + 1; k < C; ++k) {
+          xa += GA[k] * g.Li[k][m];
+          xh += GH[k] * g.Li[k][m];
+        }
+        GX[a][m] = xa + g.bt[m] * xh;
+        Gbt[m] += g.Sxq[a][m] * xh;
+#pragma unroll
+        for (int k = m; k < C; ++k) GL[k][m] += (GA[k] + GH[k] * g.bt[m]) * g.Sxq[a][m];
+      }
+    }
+    // W = sym(-GL Li^T) (lower triangle mirrored): G_Sq + G_Sq^T = Li^T W Li
+    T GSs[Cdim<C>::V][Cdim<C>::V];
+    {
+      T W[Cdim<C>::V][Cdim<C>::V];
+#pragma unroll
+      for (int i = 0; i < C; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+          T acc = GL[i][0] * g.Li[j][0];
+#pragma unroll
+          for (int k = 1; k <= j; ++k) acc += GL[i][k] * g.Li[j][k];
+          W[i][j] = W[j][i] = -acc;
+        }
 #pragma unroll
       for (int j = 0; j < C; ++j) {
-        T acc = T(0);
+        T WL[Cdim<C>::V];   // column j of W Li
 #pragma unroll
-        for (int k = 0; k < C; ++k) acc += g.Li[k][i] * g.Li[k][j];
-        Z[i][j] = acc;
+        for (int i = 0; i < C; ++i) {
+          T acc = W[i][j] * g.Li[j][j];
+#pragma unroll
+          for (int k = j + 1; k < C; ++k) acc += W[i][k] * g.Li[k][j];
+          WL[i] = acc;
+        }
+#pragma unroll
+        for (int i = j; i < C; ++i) {
+          T acc = g.Li[i][i] * WL[i];
+#pragma unroll
+          for (int k = i + 1; k < C; ++k) acc += g.Li[k][i] * WL[k];
+          GSs[i][j] = GSs[j][i] = acc;
+        }
       }
-    // G_Sq = -Z sym(G_Z) Z + sym(Li^T Phi(Lh^T G_Lh) Li)
-    T GSq[Cdim<C>::V][Cdim<C>::V];
-    {
-      T A1[Cdim<C>::V][Cdim<C>::V];
-#pragma unroll
-      for (int i = 0; i < C; ++i)
-#pragma unroll
-        for (int j = 0; j < C; ++j) {
-          T acc = T(0);
-#pragma unroll
-          for (int k = 0; k < C; ++k) acc += Z[i][k] * T(0.5) * (G.Z[k][j] + G.Z[j][k]);
-          A1[i][j] = acc;
-        }
-#pragma unroll
-      for (int i = 0; i < C; ++i)
-#pragma unroll
-        for (int j = 0; j < C; ++j) {
-          T acc = T(0);
-#pragma unroll
-          for (int k = 0; k < C; ++k) acc += A1[i][k] * Z[k][j];
-          GSq[i][j] = -acc;
-        }
-      T Pm[Cdim<C>::V][Cdim<C>::V];   // Phi(Lh^T G_Lh)
-#pragma unroll
-      for (int i = 0; i < C; ++i)
-#pragma unroll
-        for (int j = 0; j < C; ++j) {
-          if (j > i) { Pm[i][j] = T(0); continue; }
-          T acc = T(0);
-#pragma unroll
-          for (int k = 0; k < C; ++k) acc += g.Lh[k][i] * G.Lh[k][j];
-          Pm[i][j] = (i == j) ? T(0.5) * acc : acc;
-        }
-      T B1[Cdim<C>::V][Cdim<C>::V];   // Li^T Pm
-#pragma unroll
-      for (int i = 0; i < C; ++i)
-#pragma unroll
-        for (int j = 0; j < C; ++j) {
-          T acc = T(0);
-#pragma unroll
-          for (int k = 0; k < C; ++k) acc += g.Li[k][i] * Pm[k][j];
-          B1[i][j] = acc;
-        }
-      T S1[Cdim<C>::V][Cdim<C>::V];   // B1 Li
-#pragma unroll
-      for (int i = 0; i < C; ++i)
-#pragma unroll
-        for (int j = 0; j < C; ++j) {
-          T acc = T(0);
-#pragma unroll
-          for (int k = 0; k < C; ++k) acc += B1[i][k] * g.Li[k][j];
-          S1[i][j] = acc;
-        }
-#pragma unroll
-      for (int i = 0; i < C; ++i)
-#pragma unroll
-        for (int j = 0; j < C; ++j) GSq[i][j] += T(0.5) * (S1[i][j] + S1[j][i]);
     }
     // Sigma_q = Lqx Lqx^T + Lq Lq^T ; Sigma_xq = M Lqx^T
-    T GSs[Cdim<C>::V][Cdim<C>::V];   // G_Sq + G_Sq^T
-#pragma unroll
-    for (int i = 0; i < C; ++i)
-#pragma unroll
-      for (int j = 0; j < C; ++j) GSs[i][j] = GSq[i][j] + GSq[j][i];
 #pragma unroll
     for (int k = 0; k < C; ++k)
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        T acc = T(0);
+        T acc = GX[0][k] * g.M[0][j] + GX[1][k] * g.M[1][j] + GX[2][k] * g.M[2][j];
 #pragma unroll
         for (int m = 0; m < C; ++m) acc += GSs[k][m] * T(r.lqx[m][j]);
-#pragma unroll
-        for (int m = 0; m < 3; ++m) acc += G.Sxq[m][k] * g.M[m][j];
-        out[pr.lqx + 3 * k + j] = float(acc);
+        out(pr.lqx + 3 * k + j, float(acc));
       }
     int idx = 0;
 #pragma unroll
     for (int i = 0; i < C; ++i)
 #pragma unroll
       for (int j = 0; j <= i; ++j) {
-        T acc = T(0);
+        const T Ljj = lq_entry<T, C, ROT>(r, j, j);
+        T acc = GSs[i][j] * Ljj;
 #pragma unroll
-        for (int m = j; m < C; ++m) acc += GSs[i][m] * lq_entry<T, C, ROT>(r, m, j);
-        out[pr.lq + idx] = float(i == j ? acc * lq_entry<T, C, ROT>(r, i, i) : acc);
+        for (int m = j + 1; m < C; ++m) acc += GSs[i][m] * T(r.lq[m][j]);
+        out(pr.lq + idx, float(i == j ? acc * Ljj : acc));
         ++idx;
       }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        T acc = T(0);
 #pragma unroll
-        for (int k = 0; k < C; ++k) acc += G.Sxq[i][k] * T(r.lqx[k][j]);
-        GM[i][j] += acc;
+        for (int k = 0; k < C; ++k) GM[i][j] += GX[i][k] * T(r.lqx[k][j]);
       }
 #pragma unroll
     for (int k = 0; k < C; ++k) {
-      out[pr.mu_q + k] = float(G.muq[k]);
-      T gbq = G.bq[k];
-      if (g.beta_cond && r.bq[k] < 0.0f) gbq += G.bt[k] * g.bt[k];
-      out[pr.b_q + k] = float(gbq);
+      out(pr.mu_q + k, grad(row.muq + k));
+      T gbq = T(grad(row.bq + k));
+      if (g.beta_cond && r.bq[k] < 0.0f) gbq += Gbt[k] * g.bt[k];
+      out(pr.b_q + k, float(gbq));
     }
   }
   // M = R diag(s)
@@ -758,7 +763,7 @@ __device__ __forceinline__ void geo_backward(const Raw<C, ROT>& r, const Geo<T, 
       GR[i][j] = GM[i][j] * g.s[j];
       acc += GM[i][j] * g.M[i][j];   // M = R diag(s): d/d log s_j = sum_i GM_ij R_ij s_j
     }
-    out[pr.log_s + j] = float(acc);
+    out(pr.log_s + j, float(acc));
   }
   if (ROT == UBS_ROT_QUAT) {
     T iq = m_rsqrt<T>(T(r.rq[0]) * T(r.rq[0]) + T(r.rq[1]) * T(r.rq[1]) +
@@ -772,22 +777,22 @@ __device__ __forceinline__ void geo_backward(const Raw<C, ROT>& r, const Geo<T, 
     T gz = T(2) * (-T(2) * z * GR[0][0] - w * GR[0][1] + x * GR[0][2] + w * GR[1][0] - T(2) * z * GR[1][1] +
                    y * GR[1][2] + x * GR[2][0] + y * GR[2][1]);
     T dotq = w * gw + x * gx + y * gy + z * gz;
-    out[pr.rot + 0] = float((gw - w * dotq) * iq);
-    out[pr.rot + 1] = float((gx - x * dotq) * iq);
-    out[pr.rot + 2] = float((gy - y * dotq) * iq);
-    out[pr.rot + 3] = float((gz - z * dotq) * iq);
+    out(pr.rot + 0, float((gw - w * dotq) * iq));
+    out(pr.rot + 1, float((gx - x * dotq) * iq));
+    out(pr.rot + 2, float((gy - y * dotq) * iq));
+    out(pr.rot + 3, float((gz - z * dotq) * iq));
   } else {
-    out[pr.rot + 0] = float(GR[2][1] - GR[1][2]);
-    out[pr.rot + 1] = float(GR[0][2] - GR[2][0]);
-    out[pr.rot + 2] = float(GR[1][0] - GR[0][1]);
+    out(pr.rot + 0, float(GR[2][1] - GR[1][2]));
+    out(pr.rot + 1, float(GR[0][2] - GR[2][0]));
+    out(pr.rot + 2, float(GR[1][0] - GR[0][1]));
   }
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    out[pr.mu_x + k] = float(G.mu[k]);
-    out[pr.rgb + k] = float(G.rgb[k]);
+    out(pr.mu_x + k, grad(row.mu + k));
+    out(pr.rgb + k, grad(row.rgb + k));
   }
-  out[pr.b_x] = float(G.bx);
-  out[pr.o] = float(G.o);
+  out(pr.b_x, grad(row.bx));
+  out(pr.o, grad(row.o));
 }
 
 }  // namespace ubs

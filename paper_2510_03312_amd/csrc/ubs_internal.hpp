@@ -33,7 +33,8 @@ struct DevView {
   uint32_t tile_base;    // first global tile of the view
   uint32_t rec_base;     // first record of the view
   uint32_t pix_base;     // first pixel of the view
-  uint32_t _pad[3];
+  uint32_t order_slot;   // the view's place in the list of views by scene
+  uint32_t _pad[2];
 };
 static_assert(sizeof(DevView) % 16 == 0, "DevView alignment");
 
@@ -43,6 +44,7 @@ struct DevScene {
   int64_t n;
   int32_t dim, rot, F;
   uint32_t variant;    // UBS_TUNE_NO_BETA_* bits of the frame (Sec. 5.3 ablations)
+  int32_t view0, n_views;   // its views: entries [view0, view0 + n_views) of the list by scene
   int64_t prim_base;   // first entry of this scene in per-primitive tables
   int64_t list_base;   // first entry of this scene's kept lists
   int64_t par_base;    // first float of this scene's compacted parameter copy
@@ -129,7 +131,6 @@ struct LiveIn {
   const float* par;
 };
 
-
 // Status block, mirrors ubs_status_block.
 struct DevStatus {
   unsigned long long pairs_needed;
@@ -157,7 +158,7 @@ static_assert(sizeof(DevStatus) == sizeof(ubs_status_block), "status block size"
 // Full private layout of the workspace (superset of ubs_layout).
 struct Layout {
   ubs_layout pub;
-  uint64_t off_views, off_scenes, off_offsets, off_blocksums;
+  uint64_t off_views, off_view_order, off_scenes, off_offsets, off_blocksums;
   uint64_t off_tile_counts, off_tile_cursor;  // pairs per tile (+2 counters); segment cursors
   uint64_t off_big_tiles;            // tiles sorted by a workgroup (more than 256 pairs)
   uint64_t off_hit_mask;             // per record: hits among its candidate tiles
