@@ -487,11 +487,9 @@ __global__ void __launch_bounds__(kScanThreads) scan_tile_sums_scan_kernel(
   if (threadIdx.x == 0 && total_out != nullptr) *total_out = carry;
 }
 
-// With `list` (0/1 inputs only), also the compaction: list[out[i]] = i for
-// every set in[i].
 __global__ void __launch_bounds__(kScanThreads) scan_apply_kernel(
     const uint32_t* __restrict__ in, uint32_t n, const uint32_t* __restrict__ tile_sums,
-    uint32_t* __restrict__ out, uint32_t* __restrict__ list) {
+    uint32_t* __restrict__ out) {
   __shared__ uint32_t lds[8];
   const size_t base = size_t(blockIdx.x) * kScanTile + size_t(threadIdx.x) * kScanItems;
   uint32_t vals[kScanItems];
@@ -505,10 +503,7 @@ __global__ void __launch_bounds__(kScanThreads) scan_apply_kernel(
   uint32_t run = block_exclusive_scan_u32(s, lds, &tot) + tile_sums[blockIdx.x];
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
-    if (base + k < n) {
-      out[base + k] = run;
-      if (list != nullptr && vals[k] != 0u) list[run] = uint32_t(base + k);
-    }
+    if (base + k < n) out[base + k] = run;
     run += vals[k];
   }
 }
@@ -699,7 +694,7 @@ constexpr uint32_t kSingleChunk = uint32_t(kSingleThreads * kSingleItems);
 // (order: also the tile order of the counts in `in`, when not null)
 __global__ void __launch_bounds__(kSingleThreads) scan_single_kernel(
     const uint32_t* __restrict__ in, uint32_t n, uint32_t* __restrict__ out,
-    uint32_t* __restrict__ list, DevStatus* __restrict__ status, unsigned long long capacity,
+    DevStatus* __restrict__ status, unsigned long long capacity,
     unsigned long long* __restrict__ total_out, uint32_t* __restrict__ order) {
   static_assert(kSingleThreads == kOrderBins, "the tile order takes the scan's workgroup");
   constexpr int W = kSingleThreads / 64;
@@ -753,7 +748,7 @@ __global__ void __launch_bounds__(kSingleThreads) scan_single_kernel(
     }
     __syncthreads();
     uint32_t run = carry + before + x - sum;
-    if (vec && list == nullptr && base + kSingleItems <= n) {
+    if (vec && base + kSingleItems <= n) {
       uint32_t o[kSingleItems];
 #pragma unroll
       for (int k = 0; k < kSingleItems; ++k) { o[k] = run; run += vals[k]; }
@@ -762,10 +757,7 @@ __global__ void __launch_bounds__(kSingleThreads) scan_single_kernel(
     } else {
 #pragma unroll
       for (int k = 0; k < kSingleItems; ++k) {
-        if (base + k < n) {
-          out[base + k] = run;
-          if (list != nullptr && vals[k] != 0u) list[run] = base + k;
-        }
+        if (base + k < n) out[base + k] = run;
         run += vals[k];
       }
     }
@@ -784,10 +776,11 @@ __global__ void __launch_bounds__(kSingleThreads) scan_single_kernel(
   }
 }
 
-static hipError_t scan_impl(const uint32_t* in, uint32_t n, uint32_t* tile_sums, uint32_t* out,
-                            uint32_t* list, DevStatus* status, unsigned long long capacity,
-                            hipStream_t st, unsigned long long* total_out,
-                            uint32_t* order = nullptr, uint32_t* order_hist = nullptr) {
+// order (when not null): the rasters' tile order, longest tiles first;
+// order_hist: order_hist_words(n) words for it.
+hipError_t launch_scan(const uint32_t* in, uint32_t n, uint32_t* tile_sums, uint32_t* out,
+                       DevStatus* status, unsigned long long capacity, hipStream_t st,
+                       unsigned long long* total_out, uint32_t* order, uint32_t* order_hist) {
   // the tile order: by the scan's own workgroup up to kOrderOneRound tiles,
   // else by its kernels
   if (order != nullptr && n > kOrderOneRound) {
@@ -801,7 +794,7 @@ static hipError_t scan_impl(const uint32_t* in, uint32_t n, uint32_t* tile_sums,
   }
   if (n <= kSingleScanMax) {
     hipLaunchKernelGGL(scan_single_kernel, dim3(1), dim3(kSingleThreads), 0, st, in, n, out,
-                       list, status, capacity, total_out, order);
+                       status, capacity, total_out, order);
     return hipGetLastError();
   }
   const uint32_t n_tiles = (n + kScanTile - 1) / kScanTile;
@@ -812,29 +805,12 @@ static hipError_t scan_impl(const uint32_t* in, uint32_t n, uint32_t* tile_sums,
                      n_tiles, status, capacity, total_out);
   if (n_tiles > 0)
     hipLaunchKernelGGL(scan_apply_kernel, dim3(n_tiles), dim3(kScanThreads), 0, st, in, n,
-                       tile_sums, out, list);
+                       tile_sums, out);
   return hipGetLastError();
-}
-
-// order (when not null): the rasters' tile order, longest tiles first;
-// order_hist: order_hist_words(n) words for it.
-hipError_t launch_scan(const uint32_t* in, uint32_t n, uint32_t* tile_sums, uint32_t* out,
-                       DevStatus* status, unsigned long long capacity, hipStream_t st,
-                       unsigned long long* total_out, uint32_t* order, uint32_t* order_hist) {
-  return scan_impl(in, n, tile_sums, out, nullptr, status, capacity, st, total_out, order,
-                   order_hist);
 }
 
 uint64_t order_hist_words(uint64_t n_tiles) {
   return uint64_t(kOrderBins) * ((n_tiles + kOrderGroupTiles - 1) / kOrderGroupTiles);
-}
-
-// Exclusive scan of a 0/1 flag array and, in the same pass, the compacted
-// list of its set entries (ascending); *total_out gets their number.
-hipError_t launch_scan_compact(const uint32_t* flags, uint32_t n, uint32_t* tile_sums,
-                               uint32_t* offsets, uint32_t* list, hipStream_t st,
-                               unsigned long long* total_out) {
-  return scan_impl(flags, n, tile_sums, offsets, list, nullptr, 0ull, st, total_out);
 }
 
 hipError_t launch_bin_emit(const float* records, const uint8_t* live, const DevView* views,
