@@ -402,7 +402,7 @@ ubs_status ubs_relocate(int32_t dim, int32_t rot, int64_t n, float* params, floa
  * forbid hipMalloc.  Same arguments, semantics and results as ubs_relocate
  * (minus ws, ws_bytes, ws_bytes_needed).  The workspace is a static device
  * array inside the library of the size ubs_relocate needs for
- * UBS_RELOCATE_NOALLOC_MAX_N primitives (about 48 MiB), one per GPU, held
+ * UBS_RELOCATE_NOALLOC_MAX_N primitives (about 64 MiB), one per GPU, held
  * until the process ends; its address is looked up on the first call on
  * each device (the device current at the call).  Every call on a GPU uses
  * that GPU's one array: calls that overlap in time on one GPU (other

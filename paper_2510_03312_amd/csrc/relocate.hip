@@ -34,7 +34,7 @@ struct RelocState {
 };
 
 struct RelocLayout {
-  uint64_t cdf, o_keep, offs, targets, counts, sums_u32, sums_f64, state, bytes;
+  uint64_t cdf, o_keep, offs, src, targets, counts, sums_u32, sums_f64, state, bytes;
   uint32_t n_tiles;
 };
 
@@ -48,12 +48,14 @@ constexpr RelocLayout reloc_layout(int64_t n) {
   L.cdf = off;      off = align256(off + 8 * un);
   L.o_keep = off;   off = align256(off + 4 * un);
   L.offs = off;     off = align256(off + 4 * un);
+  L.src = off;      off = align256(off + 4 * un);
   L.targets = off;  off = align256(off + 4 * un);
   L.counts = off;   off = align256(off + 4 * un);
   L.sums_u32 = off; off = align256(off + 4 * (uint64_t(L.n_tiles) + 1));
   L.sums_f64 = off; off = align256(off + 8 * (uint64_t(L.n_tiles) + 1));
   L.state = off;    off = align256(off + sizeof(RelocState));
-  L.bytes = off;
+  // the size that ws_bytes has always had to be (4 bytes a primitive are spare)
+  L.bytes = align256(off + 4 * un);
   return L;
 }
 
@@ -254,20 +256,20 @@ __global__ void __launch_bounds__(kRelThreads) reloc_sample_kernel(
 
 constexpr uint32_t kUnchanged = 0xffffffffu;
 
-// The primitive whose rows i takes, in place of its slot (read by this thread
-// only), and its new opacity: o_keep holds the old ones, so no thread reads
-// what another writes.
+// The primitive whose rows i takes, and its new opacity: o_keep holds the old
+// ones, so no thread reads what another writes.
 __global__ void __launch_bounds__(kRelThreads) reloc_plan_kernel(
     float* __restrict__ params, int64_t n, int o_row, const float* __restrict__ o_keep,
     const uint32_t* __restrict__ targets, const uint32_t* __restrict__ counts,
-    const RelocState* __restrict__ state, uint32_t* __restrict__ slots) {
+    const RelocState* __restrict__ state, const uint32_t* __restrict__ slots,
+    uint32_t* __restrict__ src_of) {
   const int64_t i = int64_t(blockIdx.x) * kRelThreads + threadIdx.x;
   if (i >= n || !(state->total > 0.0)) return;
   const uint32_t slot = slots[i];
   uint32_t src = kUnchanged;
   if (slot & kDead) src = targets[slot & ~kDead];
   else if (counts[i] > 0u) src = uint32_t(i);
-  slots[i] = src;
+  src_of[i] = src;
   if (src != kUnchanged)
     params[int64_t(o_row) * n + i] =
         float(1.0 - pow(1.0 - double(o_keep[src]), 1.0 / (double(counts[src]) + 1.0)));
@@ -366,6 +368,7 @@ static ubs_status relocate_run(int32_t dim, int32_t rot, int64_t n, float* param
   double* cdf = reinterpret_cast<double*>(base + L.cdf);
   float* o_keep = reinterpret_cast<float*>(base + L.o_keep);
   uint32_t* slots = reinterpret_cast<uint32_t*>(base + L.offs);
+  uint32_t* src = reinterpret_cast<uint32_t*>(base + L.src);
   uint32_t* targets = reinterpret_cast<uint32_t*>(base + L.targets);
   uint32_t* counts = reinterpret_cast<uint32_t*>(base + L.counts);
   double* sums = reinterpret_cast<double*>(base + L.sums_f64);
@@ -383,9 +386,9 @@ static ubs_status relocate_run(int32_t dim, int32_t rot, int64_t n, float* param
   hipLaunchKernelGGL(reloc_sample_kernel, dim3(blocks), dim3(kRelThreads), 0, st, cdf, n, state,
                      uniforms, targets, counts, targets_out);
   hipLaunchKernelGGL(reloc_plan_kernel, dim3(blocks), dim3(kRelThreads), 0, st, params, n, pr.o,
-                     o_keep, targets, counts, state, slots);
+                     o_keep, targets, counts, state, slots, src);
   hipLaunchKernelGGL(reloc_apply_kernel, dim3(kApplyGroups), dim3(kRelThreads), 0, st, params, m, v,
-                     n, pr.F, pr.o, state, slots);
+                     n, pr.F, pr.o, state, src);
   return hipGetLastError() == hipSuccess ? UBS_OK : UBS_ERR_HIP;
 }
 
