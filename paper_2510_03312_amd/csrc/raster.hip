@@ -1,9 +1,9 @@
 // Per-tile rasterisation: front-to-back compositing and its adjoint.
 //
 // One wavefront (64 lanes) per tile, or per band of TH / SPLIT rows of it in
-// frames of few tiles.  Lane l owns the pixels of column l % TW in rows
-// l / TW + k * (64 / TW) of its band (a whole 16x16 tile gives each lane a
-// strip of 4 pixels).  The tile's sorted records are staged through LDS 64 at
+// frames of few tiles and for wide tiles.  Lane l owns the pixels of column
+// l % TW in rows l / TW + k * (64 / TW) of its band (a whole 16x16 tile gives
+// each lane a strip of 4 pixels).  The tile's sorted records are staged through LDS 64 at
 // a time (one per lane); every lane then walks the batch.  Because a lane's
 // pixels share one column, dx = px - mx is shared and the quadratic form
 // costs r = A + dy (B + c dy) per pixel with A, B per record.
@@ -112,7 +112,19 @@ struct TileGeom {
   static_assert(TH % SPLIT == 0 && TW * ROWS % 64 == 0 && 64 % TW == 0, "tile shape");
 };
 
-template <int TW, int TH, int BATCH, int SPLIT>
+// Two forms of the update.  NAN_ROWS: a stopped pixel (or one outside the
+// image) gets a NaN row coordinate, its r is NaN, and the support test fails
+// for every later record without a test of its own; a record is skipped whole
+// where its only pixels have stopped, and the update runs under lane masks,
+// without selects.  Otherwise a stopped pixel's transmittance is kept negated,
+// so that every later record fails its T (1 - alpha) >= 1e-4 test, and skipping
+// and stopping are taken by selects.  The first has fewer instructions where
+// the SIMDs are full, the second fewer branches in a row where they are not:
+// 16x16 tiles with 64 records a batch 63.0 / 58.7 us (1080p, selects / NaN
+// rows), with 128 37 / 42 (1280x720) and 64.6 / 64.6 (1080p), with 256 80 / 88,
+// 32x16 tiles 75 / 89 and 102 / 123, 16x8 24.5 / 25.9 and 58 / 61, 8x8 23.4 /
+// 24.4, the persistent grid 175 / 182.
+template <int TW, int TH, int BATCH, int SPLIT, bool NAN_ROWS>
 __device__ __forceinline__ void raster_fwd_tile(
     uint32_t tile, int band, float4* s0, float4* s1, float4* s2, const float* __restrict__ records,
     const uint32_t* __restrict__ values, const uint32_t* __restrict__ ranges,
@@ -128,17 +140,13 @@ __device__ __forceinline__ void raster_fwd_tile(
   const int px = tx * TW + lane % TW;
   const int py0 = ty * TH + band * TileGeom<TW, TH, SPLIT>::ROWS + lane / TW;
   const float fx = float(px) + 0.5f;
-  // fy: the pixels' row coordinates.  A pixel that has stopped (or lies
-  // outside the image) gets a NaN row: its r is NaN, so the support test
-  // fails for every later record without a test of its own, and a record is
-  // skipped whole where its only pixels have stopped
   float T[PPL], fy[PPL], cr[PPL], cg[PPL], cb[PPL];
   uint32_t last[PPL];
 #pragma unroll
   for (int k = 0; k < PPL; ++k) {
-    T[k] = 1.0f;
-    fy[k] = (px >= V.W || py0 + k * RSTEP >= V.H) ? __builtin_nanf("")
-                                                  : float(py0 + k * RSTEP) + 0.5f;
+    const bool outside = px >= V.W || py0 + k * RSTEP >= V.H;
+    T[k] = !NAN_ROWS && outside ? -1.0f : 1.0f;
+    fy[k] = NAN_ROWS && outside ? __builtin_nanf("") : float(py0 + k * RSTEP) + 0.5f;
     cr[k] = cg[k] = cb[k] = 0.0f; last[k] = 0;
   }
   const float band_y0 = float(ty * TH + band * TileGeom<TW, TH, SPLIT>::ROWS) + 0.5f;
@@ -148,7 +156,7 @@ __device__ __forceinline__ void raster_fwd_tile(
     // the tile is finished once every pixel has stopped (checked per batch)
     bool running = false;
 #pragma unroll
-    for (int k = 0; k < PPL; ++k) running = running || fy[k] == fy[k];
+    for (int k = 0; k < PPL; ++k) running = running || (NAN_ROWS ? fy[k] == fy[k] : T[k] >= 0.0f);
     if (__ballot(running) == 0ull) break;
     __syncthreads();
     // (wavefront-uniform: the record loop runs on scalar counters)
@@ -166,21 +174,27 @@ __device__ __forceinline__ void raster_fwd_tile(
       }
     } else {
       // only the records that may reach the band, their positions with them
-      bool keep = lane < nb;
-      Staged st;
-      if (keep) {
-        st = stage_record(records, values[b0 + uint32_t(lane)]);
-        keep = may_reach_rows(st, band_y0, band_y1);
+      int n_kept = 0;
+#pragma unroll
+      for (int m = 0; m < PER_LANE; ++m) {
+        const int q = m * 64 + lane;
+        bool keep = q < nb;
+        Staged st;
+        if (keep) {
+          st = stage_record(records, values[b0 + uint32_t(q)]);
+          keep = may_reach_rows(st, band_y0, band_y1);
+        }
+        const uint64_t kept = __ballot(keep);
+        if (keep) {
+          const int at = n_kept + __popcll(kept & ((1ull << lane) - 1ull));
+          st.g2.w = __uint_as_float(b0 - start + uint32_t(q) + 1u);
+          s0[at] = st.g0;
+          s1[at] = st.g1;
+          s2[at] = st.g2;
+        }
+        n_kept += __popcll(kept);
       }
-      const uint64_t kept = __ballot(keep);
-      if (keep) {
-        const int at = __popcll(kept & ((1ull << lane) - 1ull));
-        st.g2.w = __uint_as_float(b0 - start + uint32_t(lane) + 1u);
-        s0[at] = st.g0;
-        s1[at] = st.g1;
-        s2[at] = st.g2;
-      }
-      nb = __popcll(kept);
+      nb = n_kept;
     }
     __syncthreads();
     const uint32_t pos1 = __builtin_amdgcn_readfirstlane(b0 - start + 1u);
@@ -196,20 +210,32 @@ __device__ __forceinline__ void raster_fwd_tile(
         const float sigma = eval_sigma(r, g1.z, g1.w, &l2);
         const float alpha = fminf(kAlphaMax, sigma);
         const float test = T[k] * (1.0f - alpha);
-        // (as lane masks: the update runs under the mask, without selects)
-        const uint64_t hit = __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin);
-        const uint64_t pass = __builtin_amdgcn_ballot_w64(test >= kTStop);
-        // a hit that fails the stop test stops the pixel (rare)
-        if ((hit & ~pass) != 0ull) {
-          if (__builtin_amdgcn_inverse_ballot_w64(hit & ~pass)) fy[k] = __builtin_nanf("");
-        }
-        if (__builtin_amdgcn_inverse_ballot_w64(hit & pass)) {
-          const float w = alpha * T[k];
+        if constexpr (NAN_ROWS) {
+          const uint64_t hit = __builtin_amdgcn_ballot_w64(alpha >= kAlphaMin);
+          const uint64_t pass = __builtin_amdgcn_ballot_w64(test >= kTStop);
+          // a hit that fails the stop test stops the pixel (rare)
+          if ((hit & ~pass) != 0ull) {
+            if (__builtin_amdgcn_inverse_ballot_w64(hit & ~pass)) fy[k] = __builtin_nanf("");
+          }
+          if (__builtin_amdgcn_inverse_ballot_w64(hit & pass)) {
+            const float w = alpha * T[k];
+            cr[k] += g2.x * w;
+            cg[k] += g2.y * w;
+            cb[k] += g2.z * w;
+            T[k] = test;
+            last[k] = SPLIT == 1 ? pos1 + uint32_t(j) : __float_as_uint(g2.w);
+          }
+        } else {
+          const bool hit = alpha >= kAlphaMin;
+          const bool pass = test >= kTStop;
+          const bool con = hit && pass;
+          const float w = con ? alpha * T[k] : 0.0f;
           cr[k] += g2.x * w;
           cg[k] += g2.y * w;
           cb[k] += g2.z * w;
-          T[k] = test;
-          last[k] = SPLIT == 1 ? pos1 + uint32_t(j) : __float_as_uint(g2.w);
+          const float tn = pass ? test : -fabsf(T[k]);
+          T[k] = hit ? tn : T[k];
+          last[k] = con ? pos1 + uint32_t(j) : last[k];
         }
       }
     }
@@ -223,8 +249,8 @@ __device__ __forceinline__ void raster_fwd_tile(
       image[3 * pix + 1] = cg[k];
       image[3 * pix + 2] = cb[k];
       // (the internal copy is negated for a pixel that stopped)
-      t_ws[pix] = fy[k] == fy[k] ? T[k] : -T[k];
-      if (t_user) t_user[pix] = T[k];
+      t_ws[pix] = !NAN_ROWS || fy[k] == fy[k] ? T[k] : -T[k];
+      if (t_user) t_user[pix] = fabsf(T[k]);
       ncontrib[pix] = last[k];
     }
   }
@@ -240,7 +266,7 @@ __device__ __forceinline__ uint32_t next_tile(uint32_t* work, bool first) {
   return uint32_t(__shfl(int(t), 0, 64));
 }
 
-template <int TW, int TH, int BATCH, int SPLIT>
+template <int TW, int TH, int BATCH, int SPLIT, bool NAN_ROWS>
 __global__ void __launch_bounds__(64) raster_fwd_kernel(
     const float* __restrict__ records, const uint32_t* __restrict__ values,
     const uint32_t* __restrict__ ranges, const DevView* __restrict__ views, int n_views,
@@ -249,9 +275,9 @@ __global__ void __launch_bounds__(64) raster_fwd_kernel(
     uint32_t* __restrict__ ncontrib) {
   __shared__ float4 s0[BATCH], s1[BATCH], s2[BATCH];
   for (uint32_t q = next_tile(work, true); q / SPLIT < n_tiles; q = next_tile(work, false))
-    raster_fwd_tile<TW, TH, BATCH, SPLIT>(order[q / SPLIT], int(q % SPLIT), s0, s1, s2, records,
-                                          values, ranges, views, n_views, image, t_ws, t_user,
-                                          ncontrib);
+    raster_fwd_tile<TW, TH, BATCH, SPLIT, NAN_ROWS>(order[q / SPLIT], int(q % SPLIT), s0, s1, s2,
+                                                    records, values, ranges, views, n_views, image,
+                                                    t_ws, t_user, ncontrib);
 }
 
 // Sums over each 16-lane row by DPP row rotations (by 1, 2, 4, 8), of N
@@ -397,21 +423,27 @@ __device__ __forceinline__ void raster_bwd_tile(
       }
     } else {
       // only the records that may reach the band
-      bool keep = uint32_t(lane) < cnt;
-      Staged st;
-      if (keep) {
-        st = stage_record(records, values[start + lo + uint32_t(lane)]);
-        keep = may_reach_rows(st, band_y0, band_y1);
+      uint32_t n_kept = 0;
+#pragma unroll
+      for (int m = 0; m < PER_LANE; ++m) {
+        const uint32_t q = uint32_t(m * 64 + lane);
+        bool keep = q < cnt;
+        Staged st;
+        if (keep) {
+          st = stage_record(records, values[start + lo + q]);
+          keep = may_reach_rows(st, band_y0, band_y1);
+        }
+        const uint64_t kept = __ballot(keep);
+        if (keep) {
+          const uint32_t at = n_kept + uint32_t(__popcll(kept & ((1ull << lane) - 1ull)));
+          s0[at] = st.g0;
+          s1[at] = st.g1;
+          s2[at] = st.g2;
+          s_pos[at] = lo + q;
+        }
+        n_kept += uint32_t(__popcll(kept));
       }
-      const uint64_t kept = __ballot(keep);
-      if (keep) {
-        const int at = __popcll(kept & ((1ull << lane) - 1ull));
-        s0[at] = st.g0;
-        s1[at] = st.g1;
-        s2[at] = st.g2;
-        s_pos[at] = lo + uint32_t(lane);
-      }
-      cnt = uint32_t(__popcll(kept));
+      cnt = n_kept;
     }
     __syncthreads();
     // one record: the lane's pixel sums, folded (CHECK: test each pixel's last
@@ -602,14 +634,24 @@ struct RasterLaunch {
 //   backward  64 tiles 87 / 49 / 32, 1200 29 / 19 / 16, 1900 71 / 44 / 45 and
 //             111 / 67 / 47, 3072 61 / 45 / 53, 4108 99 / 97 / 129 and
 //             33 / 31 / 34, 8160 121 / 143 / 211
-// (the default tile shape and batch depth only: the others are the
-// autotuner's alternatives).
-constexpr uint32_t kFwdBands4 = 3072, kFwdBands2 = 8192;
+// A 32x16 tile takes two wavefronts in frames of any size, a lane then has four
+// pixels as in a 16x16 tile: forward 1800 tiles 75 / 50, 4080 102 / 80, backward
+// with the adjoint 160 / 114 and 266 / 230 (with 256 records a batch, whose LDS
+// bounds the wavefronts, forward 75 / 51 and 106 / 109).  Other shapes and batch
+// depths take one.
+constexpr uint32_t kFwdBands4 = 3072, kFwdBands2 = 8192, kFwdWide256 = 3072;
 constexpr uint32_t kBwdBands4 = 2048, kBwdBands2 = 4352;
-constexpr bool can_split(int tw, int th, int batch) { return tw == 16 && th == 16 && batch <= 64; }
+struct BandLimits {
+  uint32_t four, two;   // tiles up to which a tile takes so many wavefronts
+};
+static BandLimits band_limits(bool fwd, int tw, int th, int batch) {
+  if (tw == 32) return BandLimits{0u, fwd && batch > 128 ? kFwdWide256 : 0xffffffffu};
+  if (tw != 16 || th != 16 || batch > 64) return BandLimits{0u, 0u};
+  return fwd ? BandLimits{kFwdBands4, kFwdBands2} : BandLimits{kBwdBands4, kBwdBands2};
+}
 
 static RasterLaunch raster_geometry(uint32_t n_tiles, uint32_t* work, uint32_t persistent_blocks,
-                                    const uint32_t* order, uint32_t bands4, uint32_t bands2,
+                                    const uint32_t* order, BandLimits bands,
                                     hipStream_t st) {
   RasterLaunch g{n_tiles, nullptr, n_tiles, order, 1};
   if (work && persistent_blocks > 0 && persistent_blocks < n_tiles) {
@@ -618,7 +660,7 @@ static RasterLaunch raster_geometry(uint32_t n_tiles, uint32_t* work, uint32_t p
     g.grid = persistent_blocks;
     return g;
   }
-  g.split = n_tiles <= bands4 ? 4 : (n_tiles <= bands2 ? 2 : 1);
+  g.split = n_tiles <= bands.four ? 4 : (n_tiles <= bands.two ? 2 : 1);
   g.grid = n_tiles * uint32_t(g.split);
   return g;
 }
@@ -628,9 +670,20 @@ static hipError_t raster_fwd_t(const RasterLaunch& g, const float* records, cons
                                const uint32_t* ranges, const DevView* views, int n_views,
                                float* image, float* t_ws, float* t_user, uint32_t* ncontrib,
                                hipStream_t st) {
-  hipLaunchKernelGGL((raster_fwd_kernel<TW, TH, BATCH, SPLIT>), dim3(g.grid), dim3(64), 0, st,
-                     records, values, ranges, views, n_views, g.n_tiles, g.order, g.work, image,
-                     t_ws, t_user, ncontrib);
+  auto launch = [&](auto nan_rows) {
+    hipLaunchKernelGGL((raster_fwd_kernel<TW, TH, BATCH, SPLIT, decltype(nan_rows)::value>),
+                       dim3(g.grid), dim3(64), 0, st, records, values, ranges, views, n_views,
+                       g.n_tiles, g.order, g.work, image, t_ws, t_user, ncontrib);
+  };
+  // (NaN rows where they are faster: see raster_fwd_tile)
+  if constexpr (SPLIT > 1) {
+    launch(std::true_type());
+  } else if constexpr (TW == 16 && TH == 16 && BATCH == 64) {
+    if (g.work) launch(std::false_type());
+    else launch(std::true_type());
+  } else {
+    launch(std::false_type());
+  }
   return hipGetLastError();
 }
 
@@ -670,6 +723,9 @@ static hipError_t raster_bwd_t(const RasterLaunch& g, uint32_t* grad_dirty, cons
       return FN<8, 8, 256>(__VA_ARGS__);                                               \
     }                                                                                  \
     if (tw == 32 && th == 16) {                                                        \
+      if (bd == 64 && g.split == 2) return FN<32, 16, 64, 2>(__VA_ARGS__);             \
+      if (bd == 128 && g.split == 2) return FN<32, 16, 128, 2>(__VA_ARGS__);           \
+      if (g.split == 2) return FN<32, 16, 256, 2>(__VA_ARGS__);                        \
       if (bd == 64) return FN<32, 16, 64>(__VA_ARGS__);                                \
       if (bd == 128) return FN<32, 16, 128>(__VA_ARGS__);                              \
       return FN<32, 16, 256>(__VA_ARGS__);                                             \
@@ -684,9 +740,9 @@ hipError_t launch_raster_fwd(int tw, int th, int batch, uint32_t persistent_bloc
                              uint32_t n_tiles, float* image, float* t_ws, float* t_user,
                              uint32_t* ncontrib, hipStream_t st) {
   if (n_tiles == 0) return hipSuccess;
-  const bool split = can_split(tw, th, batch);
-  const RasterLaunch g = raster_geometry(n_tiles, work, persistent_blocks, order,
-                                         split ? kFwdBands4 : 0u, split ? kFwdBands2 : 0u, st);
+  const RasterLaunch g =
+      raster_geometry(n_tiles, work, persistent_blocks, order,
+                      band_limits(true, tw, th, batch), st);
   UBS_TILE_DISPATCH(raster_fwd_t, g, records, values, ranges, views, n_views, image, t_ws, t_user,
                     ncontrib, st);
 }
@@ -701,9 +757,9 @@ hipError_t launch_raster_bwd(int tw, int th, int batch, uint32_t persistent_bloc
                              const float* l1_target, float l1_scale, float* grad2d,
                              hipStream_t st) {
   if (n_tiles == 0) return hipSuccess;
-  const bool split = can_split(tw, th, batch);
-  const RasterLaunch g = raster_geometry(n_tiles, work, persistent_blocks, order,
-                                         split ? kBwdBands4 : 0u, split ? kBwdBands2 : 0u, st);
+  const RasterLaunch g =
+      raster_geometry(n_tiles, work, persistent_blocks, order,
+                      band_limits(false, tw, th, batch), st);
   UBS_TILE_DISPATCH(raster_bwd_t, g, grad_dirty, records, values, ranges, views, n_views, t_ws,
                     ncontrib, d_image, d_tfinal, l1_image, l1_target, l1_scale, grad2d, st);
 }
