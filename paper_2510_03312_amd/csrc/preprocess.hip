@@ -105,7 +105,8 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S,
   // atomic per workgroup reserves their run (ascending inside it), and each
   // wavefront then lists its own kept primitives and copies their parameter
   // rows (from LDS) to their columns of the compacted copy.
-  __shared__ uint32_t s_cnt[2], s_run;
+  __shared__ uint32_t s_cnt[2], s_run, s_total;
+  __shared__ uint8_t s_src[256];
   __shared__ unsigned long long s_keep[4];
   __shared__ uint32_t s_bin[kCountBins];
   if (threadIdx.x == 0) { s_cnt[0] = 0; s_cnt[1] = 0; }
@@ -130,6 +131,7 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S,
     partial[blockIdx.x] = s_cnt[1];
     partial[partial_stride + blockIdx.x] = s_cnt[0];
     s_run = n_keep ? atomicAdd(&kept.count[which], n_keep) : 0u;
+    s_total = n_keep;
   }
   __syncthreads();
   // entry q of the run: the kept primitives in thread order, or, where several
@@ -159,14 +161,29 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S,
     __syncthreads();
     q = s_bin[bin] + rank;
   }
-  if (!keep) return;
+  uint32_t src = threadIdx.x;   // the thread whose primitive this one lists
+  if (S.n_views > 1) {
+    // entries are listed by the threads in their order, so that the copies'
+    // stores stay dense (each thread listing its own primitive, sorted: 4
+    // scenes in 32 views 1000 us, this way 925; unsorted 915)
+    if (keep) {
+      kept.pos[i] = s_run + q;
+      s_src[q] = uint8_t(threadIdx.x);
+    }
+    __syncthreads();
+    if (threadIdx.x >= s_total) return;
+    src = s_src[threadIdx.x];
+    q = threadIdx.x;
+  } else {
+    if (!keep) return;
+    kept.pos[i] = s_run + q;
+  }
   const uint32_t p = s_run + q;
-  kept.list[size_t(which) * kept.cap + p] = uint32_t(i);
-  kept.pos[i] = p;
+  kept.list[size_t(which) * kept.cap + p] = blockIdx.x * 256u + src;
   float* par = kept.par + size_t(which) * kept.cap + p;
   const int64_t par_stride = int64_t(kKeptLists) * kept.cap;
 #pragma unroll
-  for (int k = 0; k < F; ++k) par[k * par_stride] = s_par[k][threadIdx.x];
+  for (int k = 0; k < F; ++k) par[k * par_stride] = s_par[k][src];
 }
 
 // The backward raster leaves per record the pixel sums of
@@ -328,7 +345,7 @@ __global__ void __launch_bounds__(64, AGAIN && C <= 4 ? 2 : 1) preprocess_bwd_ke
 // parameters from all over the group: 640 us where this takes 390.)  2M 7-D in
 // 8 views 726 -> 385 us, 4 scenes in 32 views 2.05 -> 1.07 ms, the forms of
 // prim_math.hpp included (580 us and 1.45 ms with all lanes in step over the
-// scene's views); the preprocess pays 15 us for the sorting of the 8 views.
+// scene's views); the preprocess pays 5 us for the sorting of the 8 views.
 constexpr int kManyViews = 32;   // views of a live mask
 constexpr int kViewWords = int(sizeof(DevView) / 4);
 
