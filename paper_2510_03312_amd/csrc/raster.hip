@@ -235,7 +235,7 @@ __device__ __forceinline__ void raster_fwd_tile(
           cb[k] += g2.z * w;
           const float tn = pass ? test : -fabsf(T[k]);
           T[k] = hit ? tn : T[k];
-          last[k] = con ? pos1 + uint32_t(j) : last[k];
+          last[k] = con ? b0 - start + uint32_t(j) + 1u : last[k];
         }
       }
     }
