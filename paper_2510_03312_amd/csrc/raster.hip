@@ -365,7 +365,10 @@ __device__ __forceinline__ void raster_bwd_tile(
 #pragma unroll
   for (int k = 0; k < PPL; ++k) {
     const int py = py0 + k * RSTEP;
-    float Tf = 1.0f;
+    // (a pixel outside the image keeps T = 0: the walk takes it along where no
+    // position is tested, and with T = 0 its every term is 0, where T = 1 would
+    // grow by 1 / (1 - alpha) a record to infinity and leave a NaN in the sums)
+    float Tf = 0.0f;
     gR[k] = gG[k] = gB[k] = gTf[k] = 0.0f; last[k] = 0;
     if (px < V.W && py < V.H) {
       const size_t pix = size_t(V.pix_base) + size_t(py) * V.W + px;
