@@ -10,14 +10,14 @@
 namespace ubs {
 
 hipError_t launch_preprocess_fwd(bool fp64, const DevScene& S, const DevView* views,
-                                 const int32_t* view_order, float* records, LiveOut live, uint32_t* partial,
-                                 uint32_t stride, hipStream_t st);
+                                 float* records, LiveOut live, uint32_t* partial, uint32_t stride,
+                                 hipStream_t st);
 hipError_t launch_bin_prepare(uint32_t* words, size_t n_words, const uint32_t* partial,
                               uint32_t n_partials, uint32_t stride, DevStatus* status,
                               hipStream_t st);
 hipError_t launch_preprocess_bwd(bool fp64, const DevScene& S, const DevView* views,
-                                 const int32_t* view_order, const float* records, float* grad2d,
-                                 LiveIn kept, float* compact, hipStream_t st);
+                                 const float* records, float* grad2d, LiveIn kept, float* compact,
+                                 hipStream_t st);
 hipError_t launch_bin_count(const float* records, const uint8_t* live, const DevView* views,
                             int n_views,
                             uint32_t n_records, uint32_t* tile_counts, uint32_t* hit_mask,
@@ -63,16 +63,13 @@ struct ViewChunk {
   int32_t first, count;
 };
 
-// Writes a chunk of view descriptors and their entries of the list of views
-// by scene; the first chunk's launch also clears the status block (s != nullptr) and the n_scenes kept-primitive counters.
+// Writes a chunk of view descriptors; the first chunk's launch also clears
+// the status block (s != nullptr) and the n_scenes kept-primitive counters.
 __global__ void upload_views_kernel(ViewChunk c, DevView* __restrict__ dst,
-                                    int32_t* __restrict__ order, DevStatus* __restrict__ s,
-                                    uint32_t* __restrict__ n_kept, int n_counters) {
+                                    DevStatus* __restrict__ s, uint32_t* __restrict__ n_kept,
+                                    int n_counters) {
   const int k = threadIdx.x;
-  if (k < c.count) {
-    dst[c.first + k] = c.v[k];
-    order[c.v[k].order_slot] = c.first + k;
-  }
+  if (k < c.count) dst[c.first + k] = c.v[k];
   if (s)
     for (int j = k; j < n_counters; j += int(blockDim.x)) n_kept[j] = 0u;
   if (s && k == 0) {
@@ -241,16 +238,17 @@ static ubs_status plan(const ubs_frame* f, Layout* L, std::vector<DevView>* dv,
     (*ds)[size_t(V.scene)].n_views += 1;
     dv->push_back(d);
   }
-  // the list of views by scene, ascending within a scene
+  // the list of views by scene, ascending within a scene: entry q of scene sc
+  // in descriptor view0 + q
   int32_t slot = 0;
   for (DevScene& d : *ds) {
     d.view0 = slot;
     slot += d.n_views;
     d.n_views = 0;
   }
-  for (DevView& d : *dv) {
-    DevScene& sc = (*ds)[size_t(d.scene)];
-    d.order_slot = uint32_t(sc.view0 + sc.n_views++);
+  for (int v = 0; v < f->n_views; ++v) {
+    DevScene& sc = (*ds)[size_t((*dv)[size_t(v)].scene)];
+    (*dv)[size_t(sc.view0 + sc.n_views++)].by_scene = v;
   }
   Layout& l = *L;
   memset(&l, 0, sizeof(l));
@@ -273,8 +271,8 @@ static ubs_status plan(const ubs_frame* f, Layout* L, std::vector<DevView>* dv,
   auto take = [&](uint64_t bytes) { const uint64_t o = off; off = align256(off + bytes); return o; };
   l.pub.off_status = take(sizeof(DevStatus));
   l.off_views = take(sizeof(DevView) * uint64_t(f->n_views > 0 ? f->n_views : 1));
-  l.off_view_order = take(4 * uint64_t(f->n_views > 0 ? f->n_views : 1));
-  l.off_scenes = take(sizeof(DevScene) * uint64_t(f->n_scenes > 0 ? f->n_scenes : 1));
+  // (64 bytes a scene that nothing reads: the size that ws_bytes has always had to be)
+  l.off_scenes = take(64 * uint64_t(f->n_scenes > 0 ? f->n_scenes : 1));
   l.pub.off_records = take(uint64_t(kRecFloats) * 4 * n_rec);
   l.off_tile_counts = take(4 * (n_tiles + 2));
   l.off_big_tiles = take(4 * n_tiles);
@@ -385,7 +383,7 @@ ubs_status ubs_preprocess(const ubs_frame* frame, void* ws, uint64_t ws_bytes, u
     c.count = frame->n_views - first < kViewChunk ? frame->n_views - first : kViewChunk;
     for (int k = 0; k < c.count; ++k) c.v[k] = p.dv[first + k];
     hipLaunchKernelGGL(upload_views_kernel, dim3(1), dim3(64), 0, s, c, views,
-                       at<int32_t>(ws, L.off_view_order), first == 0 ? status : nullptr,
+                       first == 0 ? status : nullptr,
                        at<uint32_t>(ws, L.off_live_count), frame->n_scenes * int(kKeptLists));
   }
   UBS_HIP(hipGetLastError());
@@ -404,9 +402,8 @@ ubs_status ubs_preprocess(const ubs_frame* frame, void* ws, uint64_t ws_bytes, u
                        at<uint32_t>(ws, L.off_live_count) + size_t(sc) * kKeptLists,
                        kept_list_cap(p.ds[sc].n),
                        at<float>(ws, L.off_par_compact) + p.ds[sc].par_base};
-    UBS_HIP(launch_preprocess_fwd(fp64, p.ds[sc], views, at<int32_t>(ws, L.off_view_order),
-                                  records, kept,
-                                  partial + block_base, stride, s));
+    UBS_HIP(launch_preprocess_fwd(fp64, p.ds[sc], views, records, kept, partial + block_base,
+                                  stride, s));
     block_base += uint32_t((p.ds[sc].n + 255) / 256);
   }
   stage_mark(frame, UBS_STAGE_PREPROCESS, 1, s);
@@ -535,9 +532,8 @@ ubs_status ubs_render_bwd(const ubs_frame* frame, void* ws, uint64_t ws_bytes,
                       at<uint32_t>(ws, L.off_live_count) + size_t(sc) * kKeptLists,
                       kept_list_cap(p.ds[sc].n),
                       at<float>(ws, L.off_par_compact) + p.ds[sc].par_base};
-    UBS_HIP(launch_preprocess_bwd(fp64, p.ds[sc], views, at<int32_t>(ws, L.off_view_order),
-                                  at<float>(ws, L.pub.off_records), grad2d, kept,
-                                  at<float>(ws, L.off_grad_compact), s));
+    UBS_HIP(launch_preprocess_bwd(fp64, p.ds[sc], views, at<float>(ws, L.pub.off_records), grad2d,
+                                  kept, at<float>(ws, L.off_grad_compact), s));
   }
   stage_mark(frame, UBS_STAGE_PRE_BWD, 1, s);
   UBS_HIP(hipGetLastError());

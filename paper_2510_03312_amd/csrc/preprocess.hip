@@ -43,7 +43,6 @@ struct Forms<float, C, ROT> {
 template <typename T, int C, int ROT>
 __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S,
                                                              const DevView* __restrict__ views,
-                                                             const int32_t* __restrict__ view_order,
                                                              float* __restrict__ records,
                                                              LiveOut kept,
                                                              uint32_t* __restrict__ partial,
@@ -70,7 +69,7 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S,
   }
   uint32_t visible = 0;
   for (int q = 0; q < S.n_views; ++q) {
-    const DevView& V = views[view_order[S.view0 + q]];
+    const DevView& V = views[views[S.view0 + q].by_scene];
     if (!active) continue;
     typename Form::S s;
     Form::view(r, g, V, s);
@@ -300,7 +299,7 @@ constexpr int64_t kOneRound = 1 << 18;
 
 template <typename T, int C, int ROT, bool AGAIN>
 __global__ void __launch_bounds__(64, AGAIN && C <= 4 ? 2 : 1) preprocess_bwd_kernel(
-    DevScene S, const DevView* __restrict__ views, const int32_t* __restrict__ view_order,
+    DevScene S, const DevView* __restrict__ views,
     const float* __restrict__ records, float* __restrict__ grad2d, LiveIn kept,
     float* __restrict__ compact) {
   constexpr int ROWS = grad_rows(C).N;
@@ -322,7 +321,7 @@ __global__ void __launch_bounds__(64, AGAIN && C <= 4 ? 2 : 1) preprocess_bwd_ke
 #pragma unroll
   for (int k = 0; k < ROWS; ++k) s_grad[k][lane] = 0.0f;
   if (pos >= n_entries) return;
-  const DevView& V = views[view_order[S.view0]];
+  const DevView& V = views[views[S.view0].by_scene];
   const size_t rec = size_t(V.rec_base) + i;
   RecordIn x;
   // (registers allow the record's read ahead of the geometry here)
@@ -351,7 +350,7 @@ constexpr int kViewWords = int(sizeof(DevView) / 4);
 
 template <typename T, int C, int ROT>
 __global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel(
-    DevScene S, const DevView* __restrict__ views, const int32_t* __restrict__ view_order,
+    DevScene S, const DevView* __restrict__ views,
     const float* __restrict__ records, float* __restrict__ grad2d, LiveIn kept,
     float* __restrict__ compact) {
   constexpr int ROWS = grad_rows(C).N;
@@ -377,7 +376,7 @@ __global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel
     __syncthreads();
     for (int w = lane; w < nq * kViewWords; w += 64)
       s_views[w / kViewWords][w % kViewWords] =
-          reinterpret_cast<const uint32_t*>(views + view_order[S.view0 + q0 + w / kViewWords])[w % kViewWords];
+          reinterpret_cast<const uint32_t*>(views + views[S.view0 + q0 + w / kViewWords].by_scene)[w % kViewWords];
     __syncthreads();
     uint32_t live = 0u;
 #pragma unroll 8
@@ -421,7 +420,6 @@ __global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel
 template <int C, int ROT>
 __global__ void __launch_bounds__(256) preprocess_bwd_f32_kernel(DevScene S,
                                                              const DevView* __restrict__ views,
-                                                             const int32_t* __restrict__ view_order,
                                                              const float* __restrict__ records,
                                                              float* __restrict__ grad2d,
                                                              LiveIn kept,
@@ -444,7 +442,7 @@ __global__ void __launch_bounds__(256) preprocess_bwd_f32_kernel(DevScene S,
   f32::GeoGrad<C> G;
   f32::geograd_zero<C>(G);
   for (int q = 0; q < S.n_views; ++q) {
-    const DevView& V = views[view_order[S.view0 + q]];
+    const DevView& V = views[views[S.view0 + q].by_scene];
     const size_t rec = size_t(V.rec_base) + size_t(i);
     // the record's sums and fields are read together with its live flag
     // (every row lies inside the workspace; a culled record's are unused)
@@ -519,36 +517,36 @@ __global__ void __launch_bounds__(256) scatter_dparams_kernel(DevScene S, LiveIn
 }
 
 template <typename T, int C, int ROT>
-static hipError_t pre_fwd_t(const DevScene& S, const DevView* views, const int32_t* view_order,
+static hipError_t pre_fwd_t(const DevScene& S, const DevView* views,
                             float* records, LiveOut live, uint32_t* partial, uint32_t stride,
                             hipStream_t st) {
   const unsigned blocks = unsigned((S.n + 255) / 256);
   hipLaunchKernelGGL((preprocess_fwd_kernel<T, C, ROT>), dim3(blocks), dim3(256), 0, st, S,
-                     views, view_order, records, live, partial, stride);
+                     views, records, live, partial, stride);
   return hipGetLastError();
 }
 
 template <typename T, int C, int ROT>
-static hipError_t pre_bwd_t(const DevScene& S, const DevView* views, const int32_t* view_order,
+static hipError_t pre_bwd_t(const DevScene& S, const DevView* views,
                             const float* records, float* grad2d, LiveIn kept, float* compact,
                             hipStream_t st) {
   // one lane per entry of the kKeptLists lists of cap entries
   const uint64_t entries = uint64_t(kKeptLists) * kept.cap;
   if constexpr (std::is_same<T, float>::value) {
     hipLaunchKernelGGL((preprocess_bwd_f32_kernel<C, ROT>), dim3(unsigned(entries / 256)),
-                       dim3(256), 0, st, S, views, view_order, records, grad2d, kept, compact);
+                       dim3(256), 0, st, S, views, records, grad2d, kept, compact);
   } else if (S.n_views == 1) {
     constexpr bool kMayKeep = C <= 4;   // (beyond 7-D the state spills with the parameters in it)
     if (kMayKeep && S.n <= kOneRound)
       hipLaunchKernelGGL((preprocess_bwd_kernel<T, C, ROT, !kMayKeep>),
-                         dim3(unsigned(entries / 64)), dim3(64), 0, st, S, views, view_order,
+                         dim3(unsigned(entries / 64)), dim3(64), 0, st, S, views,
                          records, grad2d, kept, compact);
     else
       hipLaunchKernelGGL((preprocess_bwd_kernel<T, C, ROT, true>), dim3(unsigned(entries / 64)),
-                         dim3(64), 0, st, S, views, view_order, records, grad2d, kept, compact);
+                         dim3(64), 0, st, S, views, records, grad2d, kept, compact);
   } else {
     hipLaunchKernelGGL((preprocess_bwd_many_kernel<T, C, ROT>), dim3(unsigned(entries / 64)),
-                       dim3(64), 0, st, S, views, view_order, records, grad2d, kept, compact);
+                       dim3(64), 0, st, S, views, records, grad2d, kept, compact);
   }
   // 16-byte stores when every row of dparams starts 16-byte aligned
   if (S.n % 4 == 0 && reinterpret_cast<uintptr_t>(S.dparams) % 16 == 0)
@@ -562,47 +560,46 @@ static hipError_t pre_bwd_t(const DevScene& S, const DevView* views, const int32
 
 template <typename T>
 static hipError_t pre_fwd_dispatch(const DevScene& S, const DevView* views,
-                                   const int32_t* view_order,
                                    float* records, LiveOut live, uint32_t* partial,
                                    uint32_t stride, hipStream_t st) {
   const int C = S.dim - 3;
   if (S.rot == UBS_ROT_QUAT) {
-    if (C == 0) return pre_fwd_t<T, 0, 0>(S, views, view_order, records, live, partial, stride, st);
-    if (C == 3) return pre_fwd_t<T, 3, 0>(S, views, view_order, records, live, partial, stride, st);
-    if (C == 4) return pre_fwd_t<T, 4, 0>(S, views, view_order, records, live, partial, stride, st);
-    if (C == 5) return pre_fwd_t<T, 5, 0>(S, views, view_order, records, live, partial, stride, st);
-    if (C == 6) return pre_fwd_t<T, 6, 0>(S, views, view_order, records, live, partial, stride, st);
-    if (C == 7) return pre_fwd_t<T, 7, 0>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 0) return pre_fwd_t<T, 0, 0>(S, views, records, live, partial, stride, st);
+    if (C == 3) return pre_fwd_t<T, 3, 0>(S, views, records, live, partial, stride, st);
+    if (C == 4) return pre_fwd_t<T, 4, 0>(S, views, records, live, partial, stride, st);
+    if (C == 5) return pre_fwd_t<T, 5, 0>(S, views, records, live, partial, stride, st);
+    if (C == 6) return pre_fwd_t<T, 6, 0>(S, views, records, live, partial, stride, st);
+    if (C == 7) return pre_fwd_t<T, 7, 0>(S, views, records, live, partial, stride, st);
   } else {
-    if (C == 0) return pre_fwd_t<T, 0, 1>(S, views, view_order, records, live, partial, stride, st);
-    if (C == 3) return pre_fwd_t<T, 3, 1>(S, views, view_order, records, live, partial, stride, st);
-    if (C == 4) return pre_fwd_t<T, 4, 1>(S, views, view_order, records, live, partial, stride, st);
-    if (C == 5) return pre_fwd_t<T, 5, 1>(S, views, view_order, records, live, partial, stride, st);
-    if (C == 6) return pre_fwd_t<T, 6, 1>(S, views, view_order, records, live, partial, stride, st);
-    if (C == 7) return pre_fwd_t<T, 7, 1>(S, views, view_order, records, live, partial, stride, st);
+    if (C == 0) return pre_fwd_t<T, 0, 1>(S, views, records, live, partial, stride, st);
+    if (C == 3) return pre_fwd_t<T, 3, 1>(S, views, records, live, partial, stride, st);
+    if (C == 4) return pre_fwd_t<T, 4, 1>(S, views, records, live, partial, stride, st);
+    if (C == 5) return pre_fwd_t<T, 5, 1>(S, views, records, live, partial, stride, st);
+    if (C == 6) return pre_fwd_t<T, 6, 1>(S, views, records, live, partial, stride, st);
+    if (C == 7) return pre_fwd_t<T, 7, 1>(S, views, records, live, partial, stride, st);
   }
   return hipErrorInvalidValue;
 }
 
 template <typename T>
-static hipError_t pre_bwd_dispatch(const DevScene& S, const DevView* views, const int32_t* view_order,
+static hipError_t pre_bwd_dispatch(const DevScene& S, const DevView* views,
                                    const float* records, float* grad2d, LiveIn kept,
                                    float* compact, hipStream_t st) {
   const int C = S.dim - 3;
   if (S.rot == UBS_ROT_QUAT) {
-    if (C == 0) return pre_bwd_t<T, 0, 0>(S, views, view_order, records, grad2d, kept, compact, st);
-    if (C == 3) return pre_bwd_t<T, 3, 0>(S, views, view_order, records, grad2d, kept, compact, st);
-    if (C == 4) return pre_bwd_t<T, 4, 0>(S, views, view_order, records, grad2d, kept, compact, st);
-    if (C == 5) return pre_bwd_t<T, 5, 0>(S, views, view_order, records, grad2d, kept, compact, st);
-    if (C == 6) return pre_bwd_t<T, 6, 0>(S, views, view_order, records, grad2d, kept, compact, st);
-    if (C == 7) return pre_bwd_t<T, 7, 0>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 0) return pre_bwd_t<T, 0, 0>(S, views, records, grad2d, kept, compact, st);
+    if (C == 3) return pre_bwd_t<T, 3, 0>(S, views, records, grad2d, kept, compact, st);
+    if (C == 4) return pre_bwd_t<T, 4, 0>(S, views, records, grad2d, kept, compact, st);
+    if (C == 5) return pre_bwd_t<T, 5, 0>(S, views, records, grad2d, kept, compact, st);
+    if (C == 6) return pre_bwd_t<T, 6, 0>(S, views, records, grad2d, kept, compact, st);
+    if (C == 7) return pre_bwd_t<T, 7, 0>(S, views, records, grad2d, kept, compact, st);
   } else {
-    if (C == 0) return pre_bwd_t<T, 0, 1>(S, views, view_order, records, grad2d, kept, compact, st);
-    if (C == 3) return pre_bwd_t<T, 3, 1>(S, views, view_order, records, grad2d, kept, compact, st);
-    if (C == 4) return pre_bwd_t<T, 4, 1>(S, views, view_order, records, grad2d, kept, compact, st);
-    if (C == 5) return pre_bwd_t<T, 5, 1>(S, views, view_order, records, grad2d, kept, compact, st);
-    if (C == 6) return pre_bwd_t<T, 6, 1>(S, views, view_order, records, grad2d, kept, compact, st);
-    if (C == 7) return pre_bwd_t<T, 7, 1>(S, views, view_order, records, grad2d, kept, compact, st);
+    if (C == 0) return pre_bwd_t<T, 0, 1>(S, views, records, grad2d, kept, compact, st);
+    if (C == 3) return pre_bwd_t<T, 3, 1>(S, views, records, grad2d, kept, compact, st);
+    if (C == 4) return pre_bwd_t<T, 4, 1>(S, views, records, grad2d, kept, compact, st);
+    if (C == 5) return pre_bwd_t<T, 5, 1>(S, views, records, grad2d, kept, compact, st);
+    if (C == 6) return pre_bwd_t<T, 6, 1>(S, views, records, grad2d, kept, compact, st);
+    if (C == 7) return pre_bwd_t<T, 7, 1>(S, views, records, grad2d, kept, compact, st);
   }
   return hipErrorInvalidValue;
 }
@@ -610,19 +607,19 @@ static hipError_t pre_bwd_dispatch(const DevScene& S, const DevView* views, cons
 // partial: this launch's slice of the per-workgroup counts (visible records
 // at partial[b], non-finite primitives at partial[stride + b]).
 hipError_t launch_preprocess_fwd(bool fp64, const DevScene& S, const DevView* views,
-                                 const int32_t* view_order, float* records, LiveOut live, uint32_t* partial,
+                                 float* records, LiveOut live, uint32_t* partial,
                                  uint32_t stride, hipStream_t st) {
   if (S.n == 0) return hipSuccess;
-  return fp64 ? pre_fwd_dispatch<double>(S, views, view_order, records, live, partial, stride, st)
-              : pre_fwd_dispatch<float>(S, views, view_order, records, live, partial, stride, st);
+  return fp64 ? pre_fwd_dispatch<double>(S, views, records, live, partial, stride, st)
+              : pre_fwd_dispatch<float>(S, views, records, live, partial, stride, st);
 }
 
 hipError_t launch_preprocess_bwd(bool fp64, const DevScene& S, const DevView* views,
-                                 const int32_t* view_order, const float* records, float* grad2d, LiveIn kept,
+                                 const float* records, float* grad2d, LiveIn kept,
                                  float* compact, hipStream_t st) {
   if (S.n == 0) return hipSuccess;
-  return fp64 ? pre_bwd_dispatch<double>(S, views, view_order, records, grad2d, kept, compact, st)
-              : pre_bwd_dispatch<float>(S, views, view_order, records, grad2d, kept, compact, st);
+  return fp64 ? pre_bwd_dispatch<double>(S, views, records, grad2d, kept, compact, st)
+              : pre_bwd_dispatch<float>(S, views, records, grad2d, kept, compact, st);
 }
 
 }  // namespace ubs

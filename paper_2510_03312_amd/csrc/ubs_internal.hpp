@@ -33,7 +33,9 @@ struct DevView {
   uint32_t tile_base;    // first global tile of the view
   uint32_t rec_base;     // first record of the view
   uint32_t pix_base;     // first pixel of the view
-  uint32_t order_slot;   // the view's place in the list of views by scene
+  // entry of the list of views by scene whose place is this descriptor's
+  // index: the list travels in the descriptors' spare words
+  int32_t by_scene;
   uint32_t _pad[2];
 };
 static_assert(sizeof(DevView) % 16 == 0, "DevView alignment");
@@ -158,7 +160,7 @@ static_assert(sizeof(DevStatus) == sizeof(ubs_status_block), "status block size"
 // Full private layout of the workspace (superset of ubs_layout).
 struct Layout {
   ubs_layout pub;
-  uint64_t off_views, off_view_order, off_scenes, off_offsets, off_blocksums;
+  uint64_t off_views, off_scenes, off_offsets, off_blocksums;
   uint64_t off_tile_counts, off_tile_cursor;  // pairs per tile (+2 counters); segment cursors
   uint64_t off_big_tiles;            // tiles sorted by a workgroup (more than 256 pairs)
   uint64_t off_hit_mask;             // per record: hits among its candidate tiles
