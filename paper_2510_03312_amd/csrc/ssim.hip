@@ -50,10 +50,20 @@ constexpr int kSsimThreads = 192;                // one wavefront per channel
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 constexpr int kSsimViewChunk = 64;
-// Frames of up to this many tiles take the kernels for few tiles: loss and
-// gradient of 960x540 (272 tiles) 80 us against 86, of 1280x720 (450) 110
-// against 89, of 320x180 34 against 70.
-constexpr uint64_t kFewTiles = 300;
+// Which frames take the kernels for few tiles, of 16 x 16 pixels: those of up to
+// kFewTiles such tiles (loss and gradient in us, these / the walk: 2040 tiles
+// 59 / 67, 2268 64 / 68, 2400 67 / 68, 2772 69 / 69, 3600 80 / 70), and those of
+// narrow views, whose 128 x 16 tiles are so empty that they hold at most
+// kFewPerWalk tiles of 16 x 16 each (1024 views of 32x32, two each, 105 / 196;
+// 33x16384, three, 70 / 89; 1000 views of 48x48, three, 201 / 255; 64x16384,
+// four, 103 / 89; 1024 views of 64x64, four, 370 / 333).
+constexpr uint64_t kFewTiles = 2304, kFewPerWalk = 3;
+// Of those, frames of up to this many tiles take a workgroup's three channels
+// side by side (64x48 15.1 us, one after the other 19.7; 320x180 18 / 22;
+// 480x270, 510 tiles, 25.0 / 26.7): two such workgroups fit a CU.  More tiles
+// take workgroups of one channel at a time, of which eight fit (500x290, 608
+// tiles, 32.3 / 29.0; 640x480 42.5 / 35.9).
+constexpr uint64_t kFewOneRound = 512;
 
 struct SsimView {
   int32_t W, H, tiles_x;
@@ -87,11 +97,17 @@ struct SsimTaps {
 };
 
 __device__ __forceinline__ SsimView ssim_view_of_tile(const SsimViews& vs, uint32_t tile) {
-  int lo = 0, hi = vs.n - 1;
   if (vs.many) {
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (vs.many[mid].tile_base <= tile) lo = mid; else hi = mid - 1;
+    // the last view whose first tile is at or before this one, a wavefront's 64
+    // probes at a time (two rounds of loads for 1024 views, where a binary
+    // search waits for ten, one after the other: 1024 views of 32x32 137 -> 130 us)
+    int lo = 0, n = vs.n;
+    while (n > 1) {
+      const int step = (n + 63) / 64, at = int(threadIdx.x & 63) * step;
+      const bool past = at < n && vs.many[lo + at].tile_base <= tile;
+      const int k = __builtin_amdgcn_readfirstlane(63 - __clzll(__ballot(past))) * step;
+      lo += k;
+      n = min(step, n - k);
     }
     return vs.many[lo];
   }
@@ -397,8 +413,8 @@ __global__ void __launch_bounds__(kSsimThreads) ssim_bwd_kernel(
 // Frames of few tiles: a wavefront that walks 26 rows is then all that a SIMD
 // has, and takes a microsecond a row.  These kernels take a tile of 16 x 16 by
 // kFewThreads threads per channel, all of a patch at once, passes separated by
-// barriers; the chip's idle SIMDs pay for the halo (320x180 42 -> 34 us, with
-// the channels one after the other before).
+// barriers; the chip's idle SIMDs pay for the halo.  NCH channels side by side,
+// the others one after the other.
 // ---------------------------------------------------------------------------
 constexpr int kSsimTile = 16;
 constexpr int kSsimP = kSsimTile + 2 * kSsimR;   // 26
@@ -468,48 +484,53 @@ __device__ __forceinline__ FewTileAt few_tile_at(const SsimViews& views, uint32_
   return FewTileAt{V.W, V.H, lt - ty * V.tiles_x, ty, size_t(V.pix_base)};
 }
 
-__global__ void __launch_bounds__(3 * kFewThreads) ssim_fwd_few_kernel(
+template <int NCH>
+__global__ void __launch_bounds__(NCH * kFewThreads) ssim_fwd_few_kernel(
     SsimViews views, const float* __restrict__ image, const float* __restrict__ target,
     SsimTaps taps, float scale, float* __restrict__ dstat, uint32_t n_pixels,
     double* __restrict__ tile_sums) {
-  __shared__ float s_all[3][4][kSsimP][kSsimP];   // x, y, x^2 + y^2, x y
-  __shared__ float s_tmp[3][4][kSsimP][kSsimTmpW];
-  __shared__ double s_red[2][12];
+  __shared__ float s_all[NCH][4][kSsimP][kSsimP];   // x, y, x^2 + y^2, x y
+  __shared__ float s_tmp[NCH][4][kSsimP][kSsimTmpW];
+  __shared__ double s_red[2][4 * NCH];
   const uint32_t tile = blockIdx.x;
   const FewTileAt at = few_tile_at(views, tile);
-  const int ch = __builtin_amdgcn_readfirstlane(threadIdx.x / kFewThreads);
+  const int wg_ch = __builtin_amdgcn_readfirstlane(threadIdx.x / kFewThreads);
   const int tid = threadIdx.x % kFewThreads;
   const int x0 = at.tx * kSsimTile - kSsimR, y0 = at.ty * kSsimTile - kSsimR;
-  float(*s_in)[kSsimP][kSsimP] = s_all[ch];
-  for (int e = tid; e < kSsimP * kSsimP; e += kFewThreads) {
-    const int r = e / kSsimP, c = e % kSsimP;
-    const int gx = x0 + c, gy = y0 + r;
-    float a = 0.0f, b = 0.0f;
-    if (gx >= 0 && gx < at.W && gy >= 0 && gy < at.H) {
-      const size_t q = 3 * (at.pix + size_t(gy) * at.W + gx) + ch;
-      a = image[q];
-      b = target[q];
-    }
-    s_in[0][r][c] = a;
-    s_in[1][r][c] = b;
-    s_in[2][r][c] = a * a + b * b;
-    s_in[3][r][c] = a * b;
-  }
-  __syncthreads();
   const int r = tid / kSsimTile, c = tid % kSsimTile;
-  const float l1 = fabsf(s_in[0][r + kSsimR][c + kSsimR] - s_in[1][r + kSsimR][c + kSsimR]);
-  __syncthreads();
-  float st[4];
-  window_16x16<4>(s_in, s_tmp[ch], taps, st);
-  double s_sum = 0.0, l1_sum = 0.0;
   const int px = at.tx * kSsimTile + c, py = at.ty * kSsimTile + r;
-  if (px < at.W && py < at.H) {
-    float d[3];
-    s_sum = double(ssim_point(st, scale, d));
-    l1_sum = double(l1);
-    float* out = dstat + size_t(3 * ch) * n_pixels + at.pix + size_t(py) * at.W + px;
+  float(*s_in)[kSsimP][kSsimP] = s_all[wg_ch];
+  double s_sum = 0.0, l1_sum = 0.0;
+#pragma unroll 1
+  for (int ch = wg_ch; ch < 3; ch += NCH) {
+    for (int e = tid; e < kSsimP * kSsimP; e += kFewThreads) {
+      const int pr = e / kSsimP, pc = e % kSsimP;
+      const int gx = x0 + pc, gy = y0 + pr;
+      float a = 0.0f, b = 0.0f;
+      if (gx >= 0 && gx < at.W && gy >= 0 && gy < at.H) {
+        const size_t q = 3 * (at.pix + size_t(gy) * at.W + gx) + ch;
+        a = image[q];
+        b = target[q];
+      }
+      s_in[0][pr][pc] = a;
+      s_in[1][pr][pc] = b;
+      s_in[2][pr][pc] = a * a + b * b;
+      s_in[3][pr][pc] = a * b;
+    }
+    __syncthreads();
+    const float l1 = fabsf(s_in[0][r + kSsimR][c + kSsimR] - s_in[1][r + kSsimR][c + kSsimR]);
+    __syncthreads();
+    float st[4];
+    window_16x16<4>(s_in, s_tmp[wg_ch], taps, st);
+    if (px < at.W && py < at.H) {
+      float d[3];
+      s_sum += double(ssim_point(st, scale, d));
+      l1_sum += double(l1);
+      float* out = dstat + size_t(3 * ch) * n_pixels + at.pix + size_t(py) * at.W + px;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) out[k * size_t(n_pixels)] = d[k];
+      for (int k = 0; k < 3; ++k) out[k * size_t(n_pixels)] = d[k];
+    }
+    if (NCH < 3) __syncthreads();
   }
   // tile sums of S and |x - y|
 #pragma unroll
@@ -525,45 +546,50 @@ __global__ void __launch_bounds__(3 * kFewThreads) ssim_fwd_few_kernel(
   if (threadIdx.x < 2) {
     double t = 0.0;
 #pragma unroll
-    for (int k = 0; k < 12; ++k) t += s_red[threadIdx.x][k];
+    for (int k = 0; k < 4 * NCH; ++k) t += s_red[threadIdx.x][k];
     tile_sums[2 * size_t(tile) + threadIdx.x] = t;
   }
 }
 
-__global__ void __launch_bounds__(3 * kFewThreads) ssim_bwd_few_kernel(
+template <int NCH>
+__global__ void __launch_bounds__(NCH * kFewThreads) ssim_bwd_few_kernel(
     SsimViews views, const float* __restrict__ image, const float* __restrict__ target,
     SsimTaps taps, float l1_weight, const float* __restrict__ dstat, uint32_t n_pixels,
     float* __restrict__ d_image) {
-  __shared__ float s_all[3][3][kSsimP][kSsimP];   // d/dm, d/dsxx, d/dsxy
-  __shared__ float s_tmp[3][3][kSsimP][kSsimTmpW];
+  __shared__ float s_all[NCH][3][kSsimP][kSsimP];   // d/dm, d/dsxx, d/dsxy
+  __shared__ float s_tmp[NCH][3][kSsimP][kSsimTmpW];
   const FewTileAt at = few_tile_at(views, blockIdx.x);
-  const int ch = __builtin_amdgcn_readfirstlane(threadIdx.x / kFewThreads);
+  const int wg_ch = __builtin_amdgcn_readfirstlane(threadIdx.x / kFewThreads);
   const int tid = threadIdx.x % kFewThreads;
   const int x0 = at.tx * kSsimTile - kSsimR, y0 = at.ty * kSsimTile - kSsimR;
   const int px = at.tx * kSsimTile + tid % kSsimTile, py = at.ty * kSsimTile + tid / kSsimTile;
   const bool inside = px < at.W && py < at.H;
-  const size_t own = 3 * (at.pix + (inside ? size_t(py) * at.W + px : 0)) + ch;
-  const float x = image[own], y = target[own];
-  float(*s_in)[kSsimP][kSsimP] = s_all[ch];
-  for (int e = tid; e < kSsimP * kSsimP; e += kFewThreads) {
-    const int r = e / kSsimP, c = e % kSsimP;
-    const int gx = x0 + c, gy = y0 + r;
-    float v[3] = {0.0f, 0.0f, 0.0f};
-    if (gx >= 0 && gx < at.W && gy >= 0 && gy < at.H) {
-      const float* q = dstat + size_t(3 * ch) * n_pixels + at.pix + size_t(gy) * at.W + gx;
+  float(*s_in)[kSsimP][kSsimP] = s_all[wg_ch];
+#pragma unroll 1
+  for (int ch = wg_ch; ch < 3; ch += NCH) {
+    const size_t own = 3 * (at.pix + (inside ? size_t(py) * at.W + px : 0)) + ch;
+    const float x = image[own], y = target[own];
+    for (int e = tid; e < kSsimP * kSsimP; e += kFewThreads) {
+      const int r = e / kSsimP, c = e % kSsimP;
+      const int gx = x0 + c, gy = y0 + r;
+      float v[3] = {0.0f, 0.0f, 0.0f};
+      if (gx >= 0 && gx < at.W && gy >= 0 && gy < at.H) {
+        const float* q = dstat + size_t(3 * ch) * n_pixels + at.pix + size_t(gy) * at.W + gx;
 #pragma unroll
-      for (int k = 0; k < 3; ++k) v[k] = q[k * size_t(n_pixels)];
+        for (int k = 0; k < 3; ++k) v[k] = q[k * size_t(n_pixels)];
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) s_in[k][r][c] = v[k];
     }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) s_in[k][r][c] = v[k];
-  }
-  __syncthreads();
-  float w[3];
-  window_16x16<3>(s_in, s_tmp[ch], taps, w);
-  if (inside) {
-    const float diff = x - y;
-    const float sgn = diff > 0.0f ? 1.0f : (diff < 0.0f ? -1.0f : 0.0f);
-    d_image[own] = w[0] + 2.0f * x * w[1] + y * w[2] + l1_weight * sgn;
+    __syncthreads();
+    float w[3];
+    window_16x16<3>(s_in, s_tmp[wg_ch], taps, w);
+    if (inside) {
+      const float diff = x - y;
+      const float sgn = diff > 0.0f ? 1.0f : (diff < 0.0f ? -1.0f : 0.0f);
+      d_image[own] = w[0] + 2.0f * x * w[1] + y * w[2] + l1_weight * sgn;
+    }
+    if (NCH < 3) __syncthreads();
   }
 }
 
@@ -607,45 +633,47 @@ extern "C" ubs_status ubs_ssim_loss(int32_t n_views, const int32_t* sizes, const
   if (n_views < 0 || n_views > UBS_MAX_VIEWS || (n_views > 0 && !sizes)) return UBS_ERR_ARG;
   if (!(lambda_ssim >= 0.0f && lambda_ssim <= 1.0f)) return UBS_ERR_ARG;
   std::vector<SsimView> vs(size_t(n_views > 0 ? n_views : 0));
-  uint64_t tiles = 0, pixels = 0;
+  uint64_t pixels = 0, n_walk = 0, n_few = 0;   // (tiles of 128 x 16 and of 16 x 16)
   for (int v = 0; v < n_views; ++v) {
     const int W = sizes[2 * v], H = sizes[2 * v + 1];
     if (W < 1 || H < 1 || W > 16384 || H > 16384) return UBS_ERR_ARG;
     SsimView s{};
     s.W = W;
     s.H = H;
-    s.tiles_x = (W + kTileW - 1) / kTileW;
     s.pix_base = uint32_t(pixels);
-    tiles += uint64_t(s.tiles_x) * uint64_t((H + kTileH - 1) / kTileH);
+    n_walk += uint64_t((W + kTileW - 1) / kTileW) * uint64_t((H + kTileH - 1) / kTileH);
+    n_few += uint64_t((W + kSsimTile - 1) / kSsimTile) * uint64_t((H + kSsimTile - 1) / kSsimTile);
     pixels += uint64_t(W) * uint64_t(H);
     if (pixels > 0x7fffffffull) return UBS_ERR_UNSUPPORTED;
     vs[size_t(v)] = s;
   }
-  const bool few = tiles <= kFewTiles;
-  if (few)
-    for (SsimView& s : vs) s.tiles_x = (s.W + kSsimTile - 1) / kSsimTile;
-  const int tile_h = few ? kSsimTile : kTileH;
-  tiles = 0;
-  for (SsimView& s : vs) {
-    s.tile_base = uint32_t(tiles);
-    tiles += uint64_t(s.tiles_x) * uint64_t((s.H + tile_h - 1) / tile_h);
-  }
   const uint64_t off_views = 0;
   const uint64_t off_sums = ssim_align(off_views + sizeof(SsimView) * uint64_t(n_views > 0 ? n_views : 1));
-  const uint64_t off_dstat = ssim_align(off_sums + 16 * (tiles > 0 ? tiles : 1));
-  const uint64_t need = ssim_align(off_dstat + 36 * pixels);
+  auto dstat_at = [&](uint64_t tiles) { return ssim_align(off_sums + 16 * (tiles > 0 ? tiles : 1)); };
+  auto bytes = [&](uint64_t tiles) { return ssim_align(dstat_at(tiles) + 36 * pixels); };
+  bool few = n_few <= kFewTiles || n_few <= kFewPerWalk * n_walk;
   if (!ws) {
     if (!ws_bytes_needed) return UBS_ERR_ARG;
-    *ws_bytes_needed = need;
+    *ws_bytes_needed = bytes(few ? n_few : n_walk);
     return UBS_OK;
   }
-  if (ws_bytes < need) return UBS_ERR_CAPACITY;
+  // (a workspace that holds no more than the walk's fewer sums takes the walk)
+  if (ws_bytes < bytes(n_few)) few = false;
+  const uint64_t tiles = few ? n_few : n_walk;
+  if (ws_bytes < bytes(tiles)) return UBS_ERR_CAPACITY;
+  const int tile_w = few ? kSsimTile : kTileW, tile_h = few ? kSsimTile : kTileH;
+  uint64_t first_tile = 0;
+  for (SsimView& s : vs) {
+    s.tiles_x = (s.W + tile_w - 1) / tile_w;
+    s.tile_base = uint32_t(first_tile);
+    first_tile += uint64_t(s.tiles_x) * uint64_t((s.H + tile_h - 1) / tile_h);
+  }
   if (pixels > 0 && (!image || !target || !d_image)) return UBS_ERR_ARG;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* base = static_cast<char*>(ws);
   SsimView* dviews = reinterpret_cast<SsimView*>(base + off_views);
   double* sums = reinterpret_cast<double*>(base + off_sums);
-  float* dstat = reinterpret_cast<float*>(base + off_dstat);
+  float* dstat = reinterpret_cast<float*>(base + dstat_at(tiles));
   SsimViews views{};
   views.n = n_views;
   for (int k = 0; k < n_views && k < kFewViews; ++k) views.few[k] = vs[size_t(k)];
@@ -671,11 +699,15 @@ extern "C" ubs_status ubs_ssim_loss(int32_t n_views, const int32_t* sizes, const
   if (tiles > 0) {
     const float scale = float(-double(lambda_ssim) / n_entries);
     const float l1_weight = float((1.0 - double(lambda_ssim)) / n_entries);
-    const dim3 grid{unsigned(tiles)}, block{unsigned(few ? 3 * kFewThreads : kSsimThreads)};
-    hipLaunchKernelGGL(few ? ssim_fwd_few_kernel : ssim_fwd_kernel, grid, block, 0, st, views, image,
-                       target, taps, scale, dstat, uint32_t(pixels), sums);
-    hipLaunchKernelGGL(few ? ssim_bwd_few_kernel : ssim_bwd_kernel, grid, block, 0, st, views, image,
-                       target, taps, l1_weight, dstat, uint32_t(pixels), d_image);
+    const dim3 grid{unsigned(tiles)}, block{unsigned(few ? (n_few <= kFewOneRound ? 3 : 1) * kFewThreads : kSsimThreads)};
+    const auto fwd = !few ? ssim_fwd_kernel
+                          : (n_few <= kFewOneRound ? ssim_fwd_few_kernel<3> : ssim_fwd_few_kernel<1>);
+    const auto bwd = !few ? ssim_bwd_kernel
+                          : (n_few <= kFewOneRound ? ssim_bwd_few_kernel<3> : ssim_bwd_few_kernel<1>);
+    hipLaunchKernelGGL(fwd, grid, block, 0, st, views, image, target, taps, scale, dstat,
+                       uint32_t(pixels), sums);
+    hipLaunchKernelGGL(bwd, grid, block, 0, st, views, image, target, taps, l1_weight, dstat,
+                       uint32_t(pixels), d_image);
   }
   if (loss && tiles > 0)
     hipLaunchKernelGGL(ssim_loss_kernel, dim3(1), dim3(256), 0, st, sums, uint32_t(tiles),
