@@ -237,14 +237,14 @@ __device__ __forceinline__ void load_record(const uint8_t* __restrict__ rec_live
   }
 }
 
-// The adjoint of one record: its share of the primitive's gradient rows is
-// added to the lane's column of s_grad.  (Plain adds: every column is one
-// lane's.  LDS float atomics took pre_bwd from 82 to 130 us.)
-template <typename T, int C, int ROT, int LANES>
+// The adjoint of one record: its share of the primitive's gradients is added to
+// the lane's column of the sums.  (Plain adds: every column is one lane's.  LDS
+// float atomics took pre_bwd from 82 to 130 us.)
+template <typename T, int C, int ROT, typename Sums>
 __device__ __forceinline__ void record_adjoint(const Raw<C, ROT>& r, const Geo<T, C, ROT>& g,
                                                const DevView& V, RecordIn& x,
                                                float* __restrict__ grad_row,
-                                               float (*s_grad)[LANES], int lane) {
+                                               Sums& sums, int lane) {
   record_gradient_from_sums(x.fields, x.sums);
   // (rows start 8-byte aligned)
   float2* gp = reinterpret_cast<float2*>(grad_row);
@@ -253,20 +253,20 @@ __device__ __forceinline__ void record_adjoint(const Raw<C, ROT>& r, const Geo<T
   grad_row[6] = x.sums[6];
   ViewState<T, C> s;
   view_forward<T, C, ROT, true>(r, g, V, s);
-  view_backward<T, C, ROT>(g, V, s, x.sums, [&](int k, T y) { s_grad[k][lane] += float(y); });
+  view_backward<T, C, ROT>(g, V, s, x.sums, [&](int k, T y) { sums.add(k, y, lane); });
 }
 
 // The last step: gradient rows to parameter rows, written to column t of the
 // compacted buffer.  AGAIN: the parameters are read once more, and what only
 // this step needs of them (s, M, Sigma_xq, H) is formed again; kept over the
 // views they would take the registers of the second wavefront per SIMD.
-template <typename T, int C, int ROT, int LANES, bool AGAIN>
+template <typename T, int C, int ROT, bool AGAIN, typename Sums>
 __device__ __forceinline__ void write_gradient(const Raw<C, ROT>& r, const float* __restrict__ par,
                                                int64_t stride, uint32_t t, Geo<T, C, ROT>& g,
-                                               float (*s_grad)[LANES], int lane,
+                                               const Sums& sums, int lane,
                                                float* __restrict__ compact) {
-  auto grad = [&](int k) { return s_grad[k][lane]; };
-  auto out = [&](int k, float x) { compact[int64_t(k) * stride + t] = x; };
+  auto grad = [&](int k) { return sums.get(k, lane); };
+  auto out = [&](int k, T x) { compact[int64_t(k) * stride + t] = float(x); };
   if constexpr (AGAIN) {
     uint32_t t2 = t;
     asm volatile("" : "+v"(t2));
@@ -302,8 +302,7 @@ __global__ void __launch_bounds__(64, AGAIN && C <= 4 ? 2 : 1) preprocess_bwd_ke
     DevScene S, const DevView* __restrict__ views,
     const float* __restrict__ records, float* __restrict__ grad2d, LiveIn kept,
     float* __restrict__ compact) {
-  constexpr int ROWS = grad_rows(C).N;
-  __shared__ float s_grad[ROWS][64];
+  __shared__ GradSums<C, 64, true> s_grad;
   // workgroup b takes entries 64 (b / kKeptLists) + [0, 64) of kept list
   // b mod kKeptLists (cap is a multiple of 64), so the workgroups holding
   // entries come first in the grid whatever the lists' counts
@@ -318,8 +317,7 @@ __global__ void __launch_bounds__(64, AGAIN && C <= 4 ? 2 : 1) preprocess_bwd_ke
   const int64_t stride = int64_t(kKeptLists) * kept.cap;
   Raw<C, ROT> r;
   load_raw<C, ROT>(kept.par, stride, t, r);
-#pragma unroll
-  for (int k = 0; k < ROWS; ++k) s_grad[k][lane] = 0.0f;
+  s_grad.clear(lane);
   if (pos >= n_entries) return;
   const DevView& V = views[views[S.view0].by_scene];
   const size_t rec = size_t(V.rec_base) + i;
@@ -330,8 +328,8 @@ __global__ void __launch_bounds__(64, AGAIN && C <= 4 ? 2 : 1) preprocess_bwd_ke
   geo_forward<T, C, ROT>(r, g, S.variant);
   if constexpr (AGAIN) load_record(kept.rec_live, records, grad2d, rec, x);
   if (x.live)
-    record_adjoint<T, C, ROT, 64>(r, g, V, x, grad2d + rec * kGradFloats, s_grad, lane);
-  write_gradient<T, C, ROT, 64, AGAIN>(r, kept.par, stride, t, g, s_grad, lane, compact);
+    record_adjoint<T, C, ROT>(r, g, V, x, grad2d + rec * kGradFloats, s_grad, lane);
+  write_gradient<T, C, ROT, AGAIN>(r, kept.par, stride, t, g, s_grad, lane, compact);
 }
 
 // Adjoint of a scene that several views see.  A primitive is live in some of
@@ -353,8 +351,7 @@ __global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel
     DevScene S, const DevView* __restrict__ views,
     const float* __restrict__ records, float* __restrict__ grad2d, LiveIn kept,
     float* __restrict__ compact) {
-  constexpr int ROWS = grad_rows(C).N;
-  __shared__ float s_grad[ROWS][64];
+  __shared__ GradSums<C, 64, false> s_grad;
   __shared__ uint32_t s_views[kManyViews][kViewWords];
   const int lane = threadIdx.x;
   const uint32_t lo = blockIdx.x % kKeptLists;
@@ -386,8 +383,7 @@ __global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel
   };
   int nq = min(kManyViews, S.n_views);
   uint32_t live = stage_views(0, nq);
-#pragma unroll
-  for (int k = 0; k < ROWS; ++k) s_grad[k][lane] = 0.0f;
+  s_grad.clear(lane);
   Geo<T, C, ROT> g;
   geo_forward<T, C, ROT>(r, g, S.variant);
   for (int q0 = 0;;) {
@@ -404,7 +400,7 @@ __global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel
 #pragma unroll
       for (int k = 0; k < C; ++k) asm volatile("" : "+v"(r.muq[k]));
       asm volatile("" : "+v"(r.o), "+v"(r.bx));
-      record_adjoint<T, C, ROT, 64>(r, g, V, y, grad2d + rec * kGradFloats, s_grad, lane);
+      record_adjoint<T, C, ROT>(r, g, V, y, grad2d + rec * kGradFloats, s_grad, lane);
     }
     q0 += nq;
     if (q0 >= S.n_views) break;
@@ -412,7 +408,7 @@ __global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel
     live = stage_views(q0, nq);
   }
   if (!active) return;
-  write_gradient<T, C, ROT, 64, true>(r, kept.par, stride, t, g, s_grad, lane, compact);
+  write_gradient<T, C, ROT, true>(r, kept.par, stride, t, g, s_grad, lane, compact);
 }
 
 // Adjoint of the float32 option (a lane per list entry, all lanes in step over

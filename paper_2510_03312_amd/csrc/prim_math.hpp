@@ -485,29 +485,57 @@ __device__ __forceinline__ void view_forward(const Raw<C, ROT>& r, const Geo<T, 
   s.live = live;
 }
 
-// The gradients w.r.t. the view-independent quantities, summed over views,
-// live in LDS, one float32 each (each view's contribution is evaluated in T):
-// entry k of a primitive in row k.  Rows: G_Sc (6), G_A (3 C), G_Li (lower
-// triangle, row-major), mu_x, mu_q, b_q, bt, b_x, o, rgb.
+// The gradients w.r.t. the view-independent quantities, summed over views.
+// Rows: G_Sc (6), bt, G_A (3 C), G_Li (lower triangle, row-major), mu_x, mu_q,
+// b_q, b_x, o, rgb.
 struct GradRows {
-  int sc, a, li, mu, muq, bq, bt, bx, o, rgb, N;
+  int sc, bt, a, li, mu, muq, bq, bx, o, rgb, N;
 };
 __host__ __device__ constexpr GradRows grad_rows(int C) {
   GradRows r{};
   int k = 0;
   r.sc = k; k += 6;
+  r.bt = k; k += C;
   r.a = k; k += 3 * C;
   r.li = k; k += C * (C + 1) / 2;
   r.mu = k; k += 3;
   r.muq = k; k += C;
   r.bq = k; k += C;
-  r.bt = k; k += C;
   r.bx = k; k += 1;
   r.o = k; k += 1;
   r.rgb = k; k += 3;
   r.N = k;
   return r;
 }
+
+// The sums of LANES primitives, in LDS: a lane's column holds its primitive's.
+// A view's contribution is added in float64.  G_Sc, and with ONE_VIEW G_A and bt,
+// stay float64: the last step forms parts of most parameters' gradients from
+// them, whose error they would be if rounded (rotations and log scales of one 7-D
+// view 3.6e-8 relative to float64, with the three in float64 2.5e-8).  The others
+// are rounded as they are kept.  (G_A in float64 over several views made that
+// adjoint 6 % slower by its LDS traffic, and it is no further off without than the
+// forms through Sigma_q^-1 were: 7-D in eight views 5.7e-8 against 7.0e-8.)
+template <int C, int LANES, bool ONE_VIEW>
+struct GradSums {
+  static constexpr int kWide = ONE_VIEW ? grad_rows(C).li : grad_rows(C).bt;
+  static constexpr int kRows = grad_rows(C).N - kWide;
+  double wide[kWide][LANES];
+  float row[kRows][LANES];
+  __host__ __device__ __forceinline__ void clear(int lane) {
+#pragma unroll
+    for (int k = 0; k < kWide; ++k) wide[k][lane] = 0.0;
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) row[k][lane] = 0.0f;
+  }
+  __host__ __device__ __forceinline__ void add(int k, double x, int lane) {
+    if (k < kWide) wide[k][lane] += x;
+    else row[k - kWide][lane] = float(double(row[k - kWide][lane]) + x);
+  }
+  __host__ __device__ __forceinline__ double get(int k, int lane) const {
+    return k < kWide ? wide[k][lane] : double(row[k - kWide][lane]);
+  }
+};
 
 // Adjoint of view_forward for one view.  gr: d loss / d record fields
 // (mx, my, a, b, c, o(q), beta, r, g, b); add(row, x) adds to a gradient row.
@@ -636,7 +664,7 @@ __device__ __forceinline__ void geo_backward(const Raw<C, ROT>& r, const Geo<T, 
   constexpr GradRows row = grad_rows(C);
   T Gsc[6];
 #pragma unroll
-  for (int k = 0; k < 6; ++k) Gsc[k] = T(grad(row.sc + k));
+  for (int k = 0; k < 6; ++k) Gsc[k] = grad(row.sc + k);
   T GM[3][3];
   // Sigma_c = M M^T - ... (G_Sc symmetric): G_M = 2 G_Sc M
 #pragma unroll
@@ -654,15 +682,15 @@ __device__ __forceinline__ void geo_backward(const Raw<C, ROT>& r, const Geo<T, 
 #pragma unroll
     for (int i = 0; i < C; ++i) {
 #pragma unroll
-      for (int j = 0; j <= i; ++j) GL[i][j] = T(grad(row.li + i * (i + 1) / 2 + j));
-      Gbt[i] = T(grad(row.bt + i));
+      for (int j = 0; j <= i; ++j) GL[i][j] = grad(row.li + i * (i + 1) / 2 + j);
+      Gbt[i] = grad(row.bt + i);
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       T GA[Cdim<C>::V], GH[Cdim<C>::V];
 #pragma unroll
       for (int k = 0; k < C; ++k) {
-        GA[k] = T(grad(row.a + C * a + k));
+        GA[k] = grad(row.a + C * a + k);
         GH[k] = T(0);
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
@@ -724,7 +752,7 @@ __device__ __forceinline__ void geo_backward(const Raw<C, ROT>& r, const Geo<T, 
         T acc = GX[0][k] * g.M[0][j] + GX[1][k] * g.M[1][j] + GX[2][k] * g.M[2][j];
 #pragma unroll
         for (int m = 0; m < C; ++m) acc += GSs[k][m] * T(r.lqx[m][j]);
-        out(pr.lqx + 3 * k + j, float(acc));
+        out(pr.lqx + 3 * k + j, acc);
       }
     int idx = 0;
 #pragma unroll
@@ -735,7 +763,7 @@ __device__ __forceinline__ void geo_backward(const Raw<C, ROT>& r, const Geo<T, 
         T acc = GSs[i][j] * Ljj;
 #pragma unroll
         for (int m = j + 1; m < C; ++m) acc += GSs[i][m] * T(r.lq[m][j]);
-        out(pr.lq + idx, float(i == j ? acc * Ljj : acc));
+        out(pr.lq + idx, i == j ? acc * Ljj : acc);
         ++idx;
       }
 #pragma unroll
@@ -748,9 +776,9 @@ __device__ __forceinline__ void geo_backward(const Raw<C, ROT>& r, const Geo<T, 
 #pragma unroll
     for (int k = 0; k < C; ++k) {
       out(pr.mu_q + k, grad(row.muq + k));
-      T gbq = T(grad(row.bq + k));
+      T gbq = grad(row.bq + k);
       if (g.beta_cond && r.bq[k] < 0.0f) gbq += Gbt[k] * g.bt[k];
-      out(pr.b_q + k, float(gbq));
+      out(pr.b_q + k, gbq);
     }
   }
   // M = R diag(s)
@@ -763,7 +791,7 @@ __device__ __forceinline__ void geo_backward(const Raw<C, ROT>& r, const Geo<T, 
       GR[i][j] = GM[i][j] * g.s[j];
       acc += GM[i][j] * g.M[i][j];   // M = R diag(s): d/d log s_j = sum_i GM_ij R_ij s_j
     }
-    out(pr.log_s + j, float(acc));
+    out(pr.log_s + j, acc);
   }
   if (ROT == UBS_ROT_QUAT) {
     T iq = m_rsqrt<T>(T(r.rq[0]) * T(r.rq[0]) + T(r.rq[1]) * T(r.rq[1]) +
@@ -777,14 +805,14 @@ __device__ __forceinline__ void geo_backward(const Raw<C, ROT>& r, const Geo<T, 
     T gz = T(2) * (-T(2) * z * GR[0][0] - w * GR[0][1] + x * GR[0][2] + w * GR[1][0] - T(2) * z * GR[1][1] +
                    y * GR[1][2] + x * GR[2][0] + y * GR[2][1]);
     T dotq = w * gw + x * gx + y * gy + z * gz;
-    out(pr.rot + 0, float((gw - w * dotq) * iq));
-    out(pr.rot + 1, float((gx - x * dotq) * iq));
-    out(pr.rot + 2, float((gy - y * dotq) * iq));
-    out(pr.rot + 3, float((gz - z * dotq) * iq));
+    out(pr.rot + 0, (gw - w * dotq) * iq);
+    out(pr.rot + 1, (gx - x * dotq) * iq);
+    out(pr.rot + 2, (gy - y * dotq) * iq);
+    out(pr.rot + 3, (gz - z * dotq) * iq);
   } else {
-    out(pr.rot + 0, float(GR[2][1] - GR[1][2]));
-    out(pr.rot + 1, float(GR[0][2] - GR[2][0]));
-    out(pr.rot + 2, float(GR[1][0] - GR[0][1]));
+    out(pr.rot + 0, GR[2][1] - GR[1][2]);
+    out(pr.rot + 1, GR[0][2] - GR[2][0]);
+    out(pr.rot + 2, GR[1][0] - GR[0][1]);
   }
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
