@@ -36,8 +36,8 @@
 namespace ubs {
 
 // exp of a float32 parameter.  In float64: x = n ln 2 + r with |r| <= ln 2 / 2
-// (ln 2 in two parts, the first with 21 trailing zero bits, so that n times
-// it is exact), exp(r) = 1 + r + r^2 Q(r) with Q the polynomial of degree 9
+// (ln 2 in two parts, as fdlibm's exp splits it: the first with 21 trailing zero
+// bits, so that n times it is exact), exp(r) = 1 + r + r^2 Q(r) with Q the polynomial of degree 9
 // through (exp(r) - 1 - r) / r^2 at ten Chebyshev nodes (relative error of
 // exp(r) 1.6e-17), scaled by 2^n (to infinity or zero beyond the range).
 // 20 instructions; the library's exp, whose argument may be any float64, 32.
@@ -73,13 +73,18 @@ template <> __device__ __forceinline__ double m_rsqrt<double>(double x) { return
 __device__ __forceinline__ float s_exp(float x) { return expf(x); }
 __device__ __forceinline__ float s_log1p(float x) { return log1pf(x); }
 
-// The same factors in the adjoint, where no decision hangs on their last bit:
-// exp(y) for y <= 0 and log(1 + t) for t in [0, 1] in float64 to about 3e-10
-// (exp(y) = 2^n (1 + r + r^2 Q(r)), Q of degree 5 through six Chebyshev nodes
-// of |r| <= ln 2 / 2, y below -800 giving 0; log(1 + t) = t P(t), P of degree
-// 10 through eleven).  13 and 11 instructions; the library's float32 expf and
-// log1pf take about 25 and 70 and round to float32, but their bits decide
-// records' opacities, so the forward keeps them.
+// The same factors in the adjoint, where no decision hangs on their last bit, in
+// float64: exp(y) for y <= 0 within 2.2e-10 (exp(y) = 2^n (1 + r + r^2 Q(r)), Q of
+// degree 5 through six Chebyshev nodes of |r| <= ln 2 / 2, y below -800 giving 0),
+// and log(1 + t) for t in [0, 1] within 8.5e-10 relative and 4.5e-10 absolute (t P(t),
+// P of degree 10 through eleven).  13 and 11 instructions; the library's float32
+// expf and log1pf take about 25 and 70 and round to float32, but their bits
+// decide records' opacities, so the forward keeps them.
+// Near w = 0 (t = 1) log(1 - tanh(w^2)) is the difference log 2 - 2 w^2 -
+// log(1 + t), which goes to -w^2 and keeps an absolute error of 4.5e-10 (of 3e-8
+// with log1pf): d/d b_q of a primitive queried that close to its mean, |w| below
+// about 2e-5, has no correct digits, and is at most 4.5e-10 of its d/d log o(q)
+// times e.
 __device__ __forceinline__ double s_exp_neg(double y) {
   const double yc = __builtin_fmax(y, -800.0);
   const double n = __builtin_rint(yc * 0x1.71547652b82fep+0);

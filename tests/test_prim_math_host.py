@@ -1,6 +1,8 @@
 """The per-primitive adjoint's mathematics (``csrc/prim_math.hpp``), compiled
-for the host, against float64: the parameter gradients are off float64 autograd
-of the oracle by no more than the float32 sums they are kept in account for.
+for the host, against float64: the polynomials that replace library functions
+stay within the bounds their comments state, and the parameter gradients are
+off float64 autograd of the oracle by no more than the float32 sums they are
+kept in account for.
 
 Bars of the gradients (relative L2 error of a block).  The error of sums over
 views that are rounded to float32 once per view, each exact contribution added
@@ -84,6 +86,22 @@ static void gradients(const char* in, const char* out, size_t n, int n_views) {
 }
 
 int main(int argc, char** argv) {
+  if (!strcmp(argv[1], "poly")) {
+    double e_exp = 0, e_neg = 0, r_log = 0, a_log = 0, e_tanh = 0;
+    for (int k = 0; k <= 400000; ++k) {
+      const float x = -87.0f + 174.0f * float(k) / 400000.0f;
+      e_exp = fmax(e_exp, fabs(m_exp<double>(x) / exp(double(x)) - 1.0));
+      const double y = -700.0 * k / 400000.0;
+      e_neg = fmax(e_neg, fabs(s_exp_neg(y) / exp(y) - 1.0));
+      const double t = (k + 0.0) / 400000.0, l = log1p(t);
+      a_log = fmax(a_log, fabs(s_log1p_unit(t) - l));
+      if (t > 0) r_log = fmax(r_log, fabs(s_log1p_unit(t) / l - 1.0));
+      e_tanh = fmax(e_tanh, fabs(s_half_tanh(t) * (1.0 + t) - 1.0));
+    }
+    r_log = fmax(r_log, fabs(s_log1p_unit(1e-12) / log1p(1e-12) - 1.0));
+    printf("%.17g %.17g %.17g %.17g %.17g\n", e_exp, e_neg, r_log, a_log, e_tanh);
+    return 0;
+  }
   const int dim = atoi(argv[1]), rot = atoi(argv[2]);
   const size_t n = size_t(atoll(argv[5]));
   const int nv = atoi(argv[6]);
@@ -111,6 +129,14 @@ def harness(tmp_path_factory):
     subprocess.run([hip_build.HIPCC, *hip_build.FLAGS, "--cuda-host-only", "-w", str(src), "-o",
                     str(exe)], check=True, capture_output=True)
     return str(exe), d
+
+
+def test_polynomials_stay_within_their_bounds(harness):
+    out = subprocess.run([harness[0], "poly"], check=True, capture_output=True, text=True).stdout
+    e_exp, e_neg, r_log, a_log, e_tanh = (float(x) for x in out.split())
+    print(out)
+    assert e_exp <= 2.3e-16                     # an ulp
+    assert e_neg <= 2.3e-10 and r_log <= 8.5e-10 and a_log <= 4.6e-10 and e_tanh <= 1e-14
 
 
 def _case(dim, rot, n, n_views):
