@@ -289,35 +289,44 @@ __device__ __forceinline__ void write_gradient(const Raw<C, ROT>& r, const float
 // Bound by latency: the float64 state leaves two wavefronts per SIMD (one
 // beyond 7-D), so a workgroup is one wavefront (a SIMD takes the next as soon
 // as it is free, not when its workgroup's others are), the parameters, the
-// list entry and the list's count are read together, the gradient rows lie in
+// list entry and the list's count are read together, the gradient sums lie in
 // LDS and not in registers, and the last step reads the parameters again.
 // With the triangular forms of prim_math.hpp: 1M 7-D at 1080p 49 -> 34 us, 1M
-// 6-D 55 -> 38, 1M 10-D 223 -> 43 (its state no longer spills).  A scene of up
-// to kOneRound primitives fills no SIMD twice: it keeps the parameters in
-// registers instead (250,000 7-D 14.2 us, 18 with AGAIN).
+// 6-D 55 -> 38, 1M 10-D 223 -> 43 (its state no longer spills).
+// The parameters stay in registers where that costs nothing: where a SIMD has
+// as many wavefronts with them (3-D, four, and 6-D skew, two: 1M 6-D skew, a
+// third kept, 76 -> 72 us with the scatter, all kept 159 -> 150), and in scenes of
+// up to kOneRound primitives (7-D and 6-D quaternion, one wavefront a SIMD with
+// them: 65,536 kept entries at once, which a fifth or a third of 2^18 primitives
+// is about: a fifth of 200,000 7-D kept 30.8 -> 25.5 us, a third of 50,000 6-D
+// 20.4 -> 19.5; but 100,000 to 260,000 7-D all kept 5 to 9 % slower, and 400,000,
+// a fifth kept, 40.6 -> 42.6).
+// 3-D has 14 sums, in registers, and workgroups of 256 (1M, half kept: 35.7 us
+// with sums in LDS and the parameters read again, 31.5 so; one wavefront a
+// workgroup in two views 74, four 67).
 constexpr int64_t kOneRound = 1 << 18;
+constexpr int bwd_threads(int C) { return C == 0 ? 256 : 64; }
+constexpr bool parameters_fit(int C, int rot) { return C == 0 || (C == 3 && rot == UBS_ROT_SKEW); }
 
 template <typename T, int C, int ROT, bool AGAIN>
-__global__ void __launch_bounds__(64, AGAIN && C <= 4 ? 2 : 1) preprocess_bwd_kernel(
+__global__ void __launch_bounds__(bwd_threads(C), AGAIN && C <= 4 ? 2 : 1) preprocess_bwd_kernel(
     DevScene S, const DevView* __restrict__ views,
     const float* __restrict__ records, float* __restrict__ grad2d, LiveIn kept,
     float* __restrict__ compact) {
-  __shared__ GradSums<C, 64, true> s_grad;
-  // workgroup b takes entries 64 (b / kKeptLists) + [0, 64) of kept list
-  // b mod kKeptLists (cap is a multiple of 64), so the workgroups holding
-  // entries come first in the grid whatever the lists' counts
-  const int lane = threadIdx.x;
+  // workgroup b takes entries N (b / kKeptLists) + [0, N) of kept list
+  // b mod kKeptLists (cap is a multiple of N, its threads), so the workgroups
+  // holding entries come first in the grid whatever the lists' counts
+  constexpr uint32_t N = bwd_threads(C);
   const uint32_t lo = blockIdx.x % kKeptLists;
-  const uint32_t pos = (blockIdx.x / kKeptLists) * 64u + threadIdx.x;
+  const uint32_t pos = (blockIdx.x / kKeptLists) * N + threadIdx.x;
   const uint32_t t = lo * kept.cap + pos;
   const uint32_t n_entries = kept.count[lo];
-  if ((blockIdx.x / kKeptLists) * 64u >= n_entries) return;
+  if ((blockIdx.x / kKeptLists) * N >= n_entries) return;
   // (a lane past the list's end reads an unused entry of its own list and column)
   const uint32_t i = kept.list[t];
   const int64_t stride = int64_t(kKeptLists) * kept.cap;
   Raw<C, ROT> r;
   load_raw<C, ROT>(kept.par, stride, t, r);
-  s_grad.clear(lane);
   if (pos >= n_entries) return;
   const DevView& V = views[views[S.view0].by_scene];
   const size_t rec = size_t(V.rec_base) + i;
@@ -327,9 +336,19 @@ __global__ void __launch_bounds__(64, AGAIN && C <= 4 ? 2 : 1) preprocess_bwd_ke
   Geo<T, C, ROT> g;
   geo_forward<T, C, ROT>(r, g, S.variant);
   if constexpr (AGAIN) load_record(kept.rec_live, records, grad2d, rec, x);
-  if (x.live)
-    record_adjoint<T, C, ROT>(r, g, V, x, grad2d + rec * kGradFloats, s_grad, lane);
-  write_gradient<T, C, ROT, AGAIN>(r, kept.par, stride, t, g, s_grad, lane, compact);
+  auto finish = [&](auto& sums, int column) {
+    sums.clear(column);
+    if (x.live)
+      record_adjoint<T, C, ROT>(r, g, V, x, grad2d + rec * kGradFloats, sums, column);
+    write_gradient<T, C, ROT, AGAIN>(r, kept.par, stride, t, g, sums, column, compact);
+  };
+  if constexpr (C == 0) {
+    GradSums<C, 1, true> sums;
+    finish(sums, 0);
+  } else {
+    __shared__ GradSums<C, N, true> s_grad;
+    finish(s_grad, threadIdx.x);
+  }
 }
 
 // Adjoint of a scene that several views see.  A primitive is live in some of
@@ -347,17 +366,16 @@ constexpr int kManyViews = 32;   // views of a live mask
 constexpr int kViewWords = int(sizeof(DevView) / 4);
 
 template <typename T, int C, int ROT>
-__global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel(
+__global__ void __launch_bounds__(bwd_threads(C), C <= 4 ? 2 : 1) preprocess_bwd_many_kernel(
     DevScene S, const DevView* __restrict__ views,
     const float* __restrict__ records, float* __restrict__ grad2d, LiveIn kept,
     float* __restrict__ compact) {
-  __shared__ GradSums<C, 64, false> s_grad;
   __shared__ uint32_t s_views[kManyViews][kViewWords];
-  const int lane = threadIdx.x;
+  constexpr uint32_t N = bwd_threads(C);
   const uint32_t lo = blockIdx.x % kKeptLists;
-  const uint32_t pos = (blockIdx.x / kKeptLists) * 64u + threadIdx.x;
+  const uint32_t pos = (blockIdx.x / kKeptLists) * N + threadIdx.x;
   const uint32_t n_entries = kept.count[lo];
-  if ((blockIdx.x / kKeptLists) * 64u >= n_entries) return;
+  if ((blockIdx.x / kKeptLists) * N >= n_entries) return;
   const bool active = pos < n_entries;
   // (a lane past the list's end reads an unused entry of its own list and column)
   const uint32_t t = lo * kept.cap + pos;
@@ -371,7 +389,7 @@ __global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel
   // live records among them as a mask
   auto stage_views = [&](int q0, int nq) {
     __syncthreads();
-    for (int w = lane; w < nq * kViewWords; w += 64)
+    for (int w = threadIdx.x; w < nq * kViewWords; w += N)
       s_views[w / kViewWords][w % kViewWords] =
           reinterpret_cast<const uint32_t*>(views + views[S.view0 + q0 + w / kViewWords].by_scene)[w % kViewWords];
     __syncthreads();
@@ -383,32 +401,41 @@ __global__ void __launch_bounds__(64, C <= 4 ? 2 : 1) preprocess_bwd_many_kernel
   };
   int nq = min(kManyViews, S.n_views);
   uint32_t live = stage_views(0, nq);
-  s_grad.clear(lane);
   Geo<T, C, ROT> g;
   geo_forward<T, C, ROT>(r, g, S.variant);
-  for (int q0 = 0;;) {
-    while (live != 0) {
-      const int cur = __ffs(int(live)) - 1;
-      live &= live - 1;
-      const DevView& V = view(cur);
-      const size_t rec = size_t(V.rec_base) + i;
-      RecordIn y;
-      load_record(kept.rec_live, records, grad2d, rec, y);
-      // (not carried from view to view as float64 copies)
+  auto finish = [&](auto& sums, int column) {
+    sums.clear(column);
+    for (int q0 = 0;;) {
+      while (live != 0) {
+        const int cur = __ffs(int(live)) - 1;
+        live &= live - 1;
+        const DevView& V = view(cur);
+        const size_t rec = size_t(V.rec_base) + i;
+        RecordIn y;
+        load_record(kept.rec_live, records, grad2d, rec, y);
+        // (not carried from view to view as float64 copies)
 #pragma unroll
-      for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(r.mu[k]));
+        for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(r.mu[k]));
 #pragma unroll
-      for (int k = 0; k < C; ++k) asm volatile("" : "+v"(r.muq[k]));
-      asm volatile("" : "+v"(r.o), "+v"(r.bx));
-      record_adjoint<T, C, ROT>(r, g, V, y, grad2d + rec * kGradFloats, s_grad, lane);
+        for (int k = 0; k < C; ++k) asm volatile("" : "+v"(r.muq[k]));
+        asm volatile("" : "+v"(r.o), "+v"(r.bx));
+        record_adjoint<T, C, ROT>(r, g, V, y, grad2d + rec * kGradFloats, sums, column);
+      }
+      q0 += nq;
+      if (q0 >= S.n_views) break;
+      nq = min(kManyViews, S.n_views - q0);
+      live = stage_views(q0, nq);
     }
-    q0 += nq;
-    if (q0 >= S.n_views) break;
-    nq = min(kManyViews, S.n_views - q0);
-    live = stage_views(q0, nq);
+    if (!active) return;
+    write_gradient<T, C, ROT, C != 0>(r, kept.par, stride, t, g, sums, column, compact);
+  };
+  if constexpr (C == 0) {
+    GradSums<C, 1, false> sums;
+    finish(sums, 0);
+  } else {
+    __shared__ GradSums<C, N, false> s_grad;
+    finish(s_grad, threadIdx.x);
   }
-  if (!active) return;
-  write_gradient<T, C, ROT, true>(r, kept.par, stride, t, g, s_grad, lane, compact);
 }
 
 // Adjoint of the float32 option (a lane per list entry, all lanes in step over
@@ -528,21 +555,22 @@ static hipError_t pre_bwd_t(const DevScene& S, const DevView* views,
                             hipStream_t st) {
   // one lane per entry of the kKeptLists lists of cap entries
   const uint64_t entries = uint64_t(kKeptLists) * kept.cap;
+  constexpr unsigned N = bwd_threads(C);
   if constexpr (std::is_same<T, float>::value) {
     hipLaunchKernelGGL((preprocess_bwd_f32_kernel<C, ROT>), dim3(unsigned(entries / 256)),
                        dim3(256), 0, st, S, views, records, grad2d, kept, compact);
   } else if (S.n_views == 1) {
-    constexpr bool kMayKeep = C <= 4;   // (beyond 7-D the state spills with the parameters in it)
-    if (kMayKeep && S.n <= kOneRound)
-      hipLaunchKernelGGL((preprocess_bwd_kernel<T, C, ROT, !kMayKeep>),
-                         dim3(unsigned(entries / 64)), dim3(64), 0, st, S, views,
-                         records, grad2d, kept, compact);
+    // (beyond 7-D the state spills with the parameters in it)
+    constexpr bool kMayKeep = C <= 4, kKeep = parameters_fit(C, ROT);
+    if (kKeep || (kMayKeep && S.n <= kOneRound))
+      hipLaunchKernelGGL((preprocess_bwd_kernel<T, C, ROT, !kMayKeep>), dim3(unsigned(entries / N)),
+                         dim3(N), 0, st, S, views, records, grad2d, kept, compact);
     else
-      hipLaunchKernelGGL((preprocess_bwd_kernel<T, C, ROT, true>), dim3(unsigned(entries / 64)),
-                         dim3(64), 0, st, S, views, records, grad2d, kept, compact);
+      hipLaunchKernelGGL((preprocess_bwd_kernel<T, C, ROT, !kKeep>), dim3(unsigned(entries / N)),
+                         dim3(N), 0, st, S, views, records, grad2d, kept, compact);
   } else {
-    hipLaunchKernelGGL((preprocess_bwd_many_kernel<T, C, ROT>), dim3(unsigned(entries / 64)),
-                       dim3(64), 0, st, S, views, records, grad2d, kept, compact);
+    hipLaunchKernelGGL((preprocess_bwd_many_kernel<T, C, ROT>), dim3(unsigned(entries / N)),
+                       dim3(N), 0, st, S, views, records, grad2d, kept, compact);
   }
   // 16-byte stores when every row of dparams starts 16-byte aligned
   if (S.n % 4 == 0 && reinterpret_cast<uintptr_t>(S.dparams) % 16 == 0)
