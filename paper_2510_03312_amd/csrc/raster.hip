@@ -3,8 +3,8 @@
 // One wavefront (64 lanes) per tile, or per band of TH / SPLIT rows of it in
 // frames of few tiles and for wide tiles.  Lane l owns the pixels of column
 // l % TW in rows l / TW + k * (64 / TW) of its band (a whole 16x16 tile gives
-// each lane a strip of 4 pixels).  The tile's sorted records are staged through LDS 64 at
-// a time (one per lane); every lane then walks the batch.  Because a lane's
+// each lane a strip of 4 pixels).  The tile's sorted records are staged through
+// LDS 64 at a time (one per lane); every lane then walks the batch.  Because a lane's
 // pixels share one column, dx = px - mx is shared and the quadratic form
 // costs r = A + dy (B + c dy) per pixel with A, B per record.
 //
@@ -15,7 +15,8 @@
 // first sums the gradient terms of its own pixels; the wavefront then folds
 // the ten per-record sums of two records onto fewer lanes with lane swaps,
 // finishes them with DPP sums within 16-lane rows and banks, and twenty lanes
-// add the totals to the records' accumulators in one atomic instruction.
+// add the totals to the records' accumulators in one atomic instruction (four
+// bands of a tile add theirs in LDS first).
 //
 // Both passes are bound by vector instruction issue (the per-pixel code runs
 // for the 2.6 of a tile's four 64-pixel strips that a record's ellipse
@@ -333,34 +334,35 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
   return x;
 }
 
-// HAS_DT: a gradient of the final transmittance is given (d_tfinal).
-template <int TW, int TH, int BATCH, int SPLIT, bool HAS_DT>
-__device__ __forceinline__ void raster_bwd_tile(
-    uint32_t tile, int band, float4* s0, float4* s1, float4* s2, uint32_t* s_pos,
-    const float* __restrict__ records,
-    const uint32_t* __restrict__ values, const uint32_t* __restrict__ ranges,
-    const DevView* __restrict__ views, int n_views, const float* __restrict__ t_ws,
-    const uint32_t* __restrict__ ncontrib, const float* __restrict__ d_image,
-    const float* __restrict__ d_tfinal, const float* __restrict__ l1_image,
-    const float* __restrict__ l1_target, float l1_scale, float* __restrict__ grad2d) {
-  constexpr int PPL = TileGeom<TW, TH, SPLIT>::PPL;
-  constexpr int RSTEP = TileGeom<TW, TH, SPLIT>::RSTEP;
-  constexpr int PER_LANE = BATCH / 64;
-  const int lane = threadIdx.x;
-  const DevView& V = views[view_of_tile(views, n_views, tile)];
-  const uint32_t lt = tile - V.tile_base;
-  const int ty = int(lt) / V.tiles_x, tx = int(lt) - ty * V.tiles_x;
-  const int px = tx * TW + lane % TW;
-  const int py0 = ty * TH + band * TileGeom<TW, TH, SPLIT>::ROWS + lane / TW;
-  const float fx = float(px) + 0.5f;
-  const float band_y0 = float(ty * TH + band * TileGeom<TW, TH, SPLIT>::ROWS) + 0.5f;
-  const float band_y1 = band_y0 + float(TileGeom<TW, TH, SPLIT>::ROWS - 1);
-  const uint32_t start = ranges[2 * size_t(tile)];
-  // gTf: d loss / d T_final times T_final (the transmittance gradient enters
-  // every record's d alpha as - gTf / (1 - alpha)); D: the pixel's colour
-  // gradient dotted with the colour composited behind the current record
+// What a lane keeps of its pixels in the backward walk: the transmittance in
+// front of the current record; D, the pixel's colour gradient dotted with the
+// colour composited behind it; the colour gradient; gTf = d loss / d T_final
+// times T_final (HAS_DT: a gradient of the final transmittance is given; it
+// enters every record's d alpha as - gTf / (1 - alpha)); the last contributor.
+template <int PPL>
+struct BwdPixels {
   float T[PPL], D[PPL], gR[PPL], gG[PPL], gB[PPL], gTf[PPL];
   uint32_t last[PPL];
+};
+// Where a wavefront's walk starts: records before `span` may contribute.
+// Records at or beyond a pixel's last contributor contribute nothing to it
+// unless the pixel stopped (its own alpha test fails there otherwise), so only
+// records at or beyond `stop_min`, the smallest last contributor of a stopped
+// pixel, need the position test.  (Both wavefront-uniform: the batch loop runs
+// on scalar counters.)
+struct BwdSpan {
+  uint32_t span, stop_min;
+};
+struct BwdGradients {
+  const float *d_image, *d_tfinal, *l1_image, *l1_target;
+  float l1_scale;
+};
+
+template <int PPL, int RSTEP, bool HAS_DT>
+__device__ __forceinline__ BwdSpan load_pixels(BwdPixels<PPL>& P, const DevView& V, int px, int py0,
+                                               const float* __restrict__ t_ws,
+                                               const uint32_t* __restrict__ ncontrib,
+                                               const BwdGradients& G) {
   uint32_t lane_max = 0, lane_stop = 0xffffffffu;
 #pragma unroll
   for (int k = 0; k < PPL; ++k) {
@@ -369,47 +371,171 @@ __device__ __forceinline__ void raster_bwd_tile(
     // position is tested, and with T = 0 its every term is 0, where T = 1 would
     // grow by 1 / (1 - alpha) a record to infinity and leave a NaN in the sums)
     float Tf = 0.0f;
-    gR[k] = gG[k] = gB[k] = gTf[k] = 0.0f; last[k] = 0;
+    P.gR[k] = P.gG[k] = P.gB[k] = P.gTf[k] = 0.0f; P.last[k] = 0;
     if (px < V.W && py < V.H) {
       const size_t pix = size_t(V.pix_base) + size_t(py) * V.W + px;
       Tf = t_ws[pix];
-      last[k] = ncontrib[pix];
+      P.last[k] = ncontrib[pix];
       if (Tf < 0.0f) {   // the pixel stopped
         Tf = -Tf;
-        lane_stop = min(lane_stop, last[k]);
+        lane_stop = min(lane_stop, P.last[k]);
       }
-      if (d_image) {
-        gR[k] = d_image[3 * pix];
-        gG[k] = d_image[3 * pix + 1];
-        gB[k] = d_image[3 * pix + 2];
-        if (HAS_DT) gTf[k] = d_tfinal[pix] * Tf;
+      if (G.d_image) {
+        P.gR[k] = G.d_image[3 * pix];
+        P.gG[k] = G.d_image[3 * pix + 1];
+        P.gB[k] = G.d_image[3 * pix + 2];
+        if (HAS_DT) P.gTf[k] = G.d_tfinal[pix] * Tf;
       } else {
-        const float e0 = l1_image[3 * pix] - l1_target[3 * pix];
-        const float e1 = l1_image[3 * pix + 1] - l1_target[3 * pix + 1];
-        const float e2 = l1_image[3 * pix + 2] - l1_target[3 * pix + 2];
-        gR[k] = e0 > 0.0f ? l1_scale : (e0 < 0.0f ? -l1_scale : 0.0f);
-        gG[k] = e1 > 0.0f ? l1_scale : (e1 < 0.0f ? -l1_scale : 0.0f);
-        gB[k] = e2 > 0.0f ? l1_scale : (e2 < 0.0f ? -l1_scale : 0.0f);
+        const float e0 = G.l1_image[3 * pix] - G.l1_target[3 * pix];
+        const float e1 = G.l1_image[3 * pix + 1] - G.l1_target[3 * pix + 1];
+        const float e2 = G.l1_image[3 * pix + 2] - G.l1_target[3 * pix + 2];
+        P.gR[k] = e0 > 0.0f ? G.l1_scale : (e0 < 0.0f ? -G.l1_scale : 0.0f);
+        P.gG[k] = e1 > 0.0f ? G.l1_scale : (e1 < 0.0f ? -G.l1_scale : 0.0f);
+        P.gB[k] = e2 > 0.0f ? G.l1_scale : (e2 < 0.0f ? -G.l1_scale : 0.0f);
       }
     }
-    T[k] = Tf;
-    D[k] = 0.0f;
-    lane_max = max(lane_max, last[k]);
+    P.T[k] = Tf;
+    P.D[k] = 0.0f;
+    lane_max = max(lane_max, P.last[k]);
   }
-  // (wavefront-uniform: the batch loop runs on scalar counters)
-  const uint32_t span = __builtin_amdgcn_readfirstlane(wave_max_u32(lane_max));
-  // Records at or beyond a pixel's last contributor contribute nothing to it
-  // unless the pixel stopped (its own alpha test fails there otherwise), so
-  // only records at or beyond the smallest last contributor of a stopped
-  // pixel need the position test.
-  const uint32_t stop_min = __builtin_amdgcn_readfirstlane(wave_min_u32(lane_stop));
-  // the field this lane adds for a pair of records (add_pair), or -1
-  int out_field = -1;
-  if ((lane & 3) == 0)
-    out_field = 4 * ((lane >> 2) & 1) + 2 * ((lane >> 3) & 1) + (lane >> 5);
-  else if ((lane & 15) == 1)
-    out_field = 8 + (lane >> 5);
-  for (uint32_t hi = span; hi > 0;) {
+  return BwdSpan{uint32_t(__builtin_amdgcn_readfirstlane(wave_max_u32(lane_max))),
+                 uint32_t(__builtin_amdgcn_readfirstlane(wave_min_u32(lane_stop)))};
+}
+
+// One record: the lane's pixel sums, folded (CHECK: test each pixel's last
+// contributor against the record's position).
+template <bool CHECK, int PPL, int RSTEP, bool HAS_DT>
+__device__ __forceinline__ void bwd_record(BwdPixels<PPL>& P, const float4 g0, const float4 g1,
+                                           const float4 g2, float fx, int py0, uint32_t pos,
+                                           float* h) {
+  const float dx = fx - g0.x;
+  const ColTerms ct = col_terms(g0, dx);
+  // sums over the lane's pixels (its column): q = sigma dalpha / (1 - r),
+  // dx-weighted moments come from the shared dx
+  // (zeroed through an opaque value: a plain zero would be rematerialised
+  // on every accumulating iteration)
+  float a_o, a_be, a_r, a_g, a_b, a_dr, a_dry, a_dryy;
+  opaque_zero2(a_o, a_be);
+  opaque_zero2(a_r, a_g);
+  opaque_zero2(a_b, a_dr);
+  opaque_zero2(a_dry, a_dryy);
+  // (full unroll: each pixel's state is then a fixed register; a loop
+  // iterated dynamically moves it in and out of a common window)
+#pragma unroll
+  for (int k = 0; k < PPL; ++k) {
+    const float dy = float(py0 + k * RSTEP) + 0.5f - g0.y;
+    const float r = eval_r(ct, g1.x, dy);
+    if (!((!CHECK || pos < P.last[k]) && r <= g1.y)) continue;
+    float l2;
+    const float sigma = eval_sigma(r, g1.z, g1.w, &l2);
+    const float alpha = fminf(kAlphaMax, sigma);
+    if (!(alpha >= kAlphaMin)) continue;   // (the support's rim)
+    const float ioma = fast_rcp(1.0f - alpha);
+    const float Ti = P.T[k] * ioma;
+    const float w = alpha * Ti;
+    a_r += P.gR[k] * w;
+    a_g += P.gG[k] * w;
+    a_b += P.gB[k] * w;
+    // d loss / d alpha = T_k g . (c_k - S_k) (- gTf / (1 - alpha)),
+    // S_k the normalised colour composited behind record k; S updates as
+    // S += alpha (c - S), so D = g . S as D += alpha dot
+    const float dot = (P.gR[k] * g2.x + P.gG[k] * g2.y + P.gB[k] * g2.z) - P.D[k];
+    const float dalpha = HAS_DT ? Ti * dot - P.gTf[k] * ioma : Ti * dot;
+    P.D[k] += alpha * dot;
+    P.T[k] = Ti;
+    if (!(alpha < kAlphaMax)) continue;   // (sigma follows alpha below the clamp only)
+    const float sd = alpha * dalpha;
+    a_o += sd;
+    a_be += sd * l2;
+    const float q = sd * fast_rcp(1.0f - r);
+    a_dr += q;
+    const float qy = q * dy;
+    a_dry += qy;
+    a_dryy += qy * dy;
+  }
+  // the record's pixel sums P, Q, U, V, E, A_o, A_b and colour (zeros for
+  // a record none of whose pixels contribute, a few in a hundred
+  // thousand; the per-primitive adjoint turns them into record-field
+  // gradients), the wavefront's halves folded onto each other: field 2p
+  // in lanes 0-31 of h[p], field 2p+1 in lanes 32-63
+  const float gv0 = dx * a_dr;
+  const float gv[kGradFloats] = {gv0, a_dry, dx * gv0, dx * a_dry, a_dryy,
+                                 a_o, a_be,  a_r,      a_g,        a_b};
+#pragma unroll
+  for (int p = 0; p < 5; ++p) {
+    const FPair sw = swap_halves(gv[2 * p], gv[2 * p + 1]);
+    h[p] = sw.a + sw.b;
+  }
+}
+
+// Two records' folded sums to their totals: the value this lane holds of field
+// pair_field(lane) (none where that is -1), of record a in the even rows of 16
+// lanes and of record b in the odd rows.  Every step but the last two halves the
+// number of registers, as a step of two registers is one of each half, row,
+// half-row or bank; a single record's ten fields leave the later steps half
+// empty (31 vector instructions a record, against 24 for two at a time).
+__device__ __forceinline__ int pair_field(int lane) {
+  if ((lane & 3) == 0) return 4 * ((lane >> 2) & 1) + 2 * ((lane >> 3) & 1) + (lane >> 5);
+  if ((lane & 15) == 1) return 8 + (lane >> 5);
+  return -1;
+}
+__device__ __forceinline__ float pair_total(const float* ha, const float* hb, int lane) {
+  float t[5];   // rows: field 2p of a, of b, field 2p + 1 of a, of b
+#pragma unroll
+  for (int p = 0; p < 5; ++p) {
+    const FPair sw = swap_rows(ha[p], hb[p]);
+    t[p] = sw.a + sw.b;
+  }
+  // u0: t0 in the lower half-rows, t1 in the upper; u1: t2, t3; u2: t4;
+  // then t0: banks u0, u1, u0, u1 (fields of t0, t2, t1, t3), t4: u2; then
+  // the sums within the banks of four lanes.  (Two wait states between
+  // the write of a register and its DPP read: by the order and the nops.)
+  float u0, u1, u2;
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %5, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %6, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %7, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %6, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %4, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %6, %6 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
+      : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "=&v"(u0), "=&v"(u1),
+        "=&v"(u2));
+  return (lane & 1) ? t[4] : t[0];
+}
+
+// One wavefront per tile (SPLIT 1) or per band of a tile of two; each adds its
+// records' totals itself.
+template <int TW, int TH, int BATCH, int SPLIT, bool HAS_DT>
+__device__ __forceinline__ void raster_bwd_tile(
+    uint32_t tile, int band, float4* s0, float4* s1, float4* s2, uint32_t* s_pos,
+    const float* __restrict__ records, const uint32_t* __restrict__ values,
+    const uint32_t* __restrict__ ranges, const DevView* __restrict__ views, int n_views,
+    const float* __restrict__ t_ws, const uint32_t* __restrict__ ncontrib, const BwdGradients& G,
+    float* __restrict__ grad2d) {
+  using Geom = TileGeom<TW, TH, SPLIT>;
+  constexpr int PPL = Geom::PPL, RSTEP = Geom::RSTEP, PER_LANE = BATCH / 64;
+  const int lane = threadIdx.x;
+  const DevView& V = views[view_of_tile(views, n_views, tile)];
+  const uint32_t lt = tile - V.tile_base;
+  const int ty = int(lt) / V.tiles_x, tx = int(lt) - ty * V.tiles_x;
+  const int px = tx * TW + lane % TW;
+  const int y0 = ty * TH + band * Geom::ROWS, py0 = y0 + lane / TW;
+  const float fx = float(px) + 0.5f;
+  const float band_y0 = float(y0) + 0.5f, band_y1 = band_y0 + float(Geom::ROWS - 1);
+  const uint32_t start = ranges[2 * size_t(tile)];
+  BwdPixels<PPL> P;
+  const BwdSpan W = load_pixels<PPL, RSTEP, HAS_DT>(P, V, px, py0, t_ws, ncontrib, G);
+  const int out_field = pair_field(lane);
+  for (uint32_t hi = W.span; hi > 0;) {
     const uint32_t lo = hi > uint32_t(BATCH) ? hi - uint32_t(BATCH) : 0u;
     uint32_t cnt = hi - lo;
     __syncthreads();
@@ -449,114 +575,18 @@ __device__ __forceinline__ void raster_bwd_tile(
       cnt = n_kept;
     }
     __syncthreads();
-    // one record: the lane's pixel sums, folded (CHECK: test each pixel's last
-    // contributor)
     auto record = [&](auto check, int j, float* h) {
-      constexpr bool CHECK = decltype(check)::value;
-      const uint32_t pos = SPLIT == 1 ? lo + uint32_t(j) : s_pos[j];
-      const float4 g0 = s0[j], g1 = s1[j], g2 = s2[j];
-      const float dx = fx - g0.x;
-      const ColTerms ct = col_terms(g0, dx);
-      // per-lane sums over the lane's pixels (the factors common to a record,
-      // 1/o, ln 2 and -beta, are applied by the per-primitive adjoint):
-      //   a_o = sum s,  a_be = sum s log2(1 - r),  a_dr = sum s / (1 - r)
-      //   (a_dry, a_dryy: times dy, dy^2) with s = sigma d loss / d alpha
-      // (zeros the compiler cannot rematerialise: otherwise it re-creates
-      // them on every path that skips the first pixel's update)
-      float a_r, a_g, a_b, a_o, a_be, a_dr, a_dry, a_dryy;
-      opaque_zero2(a_r, a_g);
-      opaque_zero2(a_b, a_o);
-      opaque_zero2(a_be, a_dr);
-      opaque_zero2(a_dry, a_dryy);
-#pragma unroll
-      for (int k = 0; k < PPL; ++k) {
-        const float dy = float(py0 + k * RSTEP) + 0.5f - g0.y;
-        const float r = eval_r(ct, g1.x, dy);
-        if (!((!CHECK || pos < last[k]) && r <= g1.y)) continue;
-        float l2;
-        const float sigma = eval_sigma(r, g1.z, g1.w, &l2);
-        const float alpha = fminf(kAlphaMax, sigma);
-        if (!(alpha >= kAlphaMin)) continue;   // (the support's rim)
-        const float ioma = fast_rcp(1.0f - alpha);
-        const float Ti = T[k] * ioma;
-        const float w = alpha * Ti;
-        a_r += gR[k] * w;
-        a_g += gG[k] * w;
-        a_b += gB[k] * w;
-        // g . (c - S): the colour gradient g dotted with the record's colour
-        // minus the colour S composited behind it; S updates as
-        // S += alpha (c - S), so D = g . S as D += alpha dot
-        const float dot = (gR[k] * g2.x + gG[k] * g2.y + gB[k] * g2.z) - D[k];
-        const float dalpha = HAS_DT ? Ti * dot - gTf[k] * ioma : Ti * dot;
-        D[k] += alpha * dot;
-        T[k] = Ti;
-        if (!(alpha < kAlphaMax)) continue;   // (sigma follows alpha below the clamp only)
-        const float sd = alpha * dalpha;
-        a_o += sd;
-        a_be += sd * l2;
-        const float q = sd * fast_rcp(1.0f - r);
-        a_dr += q;
-        const float qy = q * dy;
-        a_dry += qy;
-        a_dryy += qy * dy;
-      }
-      // the record's pixel sums P, Q, U, V, E, A_o, A_b and colour (zeros for
-      // a record none of whose pixels contribute, a few in a hundred
-      // thousand; the per-primitive adjoint turns them into record-field
-      // gradients), the wavefront's halves folded onto each other: field 2p
-      // in lanes 0-31 of h[p], field 2p+1 in lanes 32-63
-      const float gv0 = dx * a_dr;
-      const float gv[kGradFloats] = {gv0, a_dry, dx * gv0, dx * a_dry, a_dryy,
-                                     a_o, a_be,  a_r,      a_g,        a_b};
-#pragma unroll
-      for (int p = 0; p < 5; ++p) {
-        const FPair sw = swap_halves(gv[2 * p], gv[2 * p + 1]);
-        h[p] = sw.a + sw.b;
-      }
+      bwd_record<decltype(check)::value, PPL, RSTEP, HAS_DT>(
+          P, s0[j], s1[j], s2[j], fx, py0, SPLIT == 1 ? lo + uint32_t(j) : s_pos[j], h);
     };
-    // two records' folded sums to their totals, added to their gradient rows.
-    // Every step but the last two halves the number of registers, as a step
-    // of two registers is one of each half, row, half-row or bank; a single
-    // record's ten fields leave the later steps half empty (31 vector
-    // instructions a record and an atomic instruction each, against 24 and
-    // half an atomic instruction for two at a time).
+    // one atomic instruction for two records: lane 0 of each bank adds a field
+    // of the first eight and lane 1 of each row one of the last two, odd rows
+    // for record b (none for jb < 0)
     auto add_pair = [&](const float* ha, const float* hb, int ja, int jb) {
-      float t[5];   // rows: field 2p of a, of b, field 2p + 1 of a, of b
-#pragma unroll
-      for (int p = 0; p < 5; ++p) {
-        const FPair sw = swap_rows(ha[p], hb[p]);
-        t[p] = sw.a + sw.b;
-      }
-      // u0: t0 in the lower half-rows, t1 in the upper; u1: t2, t3; u2: t4;
-      // then t0: banks u0, u1, u0, u1 (fields of t0, t2, t1, t3), t4: u2; then
-      // the sums within the banks of four lanes.  (Two wait states between
-      // the write of a register and its DPP read: by the order and the nops.)
-      float u0, u1, u2;
-      asm volatile(
-          "s_nop 1\n\t"
-          "v_add_f32_dpp %5, %0, %0 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-          "v_add_f32_dpp %6, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-          "v_add_f32_dpp %7, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-          "v_add_f32_dpp %5, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-          "v_add_f32_dpp %6, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-          "v_add_f32_dpp %4, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-          "v_add_f32_dpp %0, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-          "v_add_f32_dpp %0, %6, %6 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
-          "v_add_f32_dpp %4, %4, %4 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-          "s_nop 0\n\t"
-          "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-          "v_add_f32_dpp %4, %4, %4 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-          "s_nop 0\n\t"
-          "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
-          : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "=&v"(u0), "=&v"(u1),
-            "=&v"(u2));
-      // one atomic instruction: lane 0 of each bank adds t0 and lane 1 of each
-      // row t4, odd rows for record b (none for jb < 0)
+      const float total = pair_total(ha, hb, lane);
       const int j = (lane & 16) ? jb : ja;
-      if (out_field >= 0 && j >= 0) {
-        atomicAdd(grad2d + size_t(__float_as_uint(s2[j].w)) * kGradFloats + out_field,
-                  (lane & 1) ? t[4] : t[0]);
-      }
+      if (out_field >= 0 && j >= 0)
+        atomicAdd(grad2d + size_t(__float_as_uint(s2[j].w)) * kGradFloats + out_field, total);
     };
     auto walk = [&](auto check) {
       int j = int(cnt) - 1;
@@ -574,7 +604,7 @@ __device__ __forceinline__ void raster_bwd_tile(
         add_pair(ha, hb, 0, -1);
       }
     };
-    if (hi <= stop_min) walk(std::false_type{}); else walk(std::true_type{});
+    if (hi <= W.stop_min) walk(std::false_type{}); else walk(std::true_type{});
     hi = lo;
   }
 }
@@ -586,27 +616,181 @@ __global__ void __launch_bounds__(64) raster_bwd_kernel(
     const float* __restrict__ records, const uint32_t* __restrict__ values,
     const uint32_t* __restrict__ ranges, const DevView* __restrict__ views, int n_views,
     uint32_t n_tiles, const uint32_t* __restrict__ order, uint32_t* __restrict__ work,
-    uint32_t* __restrict__ grad_dirty,
-    const float* __restrict__ t_ws,
-    const uint32_t* __restrict__ ncontrib, const float* __restrict__ d_image,
-    const float* __restrict__ d_tfinal, const float* __restrict__ l1_image,
-    const float* __restrict__ l1_target, float l1_scale, float* __restrict__ grad2d) {
+    uint32_t* __restrict__ grad_dirty, const float* __restrict__ t_ws,
+    const uint32_t* __restrict__ ncontrib, BwdGradients G, float* __restrict__ grad2d) {
   __shared__ float4 s0[BATCH], s1[BATCH], s2[BATCH];
   __shared__ uint32_t s_pos[SPLIT > 1 ? BATCH : 1];   // positions of the kept records
   if (blockIdx.x == 0 && threadIdx.x == 0) *grad_dirty = 1u;
   for (uint32_t q = next_tile(work, true); q / SPLIT < n_tiles; q = next_tile(work, false)) {
     const uint32_t tile = order[q / SPLIT];
     const int band = int(q % SPLIT);
-    if (d_tfinal)
-      raster_bwd_tile<TW, TH, BATCH, SPLIT, true>(tile, band, s0, s1, s2, s_pos, records, values, ranges,
-                                                  views, n_views, t_ws, ncontrib, d_image,
-                                                  d_tfinal, l1_image, l1_target, l1_scale, grad2d);
+    if (G.d_tfinal)
+      raster_bwd_tile<TW, TH, BATCH, SPLIT, true>(tile, band, s0, s1, s2, s_pos, records, values,
+                                                  ranges, views, n_views, t_ws, ncontrib, G, grad2d);
     else
-      raster_bwd_tile<TW, TH, BATCH, SPLIT, false>(tile, band, s0, s1, s2, s_pos, records, values, ranges,
-                                                   views, n_views, t_ws, ncontrib, d_image,
-                                                   d_tfinal, l1_image, l1_target, l1_scale,
-                                                   grad2d);
+      raster_bwd_tile<TW, TH, BATCH, SPLIT, false>(tile, band, s0, s1, s2, s_pos, records, values,
+                                                   ranges, views, n_views, t_ws, ncontrib, G, grad2d);
   }
+}
+
+// Four bands a tile, a wavefront of one workgroup each.  The records are staged
+// once for all of them, 64 at a time; a wavefront walks those that may reach its
+// band (a scalar mask) and leaves their totals in LDS, and after the batch the
+// bands' totals are added in a fixed order, with one atomic add a record and
+// field, as for a tile of one wavefront.  Bands that each added their own totals
+// did so in any order: with more than two addends a sum depends on it in its last
+// bit, and gradients that cancel by a factor of a thousand and more in the chain
+// to the parameters changed in their fourth digit from run to run, in one of
+// twenty frames of 20,000 7-D in eight views of 160x120.  (Two bands a tile, in
+// larger frames, add their own: at most two addends a tile, as two tiles of half
+// the height have.  Sums in LDS there cost 8 %: 3250 tiles 76.7 -> 83.0 us.)
+// The next batch's records are on their way from memory while a batch is walked.
+// 64 tiles of a 3-D frame 34.8 us (32.4 with the bands' own atomics, one
+// wavefront a tile 87), 300 tiles 22.8 (21.3, 52), 1200 33.0 (32.9, 65).
+constexpr int kBands = 4, kBandBatch = 64, kBandThreads = 64 * kBands;
+
+struct BandShared {
+  float4 rec[3][kBandBatch];
+  float total[kBands][kBandBatch * kGradFloats];
+  uint32_t mask[kBands][2];        // the records of the batch that a band walked
+  uint32_t id[2][kBandBatch];      // record indices, of this batch and the next
+  uint32_t span[kBands];
+};
+
+template <bool HAS_DT>
+__device__ __forceinline__ void raster_bwd_bands(
+    uint32_t tile, BandShared& S, const float* __restrict__ records,
+    const uint32_t* __restrict__ values, const uint32_t* __restrict__ ranges,
+    const DevView* __restrict__ views, int n_views, const float* __restrict__ t_ws,
+    const uint32_t* __restrict__ ncontrib, const BwdGradients& G, float* __restrict__ grad2d) {
+  using Geom = TileGeom<16, 16, kBands>;
+  constexpr int PPL = Geom::PPL, RSTEP = Geom::RSTEP;
+  const int lane = threadIdx.x & 63, band = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const DevView& V = views[view_of_tile(views, n_views, tile)];
+  const uint32_t lt = tile - V.tile_base;
+  const int ty = int(lt) / V.tiles_x, tx = int(lt) - ty * V.tiles_x;
+  const int px = tx * 16 + lane % 16;
+  const int y0 = ty * 16 + band * Geom::ROWS, py0 = y0 + lane / 16;
+  const float fx = float(px) + 0.5f;
+  const float band_y0 = float(y0) + 0.5f, band_y1 = band_y0 + float(Geom::ROWS - 1);
+  const uint32_t start = ranges[2 * size_t(tile)];
+  BwdPixels<PPL> P;
+  const BwdSpan W = load_pixels<PPL, RSTEP, HAS_DT>(P, V, px, py0, t_ws, ncontrib, G);
+  if (lane == 0) S.span[band] = W.span;
+  __syncthreads();
+  uint32_t hi = 0;
+#pragma unroll
+  for (int b = 0; b < kBands; ++b) hi = max(hi, S.span[b]);
+  hi = __builtin_amdgcn_readfirstlane(hi);
+  // wavefronts 0 to 2 stage a 16-byte part of the records each, a record a lane
+  float4 next = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  uint32_t next_id = 0;
+  auto load = [&](uint32_t lo, uint32_t cnt) {
+    if (band < 3 && uint32_t(lane) < cnt) {
+      next_id = values[start + lo + uint32_t(lane)];
+      next = reinterpret_cast<const float4*>(records + size_t(next_id) * kRecFloats)[band];
+    }
+  };
+  auto store = [&](uint32_t cnt, uint32_t parity) {
+    if (band < 3 && uint32_t(lane) < cnt) {
+      float4 v = next;
+      if (band == 0) v.w = 2.0f * v.w;
+      if (band == 1) v.z = hw_log2(v.z);
+      S.rec[band][lane] = v;
+      if (band == 0) S.id[parity][lane] = next_id;
+    }
+  };
+  const int out_field = pair_field(lane);
+  uint32_t cnt = min(hi, uint32_t(kBandBatch)), lo = hi - cnt, parity = 0;
+  load(lo, cnt);
+  store(cnt, parity);
+  __syncthreads();
+  while (hi > 0) {
+    const uint32_t next_cnt = min(lo, uint32_t(kBandBatch)), next_lo = lo - next_cnt;
+    // the batch's records that may reach the band, among those before its span
+    bool keep = uint32_t(lane) < cnt && lo + uint32_t(lane) < W.span;
+    if (keep) {
+      Staged st;
+      st.g0 = S.rec[0][lane];
+      st.g1 = S.rec[1][lane];
+      keep = may_reach_rows(st, band_y0, band_y1);
+    }
+    const uint64_t mask = __ballot(keep);
+    if (lane < 2) S.mask[band][lane] = uint32_t(mask >> (32 * lane));
+    load(next_lo, next_cnt);
+    auto walk = [&](auto check) {
+      uint64_t left = mask;
+      auto take = [&]() {
+        const int j = 63 - __builtin_clzll(left);
+        left &= ~(1ull << j);
+        return j;
+      };
+      while (left != 0) {
+        const int ja = take(), jb = left != 0 ? take() : -1, jc = max(jb, 0);
+        // (both records' reads ahead of the first's sums)
+        const float4 a0 = S.rec[0][ja], a1 = S.rec[1][ja], a2 = S.rec[2][ja];
+        const float4 b0 = S.rec[0][jc], b1 = S.rec[1][jc], b2 = S.rec[2][jc];
+        __builtin_amdgcn_sched_barrier(0);
+        constexpr bool CHECK = decltype(check)::value;
+        float ha[5], hb[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        bwd_record<CHECK, PPL, RSTEP, HAS_DT>(P, a0, a1, a2, fx, py0, lo + uint32_t(ja), ha);
+        if (jb >= 0)   // (the odd one out is paired with zeros)
+          bwd_record<CHECK, PPL, RSTEP, HAS_DT>(P, b0, b1, b2, fx, py0, lo + uint32_t(jb), hb);
+        const float total = pair_total(ha, hb, lane);
+        const int j = (lane & 16) ? jb : ja;
+        if (out_field >= 0 && j >= 0) S.total[band][j * kGradFloats + out_field] = total;
+      }
+    };
+    if (min(hi, W.span) <= W.stop_min) walk(std::false_type{}); else walk(std::true_type{});
+    __syncthreads();
+    // the bands' totals, one record field a thread (all reads ahead of the sums)
+    constexpr int ENTRIES = kBandBatch * kGradFloats, ITEMS = (ENTRIES + kBandThreads - 1) / kBandThreads;
+    float part[ITEMS][kBands];
+    uint32_t id[ITEMS], walked[ITEMS][kBands];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      const int e = min(int(threadIdx.x) + i * kBandThreads, ENTRIES - 1), q = e / kGradFloats;
+      id[i] = S.id[parity][q];
+#pragma unroll
+      for (int b = 0; b < kBands; ++b) {
+        part[i][b] = S.total[b][e];
+        walked[i][b] = S.mask[b][q >> 5] >> (q & 31);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      const uint32_t e = threadIdx.x + uint32_t(i * kBandThreads), q = e / kGradFloats;
+      float sum = 0.0f;
+#pragma unroll
+      for (int b = 0; b < kBands; ++b) sum = (walked[i][b] & 1u) ? sum + part[i][b] : sum;
+      if (e < cnt * kGradFloats &&
+          ((walked[i][0] | walked[i][1] | walked[i][2] | walked[i][3]) & 1u) != 0u)
+        atomicAdd(grad2d + size_t(id[i]) * kGradFloats + (e - q * kGradFloats), sum);
+    }
+    parity ^= 1u;
+    store(next_cnt, parity);
+    __syncthreads();
+    hi = lo;
+    lo = next_lo;
+    cnt = next_cnt;
+  }
+}
+
+__global__ void __launch_bounds__(kBandThreads) raster_bwd_bands_kernel(
+    const float* __restrict__ records, const uint32_t* __restrict__ values,
+    const uint32_t* __restrict__ ranges, const DevView* __restrict__ views, int n_views,
+    const uint32_t* __restrict__ order, uint32_t* __restrict__ grad_dirty,
+    const float* __restrict__ t_ws, const uint32_t* __restrict__ ncontrib, BwdGradients G,
+    float* __restrict__ grad2d) {
+  __shared__ BandShared S;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *grad_dirty = 1u;
+  const uint32_t tile = order[blockIdx.x];
+  if (G.d_tfinal)
+    raster_bwd_bands<true>(tile, S, records, values, ranges, views, n_views, t_ws, ncontrib, G,
+                           grad2d);
+  else
+    raster_bwd_bands<false>(tile, S, records, values, ranges, views, n_views, t_ws, ncontrib, G,
+                            grad2d);
 }
 
 __global__ void reset_counter_kernel(uint32_t* __restrict__ c) {
@@ -630,13 +814,21 @@ struct RasterLaunch {
 // or four wavefronts a tile, each staging only the records that may reach its
 // band, shorten that chain.  Beyond the limits the records staged and tested
 // several times (and, backward, reduced several times) cost more than that
-// saves.  Measured on 16x16 tiles, one / two / four wavefronts a tile (us):
-//   forward   64 tiles 62 / 34 / 23, 1200 21 / 14 / 11, 1900 51 / 31 / 22,
-//             3072 43 / 27 / 24, 4108 68 / 43 / 46, 8160 59 / 58 / 67 and
-//             107 / 105 / 120, 14400 105 / 114 / 133
-//   backward  64 tiles 87 / 49 / 32, 1200 29 / 19 / 16, 1900 71 / 44 / 45 and
-//             111 / 67 / 47, 3072 61 / 45 / 53, 4108 99 / 97 / 129 and
-//             33 / 31 / 34, 8160 121 / 143 / 211
+// saves.  Measured on 16x16 tiles, one / two / four wavefronts a tile (us, 7-D or
+// 3-D where marked, and 6-D):
+//   forward   64 tiles (3-D) 62 / 34 / 23, 1200 46 / 26 / 20,
+//             2772 47 / 29 / 26 and 52 / 33 / 29, 3600 42 / 27 / 28 and 66 / 42 / 43,
+//             4480 46 / 32 / 35 and 56 / 39 / 42, 6600 51 / 45 / 50 and 59 / 53 / 60,
+//             8160 62 / 58 / 67 and 111 / 105 / 120, 10000 68 / 66 / 76 and
+//             77 / 78 / 89, 14400 (6-D) 118 / 126 / 147
+//   backward  64 tiles (3-D) 92 / 51 / 35, 1200 66 / 39 / 33, 1900 (3-D) 190 / 118 / 89
+//             and 87 / 55 / 59, 2166 61 / 45 / 45 and 80 / 59 / 61, 2772 68 / 54 / 59
+//             and 75 / 61 / 68, 3600 61 / 52 / 65 and 96 / 91 / 118, 4480 76 / 68 / 86
+//             and 94 / 85 / 111, 5440 89 / 85 / 111 and 117 / 114 / 153,
+//             6600 98 / 103 / 138
+// Backward, two stays ahead of one to about 5500 tiles; the line is drawn before,
+// as a record's sum over two bands that add their own totals has more addends in
+// no fixed order (see raster_bwd_bands).
 // A 32x16 tile takes two wavefronts in frames of any size, a lane then has four
 // pixels as in a 16x16 tile: forward 1800 tiles 75 / 50, 4080 102 / 80, backward
 // with the adjoint 160 / 114 and 266 / 230 (with 256 records a batch, whose LDS
@@ -694,14 +886,16 @@ template <int TW, int TH, int BATCH, int SPLIT = 1>
 static hipError_t raster_bwd_t(const RasterLaunch& g, uint32_t* grad_dirty, const float* records,
                                const uint32_t* values, const uint32_t* ranges,
                                const DevView* views, int n_views,
-                               const float* t_ws, const uint32_t* ncontrib, const float* d_image,
-                               const float* d_tfinal, const float* l1_image,
-                               const float* l1_target, float l1_scale, float* grad2d,
-                               hipStream_t st) {
-  hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, BATCH, SPLIT>), dim3(g.grid), dim3(64), 0, st,
-                     records, values, ranges, views, n_views, g.n_tiles, g.order, g.work,
-                     grad_dirty, t_ws, ncontrib, d_image, d_tfinal, l1_image, l1_target, l1_scale,
-                     grad2d);
+                               const float* t_ws, const uint32_t* ncontrib, const BwdGradients& G,
+                               float* grad2d, hipStream_t st) {
+  if constexpr (SPLIT == kBands)
+    hipLaunchKernelGGL(raster_bwd_bands_kernel, dim3(g.n_tiles), dim3(kBandThreads), 0, st, records,
+                       values, ranges, views, n_views, g.order, grad_dirty, t_ws, ncontrib, G,
+                       grad2d);
+  else
+    hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, BATCH, SPLIT>), dim3(g.grid), dim3(64), 0, st,
+                       records, values, ranges, views, n_views, g.n_tiles, g.order, g.work,
+                       grad_dirty, t_ws, ncontrib, G, grad2d);
   return hipGetLastError();
 }
 
@@ -763,8 +957,9 @@ hipError_t launch_raster_bwd(int tw, int th, int batch, uint32_t persistent_bloc
   const RasterLaunch g =
       raster_geometry(n_tiles, work, persistent_blocks, order,
                       band_limits(false, tw, th, batch), st);
+  const BwdGradients G{d_image, d_tfinal, l1_image, l1_target, l1_scale};
   UBS_TILE_DISPATCH(raster_bwd_t, g, grad_dirty, records, values, ranges, views, n_views, t_ws,
-                    ncontrib, d_image, d_tfinal, l1_image, l1_target, l1_scale, grad2d, st);
+                    ncontrib, G, grad2d, st);
 }
 
 }  // namespace ubs
