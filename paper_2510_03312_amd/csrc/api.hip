@@ -25,7 +25,7 @@ hipError_t launch_bin_count(const float* records, const uint8_t* live, const Dev
                             uint32_t slot_cap, DevStatus* status, float* grad2d, hipStream_t st);
 hipError_t launch_scan(const uint32_t* in, uint32_t n, uint32_t* tile_sums, uint32_t* out,
                        DevStatus* status, unsigned long long capacity, hipStream_t st,
-                       unsigned long long* total_out, uint32_t* order, uint32_t* order_hist);
+                       uint32_t* order, uint32_t* order_hist);
 uint64_t order_hist_words(uint64_t n_tiles);
 hipError_t launch_bin_emit(const float* records, const uint8_t* live, const DevView* views,
                            int n_views,
@@ -444,7 +444,7 @@ ubs_status ubs_bin_sort(const ubs_frame* frame, void* ws, uint64_t ws_bytes, voi
   stage_mark(frame, UBS_STAGE_BIN_COUNT, 1, s);
   stage_mark(frame, UBS_STAGE_SCAN, 0, s);
   // segment starts of the tiles; the total sets pairs_needed and overflow
-  UBS_HIP(launch_scan(tile_counts, n_tiles, sums, tile_cursor, status, cap, s, nullptr,
+  UBS_HIP(launch_scan(tile_counts, n_tiles, sums, tile_cursor, status, cap, s,
                       at<uint32_t>(ws, L.off_tile_order), at<uint32_t>(ws, L.off_order_hist)));
   stage_mark(frame, UBS_STAGE_SCAN, 1, s);
   stage_mark(frame, UBS_STAGE_BIN_EMIT, 0, s);

@@ -465,11 +465,11 @@ __global__ void __launch_bounds__(kScanThreads) scan_tile_sums_kernel(
   if (threadIdx.x == 0) tile_sums[blockIdx.x] = tot > 0xffffffffull ? 0xffffffffu : uint32_t(tot);
 }
 
-// One block scans all tile sums in place (exclusive) and writes the total
-// (and, for the pair scan, the overflow flag of the status block).
+// One block scans all tile sums in place (exclusive) and writes the total and
+// the overflow flag to the status block.
 __global__ void __launch_bounds__(kScanThreads) scan_tile_sums_scan_kernel(
     uint32_t* __restrict__ tile_sums, uint32_t n_tiles, DevStatus* __restrict__ status,
-    unsigned long long capacity, unsigned long long* __restrict__ total_out) {
+    unsigned long long capacity) {
   __shared__ uint32_t lds[8];
   unsigned long long carry = 0;
   for (uint32_t base = 0; base < n_tiles; base += kScanThreads) {
@@ -484,7 +484,6 @@ __global__ void __launch_bounds__(kScanThreads) scan_tile_sums_scan_kernel(
     status->pairs_needed = carry;
     status->overflow = carry > capacity ? 1u : 0u;
   }
-  if (threadIdx.x == 0 && total_out != nullptr) *total_out = carry;
 }
 
 __global__ void __launch_bounds__(kScanThreads) scan_apply_kernel(
@@ -695,7 +694,7 @@ constexpr uint32_t kSingleChunk = uint32_t(kSingleThreads * kSingleItems);
 __global__ void __launch_bounds__(kSingleThreads) scan_single_kernel(
     const uint32_t* __restrict__ in, uint32_t n, uint32_t* __restrict__ out,
     DevStatus* __restrict__ status, unsigned long long capacity,
-    unsigned long long* __restrict__ total_out, uint32_t* __restrict__ order) {
+    uint32_t* __restrict__ order) {
   static_assert(kSingleThreads == kOrderBins, "the tile order takes the scan's workgroup");
   constexpr int W = kSingleThreads / 64;
   __shared__ uint32_t s_wave[W];
@@ -768,7 +767,6 @@ __global__ void __launch_bounds__(kSingleThreads) scan_single_kernel(
     status->pairs_needed = total;
     status->overflow = total > capacity ? 1u : 0u;
   }
-  if (threadIdx.x == 0 && total_out != nullptr) *total_out = total;
   if (order != nullptr) {
     __shared__ uint32_t s_bins[kOrderBins];
     __shared__ uint32_t s_tot[kOrderBins / 64];
@@ -780,7 +778,7 @@ __global__ void __launch_bounds__(kSingleThreads) scan_single_kernel(
 // order_hist: order_hist_words(n) words for it.
 hipError_t launch_scan(const uint32_t* in, uint32_t n, uint32_t* tile_sums, uint32_t* out,
                        DevStatus* status, unsigned long long capacity, hipStream_t st,
-                       unsigned long long* total_out, uint32_t* order, uint32_t* order_hist) {
+                       uint32_t* order, uint32_t* order_hist) {
   // the tile order: by the scan's own workgroup up to kOrderOneRound tiles,
   // else by its kernels
   if (order != nullptr && n > kOrderOneRound) {
@@ -794,7 +792,7 @@ hipError_t launch_scan(const uint32_t* in, uint32_t n, uint32_t* tile_sums, uint
   }
   if (n <= kSingleScanMax) {
     hipLaunchKernelGGL(scan_single_kernel, dim3(1), dim3(kSingleThreads), 0, st, in, n, out,
-                       status, capacity, total_out, order);
+                       status, capacity, order);
     return hipGetLastError();
   }
   const uint32_t n_tiles = (n + kScanTile - 1) / kScanTile;
@@ -802,7 +800,7 @@ hipError_t launch_scan(const uint32_t* in, uint32_t n, uint32_t* tile_sums, uint
     hipLaunchKernelGGL(scan_tile_sums_kernel, dim3(n_tiles), dim3(kScanThreads), 0, st, in, n,
                        tile_sums);
   hipLaunchKernelGGL(scan_tile_sums_scan_kernel, dim3(1), dim3(kScanThreads), 0, st, tile_sums,
-                     n_tiles, status, capacity, total_out);
+                     n_tiles, status, capacity);
   if (n_tiles > 0)
     hipLaunchKernelGGL(scan_apply_kernel, dim3(n_tiles), dim3(kScanThreads), 0, st, in, n,
                        tile_sums, out);

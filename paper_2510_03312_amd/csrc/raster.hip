@@ -281,24 +281,6 @@ __global__ void __launch_bounds__(64) raster_fwd_kernel(
                                                     t_ws, t_user, ncontrib);
 }
 
-// Sums over each 16-lane row by DPP row rotations (by 1, 2, 4, 8), of N
-// values at once: every lane of a row ends with the row's totals.  A rotation
-// has no out-of-row source lane, so each step is one DPP add.
-template <int CTRL>
-__device__ __forceinline__ float dpp_row(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
-}
-template <int N>
-__device__ __forceinline__ void row_sum_all(float* v) {
-#pragma unroll
-  for (int q = 0; q < N; ++q) v[q] += dpp_row<0x121>(v[q]);
-#pragma unroll
-  for (int q = 0; q < N; ++q) v[q] += dpp_row<0x122>(v[q]);
-#pragma unroll
-  for (int q = 0; q < N; ++q) v[q] += dpp_row<0x124>(v[q]);
-#pragma unroll
-  for (int q = 0; q < N; ++q) v[q] += dpp_row<0x128>(v[q]);
-}
 // Lane exchanges of gfx950: swap_halves(a, b) returns (a with its upper 32
 // lanes replaced by b's lower 32, b with its lower 32 replaced by a's upper
 // 32); swap_rows(a, b) does the same between a's odd rows and b's even rows
