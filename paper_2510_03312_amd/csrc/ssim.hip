@@ -26,10 +26,10 @@
 // pass, in which a row's value goes into the eleven outputs it belongs to: ten
 // registers a plane and column that shift by one as they are added to
 // (acc[j] = g h + acc[j + 1]).  SSIM depends on the second moments of x and y
-// through their sum and their covariance, so four planes are windowed, x, y,
-// x^2 + y^2 and (x - y)^2 (see ssim_point).  No barriers.  kTileH: 1080p gives
-// three wavefronts per SIMD; 24 and 32 rows have fewer halo rows but leave the
-// SIMDs unevenly loaded (fwd 59 and 66, bwd 54 and 104 us).
+// through their sum only, so four planes are windowed, x, y, x^2 + y^2 and
+// x y.  No barriers.  kTileH: 1080p gives three wavefronts per SIMD; 24 and 32
+// rows have fewer halo rows but leave the SIMDs unevenly loaded (fwd 59 and
+// 66, bwd 54 and 104 us).
 // Bound by instruction issue, 79 % of the cycles forward and 57 % backward
 // (which reads 133 MB in its 48 us): 1080p 89 -> 51 us forward, 85 -> 48 us
 // backward against 16x16 tiles with an LDS patch per channel (676 columns of
@@ -118,22 +118,15 @@ __device__ __forceinline__ SsimView ssim_view_of_tile(const SsimViews& vs, uint3
   return v;
 }
 
-// S of one pixel and channel from its windowed x, y, x^2 + y^2 and (x - y)^2; d:
-// its partials with respect to m_x, s_xx and s_xy, times scale.  2 s_xy is taken
-// as s_xx + s_yy less the variance of x - y: the rounding of x^2 + y^2 is then the
-// same in numerator and denominator, and S loses no digits where the images are
-// alike, which is what the gradient's error came from: 1080p with noise of 0.1
-// 4.0e-6 from five planes x, y, x^2, y^2, x y, 4.1e-6 from x^2 + y^2 and x y,
-// 3.2e-6 this way, smooth images with noise of 0.01 1.5e-5, 1.8e-5 and 7.3e-6
-// (relative L2 error against float64; 6.3e-6, 6.5e-6 and 6.7e-6 where one is
-// about the negative of the other).
+// S of one pixel and channel from its windowed x, y, x^2 + y^2 and x y; d: its
+// partials with respect to m_x, s_xx and s_xy, times scale.
 __device__ __forceinline__ float ssim_point(const float (&st)[4], float scale, float (&d)[3]) {
   const float mx = st[0], my = st[1];
   const float m2 = mx * mx + my * my;
   const float a1 = 2.0f * mx * my + kC1;
+  const float a2 = 2.0f * (st[3] - mx * my) + kC2;
   const float b1 = m2 + kC1;
-  const float b2 = __builtin_fmaf(-my, my, __builtin_fmaf(-mx, mx, st[2])) + kC2;
-  const float a2 = b2 - __builtin_fmaf(my - mx, mx - my, st[3]);
+  const float b2 = (st[2] - m2) + kC2;
   const float ib = 1.0f / (b1 * b2);
   const float ib1 = b2 * ib, ib2 = b1 * ib;
   const float S = a1 * a2 * ib;
@@ -163,18 +156,13 @@ __device__ __forceinline__ float column_step(float (&acc)[kTaps - 1], const Ssim
   return out;
 }
 
-// The taps from the outermost in, the smallest first: partial sums stay small
-// until the last ones, and so does their rounding.
-__device__ __forceinline__ constexpr int tap(int k) { return k & 1 ? kTaps - 1 - k / 2 : k / 2; }
-
 // The row's window sums of a lane's two columns, of one staged plane: twelve
-// values, v[5] and v[6] are the columns' own, read in the order of the taps.
+// values, v[5] and v[6] are the columns' own.
 __device__ __forceinline__ void row_pass(const float* row, int lane, const SsimTaps& t,
                                          float (&v)[kTaps + 1], float (&h)[2]) {
   const float2* p = reinterpret_cast<const float2*>(row) + lane;
 #pragma unroll
-  for (int q = 0; q < (kTaps + 1) / 2; ++q) {
-    const int k = q & 1 ? (kTaps - 1) / 2 - q / 2 : q / 2;
+  for (int k = 0; k < (kTaps + 1) / 2; ++k) {
     const float2 x = p[k];
     v[2 * k] = x.x;
     v[2 * k + 1] = x.y;
@@ -183,7 +171,7 @@ __device__ __forceinline__ void row_pass(const float* row, int lane, const SsimT
   for (int c = 0; c < 2; ++c) {
     h[c] = t.g[0] * v[c];
 #pragma unroll
-    for (int k = 1; k < kTaps; ++k) h[c] += t.g[tap(k)] * v[c + tap(k)];
+    for (int k = 1; k < kTaps; ++k) h[c] += t.g[k] * v[c + k];
   }
 }
 
@@ -280,7 +268,7 @@ __global__ void __launch_bounds__(kSsimThreads) ssim_fwd_kernel(
         row_of[0][i] = x;
         row_of[1][i] = y;
         row_of[2][i] = x * x + y * y;
-        row_of[3][i] = (x - y) * (x - y);
+        row_of[3][i] = x * y;
       }
     wave_order();
     if (row + 2 < n_rows) load(in_row, row + 2);
@@ -459,7 +447,7 @@ __device__ __forceinline__ void window_16x16(float (*in)[kSsimP][kSsimP],
     for (int o = 0; o < kSsimRun; ++o) {
       float acc = 0.0f;
 #pragma unroll
-      for (int k = 0; k < kTaps; ++k) acc += t.g[tap(k)] * v[o + tap(k)];
+      for (int k = 0; k <= 2 * kSsimR; ++k) acc += t.g[k] * v[o + k];
       tmp[q][r][c0 + o] = acc;
     }
   }
@@ -475,7 +463,7 @@ __device__ __forceinline__ void window_16x16(float (*in)[kSsimP][kSsimP],
     for (int o = 0; o < kSsimRun; ++o) {
       float acc = 0.0f;
 #pragma unroll
-      for (int k = 0; k < kTaps; ++k) acc += t.g[tap(k)] * v[o + tap(k)];
+      for (int k = 0; k <= 2 * kSsimR; ++k) acc += t.g[k] * v[o + k];
       in[q][r0 + o][c] = acc;
     }
   }
@@ -501,7 +489,7 @@ __global__ void __launch_bounds__(NCH * kFewThreads) ssim_fwd_few_kernel(
     SsimViews views, const float* __restrict__ image, const float* __restrict__ target,
     SsimTaps taps, float scale, float* __restrict__ dstat, uint32_t n_pixels,
     double* __restrict__ tile_sums) {
-  __shared__ float s_all[NCH][4][kSsimP][kSsimP];   // x, y, x^2 + y^2, (x - y)^2
+  __shared__ float s_all[NCH][4][kSsimP][kSsimP];   // x, y, x^2 + y^2, x y
   __shared__ float s_tmp[NCH][4][kSsimP][kSsimTmpW];
   __shared__ double s_red[2][4 * NCH];
   const uint32_t tile = blockIdx.x;
@@ -527,7 +515,7 @@ __global__ void __launch_bounds__(NCH * kFewThreads) ssim_fwd_few_kernel(
       s_in[0][pr][pc] = a;
       s_in[1][pr][pc] = b;
       s_in[2][pr][pc] = a * a + b * b;
-      s_in[3][pr][pc] = (a - b) * (a - b);
+      s_in[3][pr][pc] = a * b;
     }
     __syncthreads();
     const float l1 = fabsf(s_in[0][r + kSsimR][c + kSsimR] - s_in[1][r + kSsimR][c + kSsimR]);
