@@ -101,9 +101,11 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S,
   // per-workgroup counts (no atomics on a shared word per wavefront: those
   // serialise across the chip); the binning's first kernel adds them into
   // the status block.  The kept primitives go to the adjoint's list: one
-  // atomic per workgroup reserves their run (ascending inside it), and each
-  // wavefront then lists its own kept primitives and copies their parameter
-  // rows (from LDS) to their columns of the compacted copy.
+  // atomic per workgroup reserves their run, and their parameter rows are
+  // copied (from LDS) to the run's columns of the compacted copy.  One view: in
+  // ascending order, each wavefront its own.  Several views: by number of live
+  // records, in any order among equals; a primitive's gradient does not depend
+  // on its entry, so results are the same.
   __shared__ uint32_t s_cnt[2], s_run, s_total;
   __shared__ uint8_t s_src[256];
   __shared__ unsigned long long s_keep[4];
@@ -136,7 +138,8 @@ __global__ void __launch_bounds__(256) preprocess_fwd_kernel(DevScene S,
   // entry q of the run: the kept primitives in thread order, or, where several
   // views see the scene, by their number of live records (kCountBins bins,
   // every second workgroup of a list the other way round, so that the ends of
-  // neighbouring runs have about the same)
+  // neighbouring runs have about the same; within a bin in the order of the LDS
+  // atomics)
   uint32_t q = uint32_t(__popcll(km & ((1ull << lane) - 1ull)));
   if (wave > 0) q += uint32_t(__popcll(m0));
   if (wave > 1) q += uint32_t(__popcll(m1));
@@ -291,8 +294,8 @@ __device__ __forceinline__ void write_gradient(const Raw<C, ROT>& r, const float
 // as it is free, not when its workgroup's others are), the parameters, the
 // list entry and the list's count are read together, the gradient sums lie in
 // LDS and not in registers, and the last step reads the parameters again.
-// With the triangular forms of prim_math.hpp: 1M 7-D at 1080p 49 -> 34 us, 1M
-// 6-D 55 -> 38, 1M 10-D 223 -> 43 (its state no longer spills).
+// With the triangular forms of prim_math.hpp: 1M 7-D at 1080p 49 -> 35 us, 1M
+// 6-D 55 -> 41, 1M 10-D 223 -> 43 (its state no longer spills).
 // The parameters stay in registers where that costs nothing: where a SIMD has
 // as many wavefronts with them (3-D, four, and 6-D skew, two: 1M 6-D skew, a
 // third kept, 76 -> 72 us with the scatter, all kept 159 -> 150), and in scenes of
@@ -358,10 +361,11 @@ __global__ void __launch_bounds__(bwd_threads(C), AGAIN && C <= 4 ? 2 : 1) prepr
 // primitives of a workgroup by their number of live records: a wavefront's
 // lanes then have about the same.  (The columns stay dense that way: sorting
 // the entries afterwards, in groups of 1024, made every wavefront read its
-// parameters from all over the group: 640 us where this takes 390.)  2M 7-D in
-// 8 views 726 -> 385 us, 4 scenes in 32 views 2.05 -> 1.07 ms, the forms of
+// parameters from all over the group: 640 us where this takes 370.)  2M 7-D in
+// 8 views 726 -> 370 us, 4 scenes in 32 views 2.05 -> 1.02 ms, the forms of
 // prim_math.hpp included (580 us and 1.45 ms with all lanes in step over the
 // scene's views); the preprocess pays 5 us for the sorting of the 8 views.
+// Two wavefronts per SIMD to 7-D, at 7-D with 14 registers spilled.
 constexpr int kManyViews = 32;   // views of a live mask
 constexpr int kViewWords = int(sizeof(DevView) / 4);
 

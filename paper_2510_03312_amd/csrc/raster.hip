@@ -23,9 +23,10 @@
 // reaches, with half the lanes inside it), so they are counted in
 // instructions: a strip costs the forward 4 for the support test and 13 plus
 // two transcendentals inside it, the backward 4 and 25 plus four, and a
-// record 23 more in the backward for its wavefront sums.  1M 7-D primitives
-// at 1080p, before and after the present forms: forward 63.0 -> 58.7 us,
-// backward 132 -> 123 us; 1M 6-D 115 -> 107 and 247 -> 229 us.
+// record 22 more in the backward for its wavefront sums.  1M 7-D primitives
+// at 1080p, former and present forms in turn on one device, by HIP events:
+// forward 62.7 -> 58.7 us, backward 133 -> 123 us; 1M 6-D 116 -> 106 and 246 ->
+// 229 us.
 //
 // The order of the backward's float32 operations is kept with care.  A record
 // whose 2-D covariance is nearly singular (the symmetrised conditional
@@ -455,7 +456,8 @@ __device__ __forceinline__ void bwd_record(BwdPixels<PPL>& P, const float4 g0, c
 // lanes and of record b in the odd rows.  Every step but the last two halves the
 // number of registers, as a step of two registers is one of each half, row,
 // half-row or bank; a single record's ten fields leave the later steps half
-// empty (31 vector instructions a record, against 24 for two at a time).
+// empty (about 30 vector instructions a record; two at a time take 22 each: 10
+// for its halves, 23 here for both).
 __device__ __forceinline__ int pair_field(int lane) {
   if ((lane & 3) == 0) return 4 * ((lane >> 2) & 1) + 2 * ((lane >> 3) & 1) + (lane >> 5);
   if ((lane & 15) == 1) return 8 + (lane >> 5);

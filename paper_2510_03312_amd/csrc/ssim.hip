@@ -27,7 +27,10 @@
 // registers a plane and column that shift by one as they are added to
 // (acc[j] = g h + acc[j + 1]).  SSIM depends on the second moments of x and y
 // through their sum only, so four planes are windowed, x, y, x^2 + y^2 and
-// x y.  No barriers.  kTileH: 1080p gives three wavefronts per SIMD; 24 and 32
+// x y.  (The sum's rounding is that of a larger number than either square's: the
+// gradient's error against float64 is 4.1e-6 at 1080p with noise of 0.1, with
+// five planes 4.0e-6, and 1.8e-5 against 1.5e-5 on smooth images with noise of
+// 0.01.)  No barriers.  kTileH: 1080p gives three wavefronts per SIMD; 24 and 32
 // rows have fewer halo rows but leave the SIMDs unevenly loaded (fwd 59 and
 // 66, bwd 54 and 104 us).
 // Bound by instruction issue, 79 % of the cycles forward and 57 % backward
